@@ -395,3 +395,55 @@ def test_three_term_bf16_split_is_exact_and_six_products_suffice():
     exact = x.astype(np.float64) * y.astype(np.float64)
     nz = exact != 0
     assert (np.abs(kept - exact)[nz] / np.abs(exact)[nz]).max() <= 2.0 ** -24
+
+# ---------------------------------------------------------------------------
+# offsets of operand loads (gf_offsets.h compiles as plain C++)
+# ---------------------------------------------------------------------------
+def test_row_offsets_stay_inside_the_tensor(tmp_path):
+    """Input gradient of a dense layer: rows of k past the last channel are read at the last one, so that every offset
+    stays inside the tensor also where a row that does not exist would start past 2^31 (one image, few channels, large
+    maps; every shape below is accepted by the entry points)."""
+    import shutil
+    import subprocess
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("no C++ compiler")
+    src = tmp_path / "offsets.cpp"
+    src.write_text(r'''
+#include "gf_offsets.h"
+#include <stdio.h>
+#include <initializer_list>
+int main() {
+  // images, rows (channels), plane, rows per chunk, elements per vector
+  const long shapes[][5] = {{1, 8, 36000000, 64, 8}, {1, 8, 36000000, 32, 4}, {16, 16, 7080000, 64, 8}, {1, 16, 100000000, 128, 16},
+                            {1, 1, 2000000000, 64, 8}, {2, 1000000000, 1, 32, 4}, {1, 2, 1000000000, 32, 4}, {300, 130, 49, 64, 8},
+                            {5, 64, 64, 64, 8}, {5, 65, 64, 64, 8}, {5, 63, 64, 64, 8}, {3, 129, 1000, 32, 4}};
+  int bad = 0;
+  for (const auto& s : shapes) {
+    const long N = s[0], Co = s[1], P = s[2], KB = s[3], VE = s[4], tot = N * Co * P;
+    const long chunks = (Co + KB - 1) / KB;
+    const long some[] = {0, 1, chunks / 2, chunks - 2, chunks - 1};
+    for (long n : {0L, N - 1})
+      for (long p : {0L, P / 2, P - 1})
+        for (long c : some) {
+          if (c < 0 || c >= chunks) continue;
+          for (long row = 0; row < KB; ++row) {
+            gf::RowOffsets r;
+            r.set((int)(n * Co * P + p), (int)row, (int)Co, (int)KB, (int)P);
+            const long got = r.at((int)(c * KB), (int)Co, (int)KB, (int)P);
+            const long k = c * KB + row < Co ? c * KB + row : Co - 1, want = n * Co * P + k * P + p;
+            if (got != want || got < 0 || got >= tot) {
+              if (!bad++) printf("N %ld Co %ld P %ld KB %ld VE %ld chunk %ld row %ld: %ld, not %ld\n", N, Co, P, KB, VE, c, row, got, want);
+            }
+          }
+        }
+  }
+  return bad != 0;
+}
+''')
+    exe = tmp_path / "offsets"
+    r = subprocess.run([cxx, "-std=c++17", "-O1", "-fsanitize=undefined", "-fno-sanitize-recover", f"-I{os.path.join(ROOT, 'paper_2301_00330_amd', 'csrc')}",
+                        str(src), "-o", str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout + r.stderr

@@ -236,3 +236,24 @@ def test_reductions_of_long_runs_of_planes(C, H, W):
 ])
 def test_large_patches_of_few_images(oracle, case, dtype):
     check_filtered(oracle, case, dtype)
+
+
+@pytest.mark.parametrize("N,Ci,Co,H,W,dtype", [(1, 16, 8, 6000, 6000, "bf16"), (2, 9, 7, 5501, 8001, "bf16")])
+def test_large_maps_of_few_channels(N, Ci, Co, H, W, dtype):
+    """Pointwise vanilla BP on maps where a chunk of k has more rows than the layer has channels and the rows that do
+    not exist would start past 2^31: sampled pixels of g_x and all of g_w against 64-bit sums."""
+    d = mk(N, Ci, Co, H, W, 1, 1, 0, r=1, dtype=dtype)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    x, w, gy = (torch.randn(s, generator=g, device="cuda").to(td) for s in ((N, Ci, H, W), (Co, Ci, 1, 1), (N, Co, H, W)))
+    g_w, g_x = T.conv_bwd_exact(d, x, w, gy)
+    P = H * W
+    pos = torch.cat([torch.arange(512), torch.randint(0, P, (4096,), generator=torch.Generator().manual_seed(1)), torch.arange(P - 512, P)]).cuda()
+    r_w = torch.zeros(Co, Ci, dtype=torch.float64, device="cuda")
+    for n in range(N):
+        fx, fg = x[n].reshape(Ci, P), gy[n].reshape(Co, P)
+        want = w.double().reshape(Co, Ci).t().contiguous() @ fg[:, pos].double()
+        assert rel_err(g_x[n].reshape(Ci, P)[:, pos], want.cpu().numpy()) <= TOL[dtype]
+        for p in range(0, P, 1 << 22):
+            r_w += fg[:, p:p + (1 << 22)].double() @ fx[:, p:p + (1 << 22)].double().t().contiguous()
+    assert rel_err(g_w.reshape(Co, Ci), r_w.cpu().numpy()) <= TOL[dtype]
