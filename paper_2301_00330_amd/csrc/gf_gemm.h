@@ -17,14 +17,38 @@ template <class T> struct El;
 // elements per 128-byte chunk / 16-byte vector, matrix steps per chunk, bytes of an element (of a term) in LDS, accumulator
 template <> struct El<float> { static constexpr int KB = 32, VE = 4, KS = 2, EB = 2; typedef f32x16 acc; };
 template <> struct El<bf16_t> { static constexpr int KB = 64, VE = 8, KS = 4, EB = 2; typedef f32x16 acc; };
+// fp32 operands multiplied as they are, v_mfma_f32_32x32x2_f32 (a tile's second pass: see split_failed)
+struct raw_f32 { float v; };
+template <> struct El<raw_f32> { static constexpr int KB = 32, VE = 4, KS = 4, EB = 4; typedef f32x16 acc; };
+template <> struct Unal<raw_f32> : Unal<float> {};
 template <> struct El<int8_t> { static constexpr int KB = 128, VE = 16, KS = 4, EB = 1; typedef i32x16 acc; };
 
-template <class T> constexpr int terms_of() { return sizeof(T) == 4 ? 3 : 1; }   // bf16 terms of an operand
+// the lane's number in the block; in a second pass as a value of its own, so that nothing derived from it is kept in
+// registers through the first
+template <class T>
+__device__ __forceinline__ int lane_id() {
+  int t = threadIdx.x;
+  if (__is_same(T, raw_f32)) asm volatile("" : "+v"(t));
+  return t;
+}
+
+template <class T> constexpr bool is_split() { return __is_same(T, float); }
+template <class T> constexpr int terms_of() { return is_split<T>() ? 3 : 1; }   // bf16 terms of an operand
 
 // Accumulators of a wave: TM x TN tiles of 32 x 32; row of such a tile that element v of lane
 // `lane` holds (the column is lane % 32).  Tile (i, j) of wave (wm, wn) covers rows 64 i + 32 wm .. of the block
 // tile and columns 64 j + 32 wn .., so 64 consecutive rows are complete per i.
 __device__ __forceinline__ int acc_row(int lane, int v) { return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); }
+
+template <class A, int TM, int TN>
+__device__ __forceinline__ void zero_acc(A (&acc)[TM][TN]) {
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
+}
 
 // Four fp32 values as three bf16 terms, x = t0 + t1 + t2 exactly: every term is the nearest bf16 of what the
 // earlier ones leave (|t1| <= 2^-8 |x|, |t2| <= 2^-16 |x|), both remainders are exact in fp32, and the second
@@ -32,9 +56,13 @@ __device__ __forceinline__ int acc_row(int lane, int v) { return 8 * (v >> 2) + 
 // that are dropped stay below 2^-23 |x y| (2^-24 at most and 2^-27 rms over random operands): the size of one
 // rounding of the fp32 accumulation.  One packed
 // conversion per pair of values and term, two shifts / masks and two subtractions per pair and remainder.
+// The split is not exact for every value.  Below about 2^-110 the last term reaches under the smallest bf16: the
+// second remainder then has bits set below the upper 16, and `low` collects them (one instruction per pair).  An
+// infinity, a NaN or a value that rounds past the largest bf16 (3.39e38) leaves inf - inf in the remainders, and every sum it
+// enters is not finite.
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void split3(const u32x4_t& v, uint2 (&t)[3]) {
+__device__ __forceinline__ void split3(const u32x4_t& v, uint2 (&t)[3], uint32_t& low) {
   f32x2_t a = {__uint_as_float(v.x), __uint_as_float(v.y)}, b = {__uint_as_float(v.z), __uint_as_float(v.w)};
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
@@ -47,6 +75,23 @@ __device__ __forceinline__ void split3(const u32x4_t& v, uint2 (&t)[3]) {
       b.x -= bf_lo(pb); b.y -= bf_hi(pb);
     }
   }
+  low |= __float_as_uint(a.x) | __float_as_uint(a.y);
+  low |= __float_as_uint(b.x) | __float_as_uint(b.y);
+  asm volatile("" : "+v"(low));   // now: else the remainders stay in registers
+}
+
+// True in all lanes of a block if a product of one of its lanes may not be what fp32 operands give: the block then takes
+// its K slab again with fp32 matrix instructions (raw_f32).  One look at the accumulators per block and slab.
+template <int TM, int TN>
+__device__ __forceinline__ bool split_failed(const f32x16 (&acc)[TM][TN], uint32_t low) {
+  float s = 0.f;   // x * 0 is 0, or NaN for an infinity or a NaN
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) s = __builtin_fmaf(acc[i][j][v], 0.f, s);
+  return __syncthreads_or((low & 0xffffu) != 0 || s != 0.f) != 0;
 }
 
 // Barrier between the waves of a block that orders LDS traffic only.  __syncthreads() also waits
@@ -131,14 +176,21 @@ __device__ __forceinline__ void mul_all(const uint4 (&fa)[TM][terms_of<T>()],
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-      if constexpr (sizeof(T) == 4) {   // smallest products first
+      if constexpr (is_split<T>()) {   // smallest products first
         acc[i][j] = mma32(fa[i][2], fb[j][0], acc[i][j]);
         acc[i][j] = mma32(fa[i][0], fb[j][2], acc[i][j]);
         acc[i][j] = mma32(fa[i][1], fb[j][1], acc[i][j]);
         acc[i][j] = mma32(fa[i][1], fb[j][0], acc[i][j]);
         acc[i][j] = mma32(fa[i][0], fb[j][1], acc[i][j]);
+        acc[i][j] = mma32(fa[i][0], fb[j][0], acc[i][j]);
+      } else if constexpr (__is_same(T, raw_f32)) {
+        const u32x4_t x = {fa[i][0].x, fa[i][0].y, fa[i][0].z, fa[i][0].w}, y = {fb[j][0].x, fb[j][0].y, fb[j][0].z, fb[j][0].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(x[e]), __uint_as_float(y[e]), acc[i][j], 0, 0, 0);
+      } else {
+        acc[i][j] = mma32(fa[i][0], fb[j][0], acc[i][j]);
       }
-      acc[i][j] = mma32(fa[i][0], fb[j][0], acc[i][j]);
     }
 }
 
@@ -146,19 +198,20 @@ __device__ __forceinline__ void mul_all(const uint4 (&fa)[TM][terms_of<T>()],
 // the four rows (codes: eight) that a transposing read takes together fall into different banks.
 template <class T, int C>
 __device__ __forceinline__ int swz(int k) {
+  if (El<T>::EB == 4) return 0;
   const int r = El<T>::EB == 2 ? k : k >> 1;
   return C == 64 ? (r >> 1) & 1 : r & 3;
 }
 
 // vector cv of row k into such a tile (fp32: into the three term tiles)
 template <class T, int C>
-__device__ __forceinline__ void put_row(unsigned char* tile, int k, int cv, const u32x4_t& v) {
+__device__ __forceinline__ void put_row(unsigned char* tile, int k, int cv, const u32x4_t& v, uint32_t& low) {
   constexpr int VE = El<T>::VE, VPB = 32 / VE;   // vectors per block of 32 columns
   constexpr int EB = El<T>::EB;
   unsigned char* d = tile + k * (C * EB) + (((cv / VPB) ^ swz<T, C>(k)) * VPB + cv % VPB) * (VE * EB);
-  if constexpr (sizeof(T) == 4) {
+  if constexpr (is_split<T>()) {
     uint2 t[3];
-    split3(v, t);
+    split3(v, t, low);
 #pragma unroll
     for (int q = 0; q < 3; ++q) *reinterpret_cast<uint2*>(d + q * (El<T>::KB * C * 2)) = t[q];
   } else {
@@ -167,12 +220,15 @@ __device__ __forceinline__ void put_row(unsigned char* tile, int k, int cv, cons
 }
 
 // the operand of one MFMA -- lane: column c0 + lane % 32, k = 16 ks + 8 (lane / 32) .. + 7, codes: 32 ks + 16 (lane / 32)
-// .. + 15 -- from such a tile.  ds_read_b64_tr_b16: sixteen lanes read a block of 4 x 16 and each gets one column of
+// .. + 15; fp32 as it is: 8 ks + 4 (lane / 32) .. + 3 -- from such a tile.  ds_read_b64_tr_b16: sixteen lanes read a block of 4 x 16 and each gets one column of
 // four, lanes 4 r .. 4 r + 3 pointing to row r; ds_read_b64_tr_b8: 8 x 16, columns of eight, lanes 2 r and 2 r + 1.
 template <class T, int C>
 __device__ __forceinline__ uint4 frag_tr(const unsigned char* tile, int ks, int c0, int lane) {
   uint2 a, b;
-  if constexpr (El<T>::EB == 2) {
+  if constexpr (El<T>::EB == 4) {
+    const uint32_t* p = reinterpret_cast<const uint32_t*>(tile) + (ks * 8 + 4 * (lane >> 5)) * C + c0 + (lane & 31);
+    return make_uint4(p[0], p[C], p[2 * C], p[3 * C]);
+  } else if constexpr (El<T>::EB == 2) {
     typedef short s16x4 __attribute__((ext_vector_type(4)));
     typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
     const int k = ks * 16 + 8 * (lane >> 5) + ((lane & 15) >> 2);

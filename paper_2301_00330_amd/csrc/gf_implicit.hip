@@ -271,13 +271,13 @@ struct XArgs {
 
 template <class T, int TM, int TN>
 struct XTile {
-  static constexpr bool SPLIT = sizeof(T) == 4;
+  static constexpr bool SPLIT = is_split<T>();
   static constexpr int TERMS = terms_of<T>();
   static constexpr int KB = El<T>::KB, VE = El<T>::VE;
   static constexpr int BM = 64 * TM, BN = 64 * TN;
   static constexpr int RW = SPLIT ? 64 + 16 : 128 + 16;   // weight gradient: bytes of one K-major row of a term
   static constexpr int WA = BM * RW, WB = BN * RW;
-  static constexpr int DA = KB * BM * 2, DB = KB * BN * 2;  // input gradient: [k][columns] bf16
+  static constexpr int DA = KB * BM * El<T>::EB, DB = KB * BN * El<T>::EB;  // input gradient: [k][columns]
   static constexpr int kW = TERMS * (WA + WB), kD = TERMS * (DA + DB);
   static constexpr int SC = BN + VE;                        // element stride of the staged result
   static constexpr int kE = 64 * SC * (int)sizeof(T);
@@ -295,49 +295,22 @@ struct XSet {
   uint32_t mb;
 };
 
-template <class T, int TM, int TN>
-__device__ __forceinline__ void zero_acc(f32x16 (&acc)[TM][TN]) {
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-}
-
 // register sets of the K loop
-template <int TM, int TN> constexpr int xsets_of() { return TM * TN == 1 ? 4 : 2; }
+template <class T, int TM, int TN> constexpr int xsets_of() { return TM * TN == 1 && !__is_same(T, raw_f32) ? 4 : 2; }
 
+// acc += g_y[rows m0 ..][chunk] * x[rows n0 .., moved by the tap][chunk]^T over the chunks of a K slab
 template <class T, int TM, int TN>
-__device__ __forceinline__ void xwgrad_block(const XArgs& a, int L, unsigned char* smem) {
+__device__ __forceinline__ void xw_mainloop(const XArgs& a, int t, int m0, int n0, int kc0, int kc1, unsigned char* smem,
+                                            f32x16 (&acc)[TM][TN], uint32_t& low) {
   using X = XTile<T, TM, TN>;
   constexpr int VE = X::VE, LA = 2 * TM, LB = 2 * TN;
   typedef XSet<LA, LB> Set;
-  // The hardware hands consecutive blocks to the eight XCDs in turn; with eight or more K slabs block L works on
-  // slab (L % 8) + 8 * (..), so that all taps and tiles of a slab share one XCD's L2 and each XCD touches an eighth
-  // of x and g_y.
-  int z, rest;
-  if (a.xcd_slabs) {
-    const int idx = L >> 3;
-    const int zl = (int)a.d_r.div((uint32_t)idx);
-    z = (L & 7) + 8 * zl;
-    rest = idx - zl * a.R;
-  } else {
-    z = (int)a.d_r.div((uint32_t)L);
-    rest = L - z * a.R;
-  }
-  if (z >= a.nz) return;  // uniform for the block
-  const int t = (int)a.d_tiles.div((uint32_t)rest), tile = rest - t * a.tiles;
-  const int by = (int)a.d_tx.div((uint32_t)tile), bx = tile - by * a.tx;
   const int delta = a.tapw ? a.tapw[t] : 0;
-  const int m0 = by * X::BM, n0 = bx * X::BN;
-  const int kc0 = z * a.cpz, kc1 = min(kc0 + a.cpz, a.nchunks);
-
   unsigned char* As = smem;
   unsigned char* Bs = smem + X::TERMS * X::WA;
   const T* gy = static_cast<const T*>(a.gy);
   const T* x = static_cast<const T*>(a.x);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = lane_id<T>(), lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   const int vi = tid & 7, row0 = tid >> 3;   // this lane's vector of the chunk, first row
   int rowa[LA], rowb[LB];
@@ -391,11 +364,12 @@ __device__ __forceinline__ void xwgrad_block(const XArgs& a, int L, unsigned cha
         s.b[i] = shifted<T>(s.b[i], min(max(o - min(max(o, 0), hi_b), -VE), VE));
       }
     }
-    const u32x4_t ka = keep_mask<T>(s.keep), kb = ka & bit_mask<T>(vec_mask<T>(s.mb, s.k0));
+    // both operands: what the tap does not read must not meet an infinity on the other side either
+    const u32x4_t m = keep_mask<T>(s.keep) & bit_mask<T>(vec_mask<T>(s.mb, s.k0));
     auto put = [&](unsigned char* tile, int term_bytes, int row, const u32x4_t& v) __attribute__((always_inline)) {
       if constexpr (X::SPLIT) {
         uint2 w[3];
-        split3(v, w);
+        split3(v, w, low);
 #pragma unroll
         for (int k = 0; k < 3; ++k) *reinterpret_cast<uint2*>(tile + k * term_bytes + row * X::RW + vi * 8) = w[k];
       } else {
@@ -403,16 +377,14 @@ __device__ __forceinline__ void xwgrad_block(const XArgs& a, int L, unsigned cha
       }
     };
 #pragma unroll
-    for (int i = 0; i < LA; ++i) put(As, X::WA, row0 + 32 * i, s.a[i] & ka);
+    for (int i = 0; i < LA; ++i) put(As, X::WA, row0 + 32 * i, s.a[i] & m);
 #pragma unroll
-    for (int i = 0; i < LB; ++i) put(Bs, X::WB, row0 + 32 * i, s.b[i] & kb);
+    for (int i = 0; i < LB; ++i) put(Bs, X::WB, row0 + 32 * i, s.b[i] & m);
   };
-  f32x16 acc[TM][TN];
-  zero_acc<T, TM, TN>(acc);
   auto mul = [&]() __attribute__((always_inline)) {
     const int r = lane & 31, kg = lane >> 5;
 #pragma unroll
-    for (int ks = 0; ks < X::KB / 16; ++ks) {   // 16 k per MFMA
+    for (int ks = 0; ks < El<T>::KS; ++ks) {
       uint4 fa[TM][X::TERMS], fb[TN][X::TERMS];
 #pragma unroll
       for (int u = 0; u < X::TERMS; ++u) {
@@ -426,7 +398,42 @@ __device__ __forceinline__ void xwgrad_block(const XArgs& a, int L, unsigned cha
       mul_all<T, TM, TN>(fa, fb, acc);
     }
   };
-  k_loop<xsets_of<TM, TN>(), Set>(kc0, kc1, fetch, stage, mul);
+  k_loop<xsets_of<T, TM, TN>(), Set>(kc0, kc1, fetch, stage, mul);
+}
+
+template <class T, int TM, int TN>
+__device__ __forceinline__ void xwgrad_block(const XArgs& a, int L, unsigned char* smem) {
+  using X = XTile<T, TM, TN>;
+  // The hardware hands consecutive blocks to the eight XCDs in turn; with eight or more K slabs block L works on
+  // slab (L % 8) + 8 * (..), so that all taps and tiles of a slab share one XCD's L2 and each XCD touches an eighth
+  // of x and g_y.
+  int z, rest;
+  if (a.xcd_slabs) {
+    const int idx = L >> 3;
+    const int zl = (int)a.d_r.div((uint32_t)idx);
+    z = (L & 7) + 8 * zl;
+    rest = idx - zl * a.R;
+  } else {
+    z = (int)a.d_r.div((uint32_t)L);
+    rest = L - z * a.R;
+  }
+  if (z >= a.nz) return;  // uniform for the block
+  const int t = (int)a.d_tiles.div((uint32_t)rest), tile = rest - t * a.tiles;
+  const int by = (int)a.d_tx.div((uint32_t)tile), bx = tile - by * a.tx;
+  const int m0 = by * X::BM, n0 = bx * X::BN;
+  const int kc0 = z * a.cpz, kc1 = min(kc0 + a.cpz, a.nchunks);
+  f32x16 acc[TM][TN];
+  uint32_t low = 0;
+  zero_acc(acc);
+  xw_mainloop<T, TM, TN>(a, t, m0, n0, kc0, kc1, smem, acc, low);
+  if constexpr (is_split<T>()) {
+    if (split_failed(acc, low)) {
+      zero_acc(acc);
+      xw_mainloop<raw_f32, TM, TN>(a, t, m0, n0, kc0, kc1, smem, acc, low);
+    }
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wm = wave >> 1, wn = wave & 1;
   float* dst = a.part + ((long)z * a.KK + t) * a.Co * a.Ci;
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -441,28 +448,19 @@ __device__ __forceinline__ void xwgrad_block(const XArgs& a, int L, unsigned cha
     }
 }
 
-// rows c_i of one column tile (64 TN positions of the padded planes, counted over the batch) of one phase
+// acc += w[steps][rows m0 ..]^T * g_y[steps][columns of the tile, moved by the tap] over steps (tap of the phase, chunk of c_o)
 template <class T, int TM, int TN>
-__device__ __forceinline__ void xdgrad_block(const XArgs& a, int L, unsigned char* smem, int2* taps_lds, int* s_flag) {
+__device__ __forceinline__ void xd_mainloop(const XArgs& a, int ph, int m0, int tni, int it0, int iters, unsigned char* smem,
+                                            const int2* taps_lds, f32x16 (&acc)[TM][TN], uint32_t& low) {
   using X = XTile<T, TM, TN>;
   constexpr int VE = X::VE, KB = X::KB, LA = 2 * TM, LB = 2 * TN;
   constexpr int VA = X::BM / VE, VB = X::BN / VE;   // vectors per row of k
   static_assert(kT % VB == 0, "a lane keeps its column vector");
   typedef XSet<LA, LB> Set;
-  const int per_ph = a.d_tm * a.d_tn;
-  const int tile = L / a.d_nz, z = L - tile * a.d_nz;
-  const int ph = tile / per_ph, rest = tile - ph * per_ph;
-  const int tni = rest / a.d_tm, tmi = rest - tni * a.d_tm;   // row tiles of one column tile run side by side
-  const int m0 = tmi * X::BM;
-  const int ntap = a.ntap[ph];
-  const int it0 = z * a.d_its, iters = min(ntap * a.nck, it0 + a.d_its);   // steps of this slab
   const int2* taps = a.tapd + (long)ph * a.KK;
   const uint8_t* tab = a.tabd + (long)ph * a.KK * a.nvd;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = lane_id<T>(), lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
-  if (tid < min(ntap, kTapsLds)) taps_lds[tid] = taps[tid];
-  __syncthreads();
-
   unsigned char* As = smem;
   unsigned char* Bs = smem + X::TERMS * X::DA;
   const T* gy = static_cast<const T*>(a.gy);
@@ -534,15 +532,13 @@ __device__ __forceinline__ void xdgrad_block(const XArgs& a, int L, unsigned cha
         if (s.k0 + (tid + i * kT) / VB >= a.Co) s.b[i] = u32x4_t{0, 0, 0, 0};
     }
 #pragma unroll
-    for (int i = 0; i < LA; ++i) put_row<T, X::BM>(As, (tid + i * kT) / VA, (tid + i * kT) % VA, s.a[i]);
+    for (int i = 0; i < LA; ++i) put_row<T, X::BM>(As, (tid + i * kT) / VA, (tid + i * kT) % VA, s.a[i], low);
 #pragma unroll
-    for (int i = 0; i < LB; ++i) put_row<T, X::BN>(Bs, (tid + i * kT) / VB, tid % VB, s.b[i]);
+    for (int i = 0; i < LB; ++i) put_row<T, X::BN>(Bs, (tid + i * kT) / VB, tid % VB, s.b[i], low);
   };
-  f32x16 acc[TM][TN];
-  zero_acc<T, TM, TN>(acc);
   auto mul = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int ks = 0; ks < KB / 16; ++ks) {
+    for (int ks = 0; ks < El<T>::KS; ++ks) {
       uint4 fa[TM][X::TERMS], fb[TN][X::TERMS];
 #pragma unroll
       for (int u = 0; u < X::TERMS; ++u) {
@@ -554,12 +550,44 @@ __device__ __forceinline__ void xdgrad_block(const XArgs& a, int L, unsigned cha
       mul_all<T, TM, TN>(fa, fb, acc);
     }
   };
-  if (it0 < iters) k_loop<xsets_of<TM, TN>(), Set>(it0, iters, fetch, stage, mul);
+  k_loop<xsets_of<T, TM, TN>(), Set>(it0, iters, fetch, stage, mul);
+}
+
+// rows c_i of one column tile (64 TN positions of the padded planes, counted over the batch) of one phase
+template <class T, int TM, int TN>
+__device__ __forceinline__ void xdgrad_block(const XArgs& a, int L, unsigned char* smem, int2* taps_lds, int* s_flag) {
+  using X = XTile<T, TM, TN>;
+  constexpr int VE = X::VE, VB = X::BN / VE;
+  const int per_ph = a.d_tm * a.d_tn;
+  const int tile = L / a.d_nz, z = L - tile * a.d_nz;
+  const int ph = tile / per_ph, rest = tile - ph * per_ph;
+  const int tni = rest / a.d_tm, tmi = rest - tni * a.d_tm;   // row tiles of one column tile run side by side
+  const int m0 = tmi * X::BM;
+  const int ntap = a.ntap[ph];
+  const int it0 = z * a.d_its, iters = min(ntap * a.nck, it0 + a.d_its);   // steps of this slab
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 1, wn = wave & 1;
+  if (tid < min(ntap, kTapsLds)) taps_lds[tid] = a.tapd[(long)ph * a.KK + tid];
+  __syncthreads();
+  f32x16 acc[TM][TN];
+  uint32_t low = 0;
+  zero_acc(acc);
+  if (it0 < iters) xd_mainloop<T, TM, TN>(a, ph, m0, tni, it0, iters, smem, taps_lds, acc, low);
+  if constexpr (is_split<T>()) {
+    if (split_failed(acc, low)) {
+      zero_acc(acc);
+      xd_mainloop<raw_f32, TM, TN>(a, ph, m0, tni, it0, iters, smem, taps_lds, acc, low);
+    }
+  }
   if (a.d_nz > 1 && !reduce_slabs<TM, TN>(acc, a.partD + (long)tile * (a.d_nz + a.d_ngrp) * (4096 * TM * TN), z,
                                           a.tickD + tile * (1 + a.d_ngrp), a.d_nz, a.d_grp, a.d_ngrp, s_flag,
                                           a.Ci - m0 - 32 * wm, 64 * TN))
     return;
 
+  const int jv = tni * VB + tid % VB;               // this lane's column vector
+  const int nimg = (int)a.d_qd.div((uint32_t)jv);
+  const int q = (jv - nimg * a.qd) * VE;
+  const bool img = nimg < a.N;
   // 64 rows at a time through LDS (rounded once to the storage type), out as 16-byte runs of pixels
   T* Cs = reinterpret_cast<T*>(smem);
   T* out = static_cast<T*>(a.gx) + (long)ph * a.N * a.Ci * a.PQ;
@@ -594,7 +622,7 @@ __device__ __forceinline__ void xdgrad_block(const XArgs& a, int L, unsigned cha
 }
 
 template <class T, int TM, int TN>
-__global__ __launch_bounds__(kT) void xgemm_k(XArgs a) {
+__global__ __launch_bounds__(kT, TM * TN == 4 ? 2 : 3) void xgemm_k(XArgs a) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[XTile<T, TM, TN>::kBytes];
   __shared__ int2 taps_lds[kTapsLds];
   __shared__ int s_flag;

@@ -257,3 +257,42 @@ def test_large_maps_of_few_channels(N, Ci, Co, H, W, dtype):
         for p in range(0, P, 1 << 22):
             r_w += fg[:, p:p + (1 << 22)].double() @ fx[:, p:p + (1 << 22)].double().t().contiguous()
     assert rel_err(g_w.reshape(Co, Ci), r_w.cpu().numpy()) <= TOL[dtype]
+
+
+def same_values(got, ref, tol):
+    """Infinities and NaN where the reference has them, the rest within tol of the largest finite value."""
+    got, fin = to64(got), np.isfinite(ref)
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+    assert np.abs(got[fin] - ref[fin]).max() <= tol * np.abs(ref[fin]).max()
+
+
+# N, C_in, C_out, H, W, K, stride, padding: a small and a large reduced map, ragged planes, every tile of the vanilla launch
+FP32_CASES = [
+    (4, 64, 72, 14, 14, 1, 1, 0), (8, 72, 64, 8, 8, 3, 1, 1), (2, 24, 40, 66, 62, 1, 1, 0), (1, 16, 16, 20, 260, 3, 1, 1),
+    (3, 65, 65, 6, 6, 3, 1, 1), (40, 129, 130, 14, 14, 3, 1, 1), (2, 40, 24, 21, 19, 3, 1, 1), (2, 24, 40, 14, 14, 3, 2, 1),
+]
+
+
+@pytest.mark.parametrize("kind", ["tiny", "large", "infinite"])
+@pytest.mark.parametrize("case", FP32_CASES)
+def test_fp32_products_of_extreme_values(oracle, case, kind):
+    """fp32 products outside the range that three bf16 terms cover: gradients around 2^-116, values past the largest
+    bf16 and infinities come out as fp32 multiplication gives them, in both directions and on both paths."""
+    N, Ci, Co, H, W, K, s, p = case
+    d = mk(N, Ci, Co, H, W, K, s, p, r=2)
+    od, sh = odesc(oracle, d), T.shapes(d)
+    x, w, gy = randn(sh["x"], 1, "f32"), randn(sh["w"], 2, "f32", scale=0.1), randn(sh["g_y"], 3, "f32")
+    if kind == "tiny":
+        gy *= 2.0 ** -116
+    elif kind == "large":
+        x[0, 1, 1, 1], gy[0, 0, 2, 2], w[1, 2, 0, 0] = 3.4e38, 1e3, -3.395e38
+        gy *= 1e-6
+    else:
+        x[0, 1, 1, 1], x[N - 1, 0, H - 1, W - 1], gy[0, 2, 0, 0] = float("inf"), float("-inf"), float("inf")
+    with np.errstate(invalid="ignore", over="ignore"):
+        r_w, r_x = oracle.bwd_exact(od, to64(x), to64(w), to64(gy))
+        f_w, f_x, _, _ = oracle.gf_backward(od, to64(x), to64(w), to64(gy))
+    g_w, g_x = T.conv_bwd_exact(d, x.cuda(), w.cuda(), gy.cuda())
+    same_values(g_w, r_w, 1e-5), same_values(g_x, r_x, 1e-5)
+    g_w, g_x, _ = T.conv_bwd_filtered(d, gy.cuda(), T.pool_activation(d, x.cuda()), w.cuda())
+    same_values(g_w, f_w, 1e-5), same_values(g_x, f_x, 1e-5)
