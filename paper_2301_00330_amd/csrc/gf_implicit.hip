@@ -351,7 +351,7 @@ __device__ __forceinline__ void xw_mainloop(const XArgs& a, int t, int m0, int n
       if (kv >= a.kvecs) { n = a.N - 1; pv = a.qv - 1; }   // past the last image: its last vector, masked
     }
   };
-  auto stage = [&](Set& s, int) __attribute__((always_inline)) {
+  auto stage = [&](Set& s, int, auto neg) __attribute__((always_inline)) {
     if (s.off) {   // first or last rows of the tensors only: shift the moved vectors back
 #pragma unroll
       for (int i = 0; i < LA; ++i) {
@@ -366,10 +366,10 @@ __device__ __forceinline__ void xw_mainloop(const XArgs& a, int t, int m0, int n
     }
     // both operands: what the tap does not read must not meet an infinity on the other side either
     const u32x4_t m = keep_mask<T>(s.keep) & bit_mask<T>(vec_mask<T>(s.mb, s.k0));
-    auto put = [&](unsigned char* tile, int term_bytes, int row, const u32x4_t& v) __attribute__((always_inline)) {
+    auto put = [&](unsigned char* tile, int term_bytes, int row, const u32x4_t& v, auto sign) __attribute__((always_inline)) {
       if constexpr (X::SPLIT) {
         uint2 w[3];
-        split3(v, w, low);
+        split3<decltype(sign)::value>(v, w, low);
 #pragma unroll
         for (int k = 0; k < 3; ++k) *reinterpret_cast<uint2*>(tile + k * term_bytes + row * X::RW + vi * 8) = w[k];
       } else {
@@ -377,11 +377,12 @@ __device__ __forceinline__ void xw_mainloop(const XArgs& a, int t, int m0, int n
       }
     };
 #pragma unroll
-    for (int i = 0; i < LA; ++i) put(As, X::WA, row0 + 32 * i, s.a[i] & m);
+    for (int i = 0; i < LA; ++i) put(As, X::WA, row0 + 32 * i, s.a[i] & m, neg);
 #pragma unroll
-    for (int i = 0; i < LB; ++i) put(Bs, X::WB, row0 + 32 * i, s.b[i] & m);
+    for (int i = 0; i < LB; ++i) put(Bs, X::WB, row0 + 32 * i, s.b[i] & m, std::false_type());
   };
-  auto mul = [&]() __attribute__((always_inline)) {
+  auto mul = [&](auto neg) __attribute__((always_inline)) {
+    typename El<T>::acc s;
     const int r = lane & 31, kg = lane >> 5;
 #pragma unroll
     for (int ks = 0; ks < El<T>::KS; ++ks) {
@@ -395,7 +396,7 @@ __device__ __forceinline__ void xw_mainloop(const XArgs& a, int t, int m0, int n
         for (int j = 0; j < TN; ++j)
           fb[j][u] = *reinterpret_cast<const uint4*>(Bs + u * X::WB + (64 * j + 32 * wn + r) * X::RW + ks * 32 + kg * 16);
       }
-      mul_all<T, TM, TN>(fa, fb, acc);
+      mul_all<T, decltype(neg)::value>(fa, fb, acc, s, ks);
     }
   };
   k_loop<xsets_of<T, TM, TN>(), Set>(kc0, kc1, fetch, stage, mul);
@@ -512,7 +513,7 @@ __device__ __forceinline__ void xd_mainloop(const XArgs& a, int ph, int m0, int 
       new_tap = false;
     }
   };
-  auto stage = [&](Set& s, int) __attribute__((always_inline)) {
+  auto stage = [&](Set& s, int, auto neg) __attribute__((always_inline)) {
     if (s.off) {   // first or last rows of g_y only: shift the moved vectors back
 #pragma unroll
       for (int i = 0; i < LB; ++i) {
@@ -532,11 +533,12 @@ __device__ __forceinline__ void xd_mainloop(const XArgs& a, int ph, int m0, int 
         if (s.k0 + (tid + i * kT) / VB >= a.Co) s.b[i] = u32x4_t{0, 0, 0, 0};
     }
 #pragma unroll
-    for (int i = 0; i < LA; ++i) put_row<T, X::BM>(As, (tid + i * kT) / VA, (tid + i * kT) % VA, s.a[i], low);
+    for (int i = 0; i < LA; ++i) put_row<T, X::BM, decltype(neg)::value>(As, (tid + i * kT) / VA, (tid + i * kT) % VA, s.a[i], low);
 #pragma unroll
     for (int i = 0; i < LB; ++i) put_row<T, X::BN>(Bs, (tid + i * kT) / VB, tid % VB, s.b[i], low);
   };
-  auto mul = [&]() __attribute__((always_inline)) {
+  auto mul = [&](auto neg) __attribute__((always_inline)) {
+    typename El<T>::acc s;
 #pragma unroll
     for (int ks = 0; ks < El<T>::KS; ++ks) {
       uint4 fa[TM][X::TERMS], fb[TN][X::TERMS];
@@ -547,7 +549,7 @@ __device__ __forceinline__ void xd_mainloop(const XArgs& a, int ph, int m0, int 
 #pragma unroll
         for (int j = 0; j < TN; ++j) fb[j][u] = frag_tr<T, X::BN>(Bs + u * X::DB, ks, 64 * j + 32 * wn, lane);
       }
-      mul_all<T, TM, TN>(fa, fb, acc);
+      mul_all<T, decltype(neg)::value>(fa, fb, acc, s, ks);
     }
   };
   k_loop<xsets_of<T, TM, TN>(), Set>(it0, iters, fetch, stage, mul);
