@@ -210,8 +210,9 @@ PyObject* pool_activation(PyObject* const* a) {   // d, x, out
   return wrap(out);
 }
 
-// descs, xs (sequences), inv_deltas (None: storage-type sums)
-PyObject* pool_activation_batch(PyObject* const* a) {
+// descs, xs, inv_deltas (sequences); without codes: storage-type sums, no third argument
+template <bool CODES>
+PyObject* pool_batch(PyObject* const* a) {
   struct Seq {
     PyObject* s;
     explicit Seq(PyObject* o) : s(PySequence_Fast(o, "a sequence is expected")) { if (!s) throw Raised(); }
@@ -219,8 +220,8 @@ PyObject* pool_activation_batch(PyObject* const* a) {
     Py_ssize_t size() const { return PySequence_Fast_GET_SIZE(s); }
     PyObject* operator[](Py_ssize_t i) const { return PySequence_Fast_GET_ITEM(s, i); }
   };
-  const bool codes = a[2] != Py_None;
   const Seq ds(a[0]), xs(a[1]);
+  const Seq v(a[CODES ? 2 : 1]);
   const Py_ssize_t m = std::min(ds.size(), xs.size());
   std::vector<gf_conv_desc> d;
   std::vector<const void*> in;
@@ -230,14 +231,13 @@ PyObject* pool_activation_batch(PyObject* const* a) {
   for (Py_ssize_t i = 0; i < m; ++i) {
     const Layer l(ds[i]);
     const at::Tensor& x = tensor(xs[i], l, l.x, "x");
-    made.push_back(make(x, l.xu, codes ? at::kChar : x.scalar_type()));
+    made.push_back(make(x, l.xu, CODES ? at::kChar : x.scalar_type()));
     d.push_back(l.d);
     in.push_back(ptr(x));
     out.push_back(ptr(made.back()));
   }
   bool same = ds.size() == m && xs.size() == m;
-  if (codes) {
-    const Seq v(a[2]);
+  if constexpr (CODES) {
     same = same && v.size() == m;
     for (Py_ssize_t i = 0; same && i < m; ++i) inv.push_back(number(v[i]));
   }
@@ -251,7 +251,7 @@ PyObject* pool_activation_batch(PyObject* const* a) {
   const gf_conv_desc* dp = m ? d.data() : &none;   // an empty call is the library's to refuse
   const void* const* ip = m ? in.data() : &no_in;
   void* const* op = m ? out.data() : &no_out;
-  if (codes)
+  if constexpr (CODES)
     call("gf_pool_activation_batch_q8", [&](void* st) {
       return gf_pool_activation_batch_q8((int32_t)m, dp, ip, inv.data(), reinterpret_cast<int8_t* const*>(op), st);
     });
@@ -266,6 +266,9 @@ PyObject* pool_activation_batch(PyObject* const* a) {
   }
   return r;
 }
+
+PyObject* pool_activation_batch(PyObject* const* a) { return pool_batch<false>(a); }
+PyObject* pool_activation_batch_q8(PyObject* const* a) { return pool_batch<true>(a); }
 
 PyObject* pool_activation_mask(PyObject* const* a) {   // d, x, hi
   const Layer l(a[0]);
@@ -496,7 +499,8 @@ PyObject* setup(PyObject* const* a) {
   {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(&entry<name, nargs>)), METH_FASTCALL, nullptr}
 
 PyMethodDef methods[] = {
-    GF_ENTRY(setup, 5), GF_ENTRY(pool_activation, 3), GF_ENTRY(pool_activation_batch, 3),
+    GF_ENTRY(setup, 5), GF_ENTRY(pool_activation, 3), GF_ENTRY(pool_activation_batch, 2),
+    GF_ENTRY(pool_activation_batch_q8, 3),
     GF_ENTRY(pool_activation_mask, 3), GF_ENTRY(filter_grad, 3), GF_ENTRY(filter_grad_snr, 3),
     GF_ENTRY(conv_bwd_weight, 5), GF_ENTRY(conv_bwd_input, 6), GF_ENTRY(conv_bwd_filtered, 6),
     GF_ENTRY(conv_bwd_chained, 7), GF_ENTRY(conv_bwd_exact, 7), GF_ENTRY(conv_bwd_unique, 6),

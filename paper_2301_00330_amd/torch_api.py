@@ -91,12 +91,12 @@ def pool_activation(d: B.ConvDesc, x: torch.Tensor, out: torch.Tensor | None = N
 
 def pool_activation_batch(descs, xs):
     """x_u of several layers from one launch (gf_pool_activation_batch)."""
-    return _C.pool_activation_batch(descs, xs, None)
+    return _C.pool_activation_batch(descs, xs)
 
 
 def pool_activation_batch_q8(descs, xs, inv_deltas):
     """x_q of several layers from one launch (gf_pool_activation_batch_q8)."""
-    return _C.pool_activation_batch(descs, xs, inv_deltas)
+    return _C.pool_activation_batch_q8(descs, xs, inv_deltas)
 
 
 def pool_activation_mask(d: B.ConvDesc, x: torch.Tensor, hi: float = float("inf")):

@@ -337,6 +337,16 @@ def test_pool_batch_host_checks(lib):
         assert ei.value.status == want
 
 
+def test_pool_batch_q8_needs_step_sizes(lib):
+    """The batched pooling with code output refuses a missing list of step sizes (also before it looks at a tensor)."""
+    import paper_2301_00330_amd.torch_api as T
+    for descs in ([], [B.ConvDesc(**OK)]):
+        with pytest.raises(TypeError):
+            T.pool_activation_batch_q8(descs, [None] * len(descs), None)
+    with pytest.raises(B.GfError):   # an empty batch of sums is the library's to refuse
+        T.pool_activation_batch([], [])
+
+
 def test_unique_elements_entry_host_checks(lib):
     """gf_conv_bwd_unique: stride-1 layers whose padding keeps the map size; workspace = vanilla BP on
     the patch grid plus the reduced g_x."""
