@@ -112,9 +112,10 @@ at::Tensor make(const at::Tensor& like, const Shape& s, at::ScalarType dt) {
   return make(like, at::IntArrayRef(s.data(), 4), dt);
 }
 
-// Scratch of a call: the caller's Workspace, else a default one per (device, current stream) -- calls on
-// different streams may overlap in time and must not share scratch memory.  `hold` keeps the buffer alive while
-// the interpreter lock is released around the launch.
+// Scratch of a call: the caller's workspace, else a default one per (device, current stream) -- calls on
+// different streams may overlap in time and must not share scratch memory.  A workspace is any object whose
+// get(bytes) returns (address, size); of torch_api.Workspace itself the buffer is read directly and `hold` keeps it
+// alive while the interpreter lock is released around the launch.
 struct Scratch {
   void* p = nullptr;
   size_t n = 0;
@@ -124,6 +125,18 @@ struct Scratch {
     size_t need = 0;
     status(gf_workspace_bytes(&l.d, op, &need), "gf_workspace_bytes");
     if (ws == Py_None) ws = default_for(on);
+    if ((PyObject*)Py_TYPE(ws) != g_workspace) {
+      PyObject* r = PyObject_CallMethod(ws, "get", "n", (Py_ssize_t)need);
+      PyObject* pair = r ? PySequence_Tuple(r) : nullptr;
+      Py_XDECREF(r);
+      unsigned long long addr = 0, size = 0;
+      const bool ok = pair && PyArg_ParseTuple(pair, "KK", &addr, &size);
+      Py_XDECREF(pair);
+      if (!ok) throw Raised();
+      p = reinterpret_cast<void*>((uintptr_t)addr);
+      n = (size_t)size;
+      return;
+    }
     if (need == 0) return;
     PyObject* b = PyObject_GetAttr(ws, g_buf);
     if (!b) throw Raised();

@@ -296,3 +296,34 @@ def test_fp32_products_of_extreme_values(oracle, case, kind):
     same_values(g_w, r_w, 1e-5), same_values(g_x, r_x, 1e-5)
     g_w, g_x, _ = T.conv_bwd_filtered(d, gy.cuda(), T.pool_activation(d, x.cuda()), w.cuda())
     same_values(g_w, f_w, 1e-5), same_values(g_x, f_x, 1e-5)
+
+
+def test_workspaces_of_other_kinds():
+    """A workspace is any object whose get(bytes) returns an address and a size: one without a `buf`, and a subclass of
+    Workspace that overrides get."""
+    class Mine:
+        def __init__(self):
+            self.mem, self.asked = torch.empty(1 << 22, dtype=torch.uint8, device="cuda"), []
+
+        def get(self, nbytes):
+            self.asked.append(nbytes)
+            return int(self.mem.data_ptr()), int(self.mem.numel())
+
+    class Counted(T.Workspace):
+        asked = 0
+
+        def get(self, nbytes):
+            self.asked += 1
+            return super().get(nbytes)
+
+    d = mk(8, 64, 72, 14, 14, 3, 1, 1)
+    sh = T.shapes(d)
+    args = [randn(sh[k], i, "f32").cuda() for i, k in enumerate(("g_y", "x_u", "w"))]
+    want = T.conv_bwd_filtered(d, *args)
+    mine, counted = Mine(), Counted()
+    for ws in (mine, counted, counted):
+        assert all(torch.equal(a, b) for a, b in zip(want, T.conv_bwd_filtered(d, *args, ws=ws)))
+    assert len(mine.asked) == 1 and mine.asked[0] > 0 and counted.asked == 2
+    with pytest.raises(TypeError):
+        Mine.get = lambda self, nbytes: None
+        T.conv_bwd_filtered(d, *args, ws=Mine())
