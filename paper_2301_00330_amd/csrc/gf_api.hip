@@ -159,8 +159,9 @@ static gf_status unique_geom(const Geom& g, Geom* red) {
 }
 
 // [vanilla BP on the patch grid][the reduced g_x when full resolution is asked for]
-static size_t ws_unique(const Geom& g, const Geom& red, bool want_gw, bool want_gx, bool reduced_out, size_t* off_red) {
-  size_t o = align256(ws_exact(red, want_gw, want_gx));
+static size_t ws_unique(const Geom& g, const Geom& red, bool want_gw, bool want_gx, bool reduced_out, size_t* off_red,
+                        bool least = false) {
+  size_t o = align256(least ? ws_exact_least(red, want_gw, want_gx) : ws_exact(red, want_gw, want_gx));
   if (off_red) *off_red = o;
   if (want_gx && !reduced_out) o += (size_t)g.N * g.Ci * g.P * g.b;
   return o;
@@ -199,6 +200,15 @@ static gf_status check_ws(size_t need, const void* ws, size_t ws_bytes) {
   if (!ws || ws_bytes < need) return GF_ERR_WORKSPACE;
   if (!aligned16(ws)) return GF_ERR_UNSUPPORTED;
   return GF_OK;
+}
+
+// Paths that exist in two forms, with the workspace gf_workspace_bytes names and with `least` of it: a call that brings
+// only the latter is accepted (*ws_bytes then tells the launch which form to take).
+static gf_status check_ws_or(size_t need, size_t least, const void* ws, size_t* ws_bytes) {
+  if (check_ws(need, ws, *ws_bytes) == GF_OK) return GF_OK;
+  const gf_status rc = check_ws(least, ws, *ws_bytes);
+  if (*ws_bytes >= need) *ws_bytes = least;
+  return rc;
 }
 
 }  // namespace gf
@@ -399,9 +409,9 @@ gf_status gf_conv_bwd_input_q8(const gf_conv_desc* desc, const int8_t* gy_q, con
   if (rc) return rc;
   if (!gy_q || !w_q || !g_x) return GF_ERR_NULL;
   if (!aligned16(gy_q) || !aligned16(w_q) || !aligned16(g_x)) return GF_ERR_UNSUPPORTED;
-  rc = check_ws(ws_bwd_input_q8(g, reduced_out != 0), ws, ws_bytes);
+  rc = check_ws_or(ws_bwd_input_q8(g, reduced_out != 0), ws_bwd_input_q8_least(g, reduced_out != 0), ws, &ws_bytes);
   if (rc) return rc;
-  return dev(launch_bwd_input_q8(g, gy_q, w_q, scale, g_x, reduced_out != 0, ws, static_cast<hipStream_t>(stream)));
+  return dev(launch_bwd_input_q8(g, gy_q, w_q, scale, g_x, reduced_out != 0, ws, ws_bytes, static_cast<hipStream_t>(stream)));
 }
 
 gf_status gf_conv_bwd_weight(const gf_conv_desc* desc, const void* x_u, const void* gy_u,
@@ -414,7 +424,7 @@ gf_status gf_conv_bwd_weight(const gf_conv_desc* desc, const void* x_u, const vo
   rc = check_ws(ws_need(g, GF_OP_BWD_WEIGHT, false), ws, ws_bytes);
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (g.r == 1) return dev(launch_exact_wgrad(g, x_u, gy_u, g_w, ws, st));
+  if (g.r == 1) return dev(launch_exact(g, x_u, nullptr, gy_u, g_w, nullptr, ws, ws_bytes, st));
   if (gemm_ok(g)) return dev(launch_dense(g, gy_u, false, x_u, nullptr, nullptr, g_w, nullptr, false, nullptr, ws, st));
   return dev(launch_gf_bwd_weight(g, x_u, gy_u, g_w, ws, st));
 }
@@ -426,10 +436,11 @@ gf_status gf_conv_bwd_input(const gf_conv_desc* desc, const void* gy_u, const vo
   if (rc) return rc;
   if (!gy_u || !w || !g_x) return GF_ERR_NULL;
   if (!aligned16(gy_u) || !aligned16(w) || !aligned16(g_x)) return GF_ERR_UNSUPPORTED;
-  rc = check_ws(ws_need(g, GF_OP_BWD_INPUT, reduced_out != 0), ws, ws_bytes);
+  const size_t need = ws_need(g, GF_OP_BWD_INPUT, reduced_out != 0);
+  rc = check_ws_or(need, g.r == 1 ? ws_exact_least(g, false, true) : need, ws, &ws_bytes);
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (g.r == 1) return dev(launch_exact_dgrad(g, w, gy_u, g_x, ws, st));
+  if (g.r == 1) return dev(launch_exact_dgrad(g, w, gy_u, g_x, ws, ws_bytes, st));
   if (gemm_ok(g))
     return dev(launch_dense(g, gy_u, false, nullptr, w, nullptr, nullptr, g_x, reduced_out != 0, nullptr, ws, st));
   return dev(launch_gf_bwd_input(g, gy_u, w, g_x, reduced_out != 0, ws, st));
@@ -499,7 +510,7 @@ static gf_status filtered_body(const gf_conv_desc* desc, const void* g_y, const 
                               hipMemcpyDeviceToDevice, st));
       if (rc) return rc;
     }
-    return dev(launch_exact(g, x_u, w, g_y, g_w, g_x, ws, st));
+    return dev(launch_exact(g, x_u, w, g_y, g_w, g_x, ws, ws_bytes, st));
   }
   if (dense_ok(g))
     return dev(launch_dense(g, g_y, true, x_u, w, gy_u, g_w, g_x, false, nullptr, ws, st));
@@ -598,7 +609,7 @@ static gf_status chained_body(const Geom& g, const void* gy_u, const void* x_u, 
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* wsb = static_cast<char*>(ws);
   const float scale = 1.f / ((float)g.s * (float)g.s);
-  if (g.r == 1) return dev(launch_exact(g, x_u, w, gy_u, g_w, g_x, ws, st));   // the maps are the full maps: vanilla BP
+  if (g.r == 1) return dev(launch_exact(g, x_u, w, gy_u, g_w, g_x, ws, ws_bytes, st));   // the maps are the full maps: vanilla BP
   if (gemm_ok(g)) {
     *mask_done = reduced_out != 0;
     return dev(launch_dense(g, gy_u, false, x_u, w, nullptr, g_w, g_x, reduced_out != 0,
@@ -659,7 +670,7 @@ gf_status gf_conv_bwd_filtered_q8(const gf_conv_desc* desc, const void* g_y, flo
   if (rc) return rc;
   rc = dev(launch_bwd_weight_q8(g, x_q, gq, scale_w, g_w, wsb + off_w, st));
   if (rc) return rc;
-  return dev(launch_bwd_input_q8(g, gq, wq, scale_x, g_x, false, wsb + off_i, st));
+  return dev(launch_bwd_input_q8(g, gq, wq, scale_x, g_x, false, wsb + off_i, ws_bwd_input_q8(g, false), st));
 }
 
 gf_status gf_conv_bwd_exact(const gf_conv_desc* desc, const void* x, const void* w,
@@ -678,10 +689,10 @@ gf_status gf_conv_bwd_exact(const gf_conv_desc* desc, const void* x, const void*
   if ((g_w && !x) || (g_x && !w)) return GF_ERR_NULL;
   if (!aligned16(g_y) || !aligned16(x) || !aligned16(w) || !aligned16(g_w) || !aligned16(g_x))
     return GF_ERR_UNSUPPORTED;
-  rc = check_ws(ws_exact(g, g_w != nullptr, g_x != nullptr), ws, ws_bytes);
+  rc = check_ws_or(ws_exact(g, g_w != nullptr, g_x != nullptr), ws_exact_least(g, g_w != nullptr, g_x != nullptr), ws, &ws_bytes);
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  return dev(launch_exact(g, x, w, g_y, g_w, g_x, ws, st));
+  return dev(launch_exact(g, x, w, g_y, g_w, g_x, ws, ws_bytes, st));
 }
 
 gf_status gf_conv_bwd_unique(const gf_conv_desc* desc, const void* gy_u, const void* x_u, const void* w,
@@ -702,12 +713,14 @@ gf_status gf_conv_bwd_unique(const gf_conv_desc* desc, const void* gy_u, const v
     return GF_ERR_UNSUPPORTED;
   size_t off_red = 0;
   const bool full = g_x && !reduced_out;
-  rc = check_ws(ws_unique(g, red, g_w != nullptr, g_x != nullptr, reduced_out != 0, &off_red), ws, ws_bytes);
+  const size_t need = ws_unique(g, red, g_w != nullptr, g_x != nullptr, reduced_out != 0, &off_red);
+  rc = check_ws_or(need, ws_unique(g, red, g_w != nullptr, g_x != nullptr, reduced_out != 0, nullptr, true), ws, &ws_bytes);
   if (rc) return rc;
+  if (ws_bytes < need) ws_unique(g, red, g_w != nullptr, g_x != nullptr, reduced_out != 0, &off_red, true);
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* wsb = static_cast<char*>(ws);
   void* gxu = full ? static_cast<void*>(wsb + off_red) : g_x;
-  rc = dev(launch_exact(red, x_u, w, gy_u, g_w, gxu, ws, st));
+  rc = dev(launch_exact(red, x_u, w, gy_u, g_w, gxu, ws, full ? off_red : ws_bytes, st));
   if (rc || !full) return rc;
   return dev(launch_replicate(g, gxu, g_x, st));
 }

@@ -313,9 +313,13 @@ size_t ws_exact(const Geom& g, bool want_gw, bool want_gx) {
   return col_bytes(g, want_gw, want_gx) + aux_bytes(g, want_gw, want_gx);
 }
 
-hipError_t launch_exact_wgrad(const Geom& g, const void* x, const void* g_y, float* g_w, void* ws,
-                              hipStream_t st) {
-  if (implicit_ok(g)) return launch_implicit(g, x, nullptr, g_y, g_w, nullptr, ws, st);
+size_t ws_exact_least(const Geom& g, bool want_gw, bool want_gx) {
+  return !want_gw && gemm_path(g) && pointwise_plain(g) ? 0 : ws_exact(g, want_gw, want_gx);
+}
+
+// (layers that launch_exact leaves)
+static hipError_t launch_exact_wgrad(const Geom& g, const void* x, const void* g_y, float* g_w, void* ws,
+                                     hipStream_t st) {
   if (gemm_path(g)) {
     const void* xcol = x;
     char* wsb = static_cast<char*>(ws);
@@ -336,7 +340,6 @@ hipError_t launch_exact_wgrad(const Geom& g, const void* x, const void* g_y, flo
     if (e != hipSuccess) return e;
     return launch_finalize(part, g_w, q.Co * q.Ci, nz, 1, 1.f, st);
   }
-  if (dw_exact_onepass_ok(g)) return launch_dw_exact_onepass(g, x, nullptr, g_y, g_w, nullptr, ws, st);
   if (dw_exact_wgrad_ok(g)) return launch_dw_exact_wgrad(g, x, g_y, g_w, ws, st);
   ExactArgs a = make_args(g);
   a.x = x;
@@ -350,9 +353,9 @@ hipError_t launch_exact_wgrad(const Geom& g, const void* x, const void* g_y, flo
   return hipGetLastError();
 }
 
-hipError_t launch_exact_dgrad(const Geom& g, const void* w, const void* g_y, void* g_x, void* ws,
+hipError_t launch_exact_dgrad(const Geom& g, const void* w, const void* g_y, void* g_x, void* ws, size_t ws_bytes,
                               hipStream_t st) {
-  if (implicit_ok(g)) return launch_implicit(g, nullptr, w, g_y, nullptr, g_x, ws, st);
+  if (implicit_ok(g) && ws_bytes >= ws_implicit(g, false, true)) return launch_implicit(g, nullptr, w, g_y, nullptr, g_x, ws, st);
   if (gemm_path(g)) {
     const Geom q = dgrad_geom(g);
     if (pointwise_plain(g)) return launch_mfma_dgrad(q, g_y, w, nullptr, g_x, nullptr, st);
@@ -389,14 +392,13 @@ hipError_t launch_exact_dgrad(const Geom& g, const void* w, const void* g_y, voi
 }
 
 hipError_t launch_exact(const Geom& g, const void* x, const void* w, const void* g_y, float* g_w, void* g_x, void* ws,
-                        hipStream_t st) {
+                        size_t ws_bytes, hipStream_t st) {
+  if (!g_w) return launch_exact_dgrad(g, w, g_y, g_x, ws, ws_bytes, st);
   if (implicit_ok(g)) return launch_implicit(g, x, w, g_y, g_w, g_x, ws, st);
   if (dw_exact_onepass_ok(g)) return launch_dw_exact_onepass(g, x, w, g_y, g_w, g_x, ws, st);
-  if (g_w) {
-    const hipError_t e = launch_exact_wgrad(g, x, g_y, g_w, ws, st);
-    if (e != hipSuccess || !g_x) return e;
-  }
-  return launch_exact_dgrad(g, w, g_y, g_x, ws, st);
+  const hipError_t e = launch_exact_wgrad(g, x, g_y, g_w, ws, st);
+  if (e != hipSuccess || !g_x) return e;
+  return launch_exact_dgrad(g, w, g_y, g_x, ws, ws_bytes, st);
 }
 
 }  // namespace gf

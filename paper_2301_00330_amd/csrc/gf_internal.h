@@ -181,10 +181,11 @@ bool q8_shape_ok(const Geom& g);
 hipError_t launch_kernel_sum_q8(const Geom& g, const void* w, float inv_delta, int8_t* w_q, hipStream_t st);
 size_t ws_bwd_weight_q8(const Geom& g);
 size_t ws_bwd_input_q8(const Geom& g, bool reduced_out);
+size_t ws_bwd_input_q8_least(const Geom& g, bool reduced_out);   // the input gradient runs with this much as well
 hipError_t launch_bwd_weight_q8(const Geom& g, const int8_t* x_q, const int8_t* gy_q, float scale, float* g_w,
                                 void* ws, hipStream_t st);
 hipError_t launch_bwd_input_q8(const Geom& g, const int8_t* gy_q, const int8_t* w_q, float scale, void* g_x,
-                               bool reduced_out, void* ws, hipStream_t st);
+                               bool reduced_out, void* ws, size_t ws_bytes, hipStream_t st);
 // full-resolution g_x from an fp32 reduced map [N, C_in, H_p, W_p] (rounded once to the storage type)
 hipError_t launch_expand_f32(const Geom& g, const float* red, void* g_x, hipStream_t st);
 // the same from a reduced map in the storage type
@@ -286,12 +287,12 @@ hipError_t launch_finalize_i32(const int* part, float* g_w, int pairs, int nz, i
 
 // S5: exact K x K backward.
 size_t ws_exact(const Geom& g, bool want_gw, bool want_gx);
-// either or both gradients (the other pointer null)
+// a call runs with this much as well: the input gradient alone of a pointwise layer has a form without a workspace
+size_t ws_exact_least(const Geom& g, bool want_gw, bool want_gx);
+// either or both gradients (the other pointer null); ws_bytes: what the workspace holds, at least ws_exact_least
 hipError_t launch_exact(const Geom& g, const void* x, const void* w, const void* g_y, float* g_w, void* g_x, void* ws,
-                        hipStream_t st);
-hipError_t launch_exact_wgrad(const Geom& g, const void* x, const void* g_y, float* g_w, void* ws,
-                              hipStream_t st);
-hipError_t launch_exact_dgrad(const Geom& g, const void* w, const void* g_y, void* g_x, void* ws,
+                        size_t ws_bytes, hipStream_t st);
+hipError_t launch_exact_dgrad(const Geom& g, const void* w, const void* g_y, void* g_x, void* ws, size_t ws_bytes,
                               hipStream_t st);
 
 

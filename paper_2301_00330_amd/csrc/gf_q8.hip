@@ -16,6 +16,8 @@
 //    themselves, an fp32 map that the expansion kernels of the floating-point path replicate
 #include "gf_internal.h"
 
+#include <algorithm>
+
 namespace gf {
 
 namespace {
@@ -292,9 +294,14 @@ hipError_t launch_bwd_weight_q8(const Geom& g, const int8_t* x_q, const int8_t* 
   return hipGetLastError();
 }
 
-// the input gradient at full resolution goes through an fp32 reduced map in the workspace
+// Dense layers: the two-product launch where the caller brings its workspace.  Else the input gradient at full
+// resolution goes through an fp32 reduced map in the workspace, the reduced one (and patch rows the kernel can store)
+// needs none.  Integer sums: the same results, bit for bit.
 size_t ws_bwd_input_q8(const Geom& g, bool reduced_out) {
   if (dense_q8_ok(g)) return ws_dense_q8(g, false, true, reduced_out, false);
+  return ws_bwd_input_q8_least(g, reduced_out);
+}
+size_t ws_bwd_input_q8_least(const Geom& g, bool reduced_out) {
   if (reduced_out || q8_dgrad_full_ok(g)) return 0;
   return (size_t)g.N * g.Ci * g.P * sizeof(float);
 }
@@ -305,8 +312,8 @@ bool q8_shape_ok(const Geom& g) {
 }
 
 hipError_t launch_bwd_input_q8(const Geom& g, const int8_t* gy_q, const int8_t* w_q, float scale, void* g_x,
-                               bool reduced_out, void* ws, hipStream_t st) {
-  if (dense_q8_ok(g))
+                               bool reduced_out, void* ws, size_t ws_bytes, hipStream_t st) {
+  if (dense_q8_ok(g) && ws_bytes >= ws_bwd_input_q8(g, reduced_out))
     return launch_dense_q8(g, gy_q, 0.f, nullptr, w_q, 0.f, scale, scale, nullptr, nullptr, g_x, reduced_out, ws, st);
   const float fscale = scale / ((float)g.s * (float)g.s);
   if (reduced_out || q8_dgrad_full_ok(g))

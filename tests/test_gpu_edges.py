@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+import paper_2301_00330_amd.binding as B
 import paper_2301_00330_amd.torch_api as T
 from test_gpu_parity import TOL, mk, odesc, randn, rel_err, to64
 
@@ -327,3 +328,43 @@ def test_workspaces_of_other_kinds():
     with pytest.raises(TypeError):
         Mine.get = lambda self, nbytes: None
         T.conv_bwd_filtered(d, *args, ws=Mine())
+
+
+# N, C_in, C_out, H, W, K, stride, r: dense layers on codes; reduced maps, patch rows of 4 k patches, others
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", [(4, 64, 72, 14, 14, 3, 1, 2), (2, 40, 24, 16, 16, 1, 1, 2), (1, 32, 300, 8, 8, 3, 2, 2), (1, 16, 16, 4, 270, 1, 1, 2)])
+def test_input_gradient_on_codes_without_workspace(oracle, case, dtype):
+    """The reduced input gradient on codes takes a null workspace on every layer, the full one where patch rows are whole
+    runs and otherwise with the reduced map as workspace: bit for bit what the workspace of gf_workspace_bytes gives."""
+    N, Ci, Co, H, W, K, s, r = case
+    d = mk(N, Ci, Co, H, W, K, s, K // 2, r=r, dtype=dtype)
+    sh = T.shapes(d)
+    rng = np.random.default_rng(5)
+    gy_q, w_q = (torch.from_numpy(rng.integers(-127, 128, z).astype(np.int8)).cuda() for z in (sh["gy_u"], sh["w"][:2]))
+    p = lambda t: int(t.data_ptr())  # noqa: E731
+    for reduced in (True, False):
+        want = T.conv_bwd_input_q8(d, gy_q, w_q, 1e-3, reduced_out=reduced)
+        got = torch.full_like(want, 7.0)
+        free = reduced or (sh["gy_u"][3] % 4 == 0 and r * s in (2, 4) and W == sh["gy_u"][3] * r * s)
+        least = 0 if free else 4 * N * Ci * sh["x_u"][2] * sh["x_u"][3]
+        mem = torch.empty(max(least, 1), dtype=torch.uint8, device="cuda")
+        B.gf_conv_bwd_input_q8(d, p(gy_q), p(w_q), 1e-3, p(got), reduced, p(mem) if least else 0, least, torch.cuda.current_stream().cuda_stream)
+        assert torch.equal(got, want), reduced
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", [(2, 64, 72, 14, 14), (1, 512, 16, 4, 4), (3, 20, 13, 31, 37), (1, 8, 600, 9, 7)])
+def test_pointwise_input_gradient_without_workspace(oracle, case, dtype):
+    """The input gradient alone of a pointwise layer, vanilla BP: a null workspace is taken."""
+    N, Ci, Co, H, W = case
+    d, u = mk(N, Ci, Co, H, W, r=1, dtype=dtype), mk(N, Ci, Co, 2 * H, 2 * W, r=2, dtype=dtype)   # u: d on its patch grid
+    sh = T.shapes(d)
+    w, gy = randn(sh["w"], 1, dtype), randn(sh["g_y"], 2, dtype)
+    _, ref = oracle.bwd_exact(odesc(oracle, d), np.zeros(sh["x"]), to64(w), to64(gy))
+    wg, gg, st = w.cuda(), gy.cuda(), torch.cuda.current_stream().cuda_stream
+    for call in (lambda o: B.gf_conv_bwd_exact(d, 0, int(wg.data_ptr()), int(gg.data_ptr()), 0, o, 0, 0, st),
+                 lambda o: B.gf_conv_bwd_input(d, int(gg.data_ptr()), int(wg.data_ptr()), o, False, 0, 0, st),
+                 lambda o: B.gf_conv_bwd_unique(u, int(gg.data_ptr()), 0, int(wg.data_ptr()), 0, o, True, 0, 0, st)):
+        out = torch.empty(sh["x"], dtype=gy.dtype, device="cuda")
+        call(int(out.data_ptr()))
+        assert rel_err(out, ref) <= TOL[dtype]
