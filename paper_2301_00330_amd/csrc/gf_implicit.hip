@@ -650,6 +650,33 @@ __device__ __forceinline__ int cdiv_dev(int a, int b) { return (a + b - 1) / b; 
 
 constexpr int kFinTaps = 9;   // taps a pass of a block holds
 
+// where the VE pixels from e0 on (over planes of H x W) stand in `planes` planes of every phase
+template <int VE>
+__device__ __forceinline__ void interleave_offsets(const FinalArgs& a, int e0, int planes, int (&at)[VE]) {
+  const int PQ = a.Hq * a.Wq;
+  const int r0 = (int)a.d_w.div((uint32_t)e0);
+  int w = e0 - r0 * a.W;
+  int pl = (int)a.d_h.div((uint32_t)r0), h = r0 - pl * a.H;
+#pragma unroll
+  for (int k = 0; k < VE; ++k) {
+    const int hs = (int)a.d_s.div((uint32_t)h), ws = (int)a.d_s.div((uint32_t)w);
+    at[k] = (((h - hs * a.s) * a.s + w - ws * a.s) * planes + pl) * PQ + hs * a.Wq + ws;
+    if (++w == a.W) {
+      w = 0;
+      if (++h == a.H) { h = 0; ++pl; }
+    }
+  }
+}
+
+template <class T, int VE>
+__device__ __forceinline__ void put_run(T* dst, int e0, int total, const T (&v)[VE]) {
+  if (e0 + VE <= total) {
+    *reinterpret_cast<uint4*>(dst + e0) = *reinterpret_cast<const uint4*>(v);
+  } else {
+    for (int k = 0; e0 + k < total; ++k) dst[e0 + k] = v[k];
+  }
+}
+
 template <class T>
 __global__ __launch_bounds__(kT) void xfinal_k(FinalArgs a) {
   const int tid = threadIdx.x;
@@ -685,8 +712,8 @@ __global__ __launch_bounds__(kT) void xfinal_k(FinalArgs a) {
     }
     return;
   }
-  // g_x[n, ci, h, w] = gxq[phase(h mod s, w mod s)][n, ci, h / s, w / s]: a block stages ppb consecutive planes of
-  // every phase -- one contiguous run each, at element alignment -- and writes their pixels as one aligned run (a
+  // g_x[n, ci, h, w] = gxq[phase(h mod s, w mod s)][n, ci, h / s, w / s].  Small planes: a block stages ppb consecutive
+  // planes of every phase -- one contiguous run each, at element alignment -- and writes their pixels as one aligned run (a
   // gather of two-byte elements from memory took 15 us for 12.8 MB).
   constexpr int VE = El<T>::VE;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -695,6 +722,17 @@ __global__ __launch_bounds__(kT) void xfinal_k(FinalArgs a) {
   const int pl0 = ((int)blockIdx.x - a.w_blocks) * a.ppb, np = min(a.ppb, a.NC - pl0);
   const T* gxq = static_cast<const T*>(a.gxq);
   T* gx = static_cast<T*>(a.gx);
+  if (a.ppb == 0) {   // large planes: a vector per lane, gathered from the phase planes
+    const int e0 = (((int)blockIdx.x - a.w_blocks) * kT + tid) * VE, total = a.NC * HW;
+    if (e0 >= total) return;
+    int at[VE];
+    interleave_offsets<VE>(a, e0, a.NC, at);
+    __attribute__((aligned(16))) T v[VE];
+#pragma unroll
+    for (int k = 0; k < VE; ++k) v[k] = gxq[e0 + k < total ? at[k] : at[0]];
+    put_run(gx, e0, total, v);
+    return;
+  }
   const int run = np * PQ, runv = cdiv_dev(run, VE);
   for (int i = tid; i < nph * runv; i += kT) {
     const int ph = i / runv, v = i - ph * runv;
@@ -716,24 +754,12 @@ __global__ __launch_bounds__(kT) void xfinal_k(FinalArgs a) {
   const int total = np * HW;
   T* dst = gx + (long)pl0 * HW;   // (host: ppb * H * W is a multiple of VE)
   for (int e0 = tid * VE; e0 < total; e0 += kT * VE) {
-    const int r0 = (int)a.d_w.div((uint32_t)e0);
-    int w = e0 - r0 * a.W;
-    int pl = (int)a.d_h.div((uint32_t)r0), h = r0 - pl * a.H;
+    int at[VE];
+    interleave_offsets<VE>(a, e0, a.ppb, at);
     __attribute__((aligned(16))) T v[VE];
 #pragma unroll
-    for (int k = 0; k < VE; ++k) {
-      const int hs = (int)a.d_s.div((uint32_t)h), ws = (int)a.d_s.div((uint32_t)w);
-      v[k] = lds[min((((h - hs * a.s) * a.s + w - ws * a.s) * a.ppb + pl) * PQ + hs * a.Wq + ws, nph * a.ppb * PQ - 1)];
-      if (++w == a.W) {
-        w = 0;
-        if (++h == a.H) { h = 0; ++pl; }
-      }
-    }
-    if (e0 + VE <= total) {
-      *reinterpret_cast<uint4*>(dst + e0) = *reinterpret_cast<const uint4*>(v);
-    } else {
-      for (int k = 0; e0 + k < total; ++k) dst[e0 + k] = v[k];
-    }
+    for (int k = 0; k < VE; ++k) v[k] = lds[min(at[k], nph * a.ppb * PQ - 1)];
+    put_run(dst, e0, total, v);
   }
 }
 
@@ -848,7 +874,7 @@ XPlan make_plan(const Geom& g, bool want_gw, bool want_gx) {
 }
 
 // planes a block of the interleave stages: a multiple of VE (runs start on vector boundaries), about 16 KB, and
-// enough blocks for the chip; 0 where that many planes do not fit LDS
+// enough blocks for the chip; 0 where that many planes do not fit LDS (from 56 x 56 on): gathered from memory
 int interleave_planes(const Geom& g, const XGeo& q) {
   const int VE = 16 / g.b;
   const long plane = (long)q.nph * q.PQ * g.b;
@@ -930,8 +956,8 @@ hipError_t implicit_t(const Geom& g, const void* x, const void* w, const void* g
   int i_blocks = 0;
   if (inter) {
     f.ppb = interleave_planes(g, q);
-    lds = (size_t)q.nph * f.ppb * q.PQ * sizeof(T) + 16;
-    i_blocks = cdiv(f.NC, f.ppb);
+    lds = f.ppb ? (size_t)q.nph * f.ppb * q.PQ * sizeof(T) + 16 : 0;
+    i_blocks = f.ppb ? cdiv(f.NC, f.ppb) : cdiv(cdiv((long)f.NC * g.H * g.W, VE), kT);
   }
   GF_LAUNCH(xfinal_k<T>, dim3(f.w_blocks + i_blocks), dim3(kT), lds, st, f);
   return hipGetLastError();
@@ -1005,7 +1031,6 @@ bool implicit_ok(const Geom& g) {
   const long reach = max_shift(g, q) + 1024;
   const long tx = (long)q.nph * g.N * g.Ci * q.PQ, ty = (long)g.N * g.Co * q.PY;
   if (tx < ve || ty < ve) return false;
-  if (g.s > 1 && interleave_planes(g, q) == 0) return false;
   if (tx + reach + pqp >= lim || ty + reach + pyp >= lim) return false;
   if ((long)g.N * g.Ci * g.H * g.W >= lim) return false;
   if ((long)g.N * pqp + 1024 >= lim || (long)g.N * pyp + 1024 >= lim) return false;

@@ -345,6 +345,16 @@ def test_pool_batch_q8_needs_step_sizes(lib):
             T.pool_activation_batch_q8(descs, [None] * len(descs), None)
 
 
+@pytest.mark.parametrize("dtype,b", [(0, 4), (1, 2)])
+def test_strided_vanilla_layers_take_no_column_tensor(lib, dtype, b):
+    """Vanilla BP of strided layers on large maps: phase planes of x and g_x and K slabs, not K_h K_w copies of a map."""
+    for N, Ci, Co, H, K, s in ((8, 64, 128, 112, 3, 2), (1, 8, 64, 512, 5, 4), (4, 24, 96, 56, 5, 2), (2, 3, 32, 224, 3, 2)):
+        d = B.ConvDesc(N=N, C_in=Ci, C_out=Co, H_in=H, W_in=H, K_h=K, K_w=K, stride=s, pad=K // 2, r=1, dtype=dtype)
+        maps = 2.2 * b * N * Ci * H * H
+        slabs = 4 * 520 * (K * K * Co * Ci if Co * Ci < 4096 else 4 * 4096)   # at most about two tiles per block of the chip
+        assert B.gf_workspace_bytes(d, B.GF_OP_BWD_EXACT) < maps + slabs, (N, Ci, Co, H, K, s)
+
+
 def test_unique_elements_entry_host_checks(lib):
     """gf_conv_bwd_unique: stride-1 layers whose padding keeps the map size; workspace = vanilla BP on
     the patch grid plus the reduced g_x."""

@@ -99,6 +99,10 @@ EXACT_CASES = [
     (3, 17, 33, 21, 19, 1, 1, 0, 1),    # pointwise: the two-product launch on the maps themselves, odd planes
     (2, 12, 20, 40, 130, 3, 4, 1, 1),   # stride 4, wide phase planes
     (300, 8, 16, 6, 6, 3, 1, 1, 1),     # many images, small maps: many slabs of one weight tile
+    (2, 24, 40, 112, 112, 3, 2, 1, 1),  # strided on planes that no block can stage: gathered from the phase planes
+    (1, 9, 7, 131, 77, 3, 2, 1, 1),     # ... of odd extents, pixels that are no whole vectors
+    (1, 8, 16, 200, 198, 5, 4, 2, 1),   # ... 16 phases
+    (3, 16, 24, 57, 57, 1, 2, 0, 1),    # ... pointwise
 ]
 
 
