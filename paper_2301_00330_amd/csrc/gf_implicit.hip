@@ -874,7 +874,8 @@ XPlan make_plan(const Geom& g, bool want_gw, bool want_gx) {
 }
 
 // planes a block of the interleave stages: a multiple of VE (runs start on vector boundaries), about 16 KB, and
-// enough blocks for the chip; 0 where that many planes do not fit LDS (from 56 x 56 on): gathered from memory
+// enough blocks for the chip; 0 where that many planes do not fit LDS (from 56 x 56 on): gathered from memory (64 ->
+// 128 channels, 112 x 112, stride 2, n = 8, both gradients: 53 us in bf16, 109 in fp32; through a column tensor 370, 568)
 int interleave_planes(const Geom& g, const XGeo& q) {
   const int VE = 16 / g.b;
   const long plane = (long)q.nph * q.PQ * g.b;
