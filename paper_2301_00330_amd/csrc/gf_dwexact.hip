@@ -500,30 +500,15 @@ __global__ __launch_bounds__(kThreads, K == 3 ? 7 : 3) void dw_exact_onepass_k(D
           win[u][4 * k] = q.x; win[u][4 * k + 1] = q.y; win[u][4 * k + 2] = q.z; win[u][4 * k + 3] = q.w;
         }
       if (a.part) {
-        float xv[kQ], chk = 0.f;
+        float xv[kQ];
 #pragma unroll
-        for (int e = 0; e < kQ; ++e) {
-          xv[e] = to_f32(xq.v[e]);
-          chk += xv[e] * 0.f;
-        }
-        if (chk == 0.f) {
+        for (int e = 0; e < kQ; ++e) xv[e] = to_f32(xq.v[e]);
 #pragma unroll
-          for (int u = 0; u < K; ++u)
+        for (int u = 0; u < K; ++u)
 #pragma unroll
-            for (int v = 0; v < K; ++v)
+          for (int v = 0; v < K; ++v)
 #pragma unroll
-              for (int e = 0; e < kQ; ++e) aw[u * K + v] += xv[e] * win[K - 1 - u][e + K - 1 - v];
-        } else {   // an infinity or NaN times the zeros of the frame would reach taps that leave the map
-#pragma unroll
-          for (int u = 0; u < K; ++u)
-#pragma unroll
-            for (int v = 0; v < K; ++v)
-#pragma unroll
-              for (int e = 0; e < kQ; ++e) {
-                const int i = h + a.p - u, j = w0 + e + a.p - v;
-                if (i >= 0 && i < a.Hy && j >= 0 && j < a.Wy && e < cnt) aw[u * K + v] += xv[e] * win[K - 1 - u][e + K - 1 - v];
-              }
-        }
+            for (int e = 0; e < kQ; ++e) aw[u * K + v] += xv[e] * win[K - 1 - u][e + K - 1 - v];
       }
       if (a.gx) {
         float acc[kQ];
@@ -549,6 +534,31 @@ __global__ __launch_bounds__(kThreads, K == 3 ? 7 : 3) void dw_exact_onepass_k(D
     }
   }
   if (!a.part) return;
+  // The zeros of the frame, and of x past the end of a row, meet every tap, also the ones that do not read there; with an
+  // infinity or a NaN on the other side that is a NaN.  Where the sums of the block are not all finite, they are
+  // formed again from what lies inside the map.
+  float fin = 0.f;
+#pragma unroll
+  for (int t = 0; t < K * K; ++t) fin = __builtin_fmaf(aw[t], 0.f, fin);
+  if (__syncthreads_or(fin != 0.f)) {
+#pragma unroll
+    for (int t = 0; t < K * K; ++t) aw[t] = 0.f;
+    for (int n = n0; n < n1; ++n) {
+      const T* gy = static_cast<const T*>(a.gy) + n * cHWy + (long)c * HWy;
+      const T* x = static_cast<const T*>(a.x) + n * cHW + (long)c * HW;
+      for (int e = tid; e < HW; e += kThreads) {
+        const int h = e / a.W, w = e - h * a.W;
+        const float xv = to_f32(x[e]);
+#pragma unroll
+        for (int u = 0; u < K; ++u)
+#pragma unroll
+          for (int v = 0; v < K; ++v) {
+            const int i = h + a.p - u, j = w + a.p - v;
+            if (i >= 0 && i < a.Hy && j >= 0 && j < a.Wy) aw[u * K + v] += xv * to_f32(gy[i * a.Wy + j]);
+          }
+      }
+    }
+  }
 #pragma unroll
   for (int t = 0; t < K * K; ++t)
     for (int m = 32; m > 0; m >>= 1) aw[t] += __shfl_xor(aw[t], m, 64);
