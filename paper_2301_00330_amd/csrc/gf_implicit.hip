@@ -673,7 +673,9 @@ __device__ __forceinline__ void put_run(T* dst, int e0, int total, const T (&v)[
   if (e0 + VE <= total) {
     *reinterpret_cast<uint4*>(dst + e0) = *reinterpret_cast<const uint4*>(v);
   } else {
-    for (int k = 0; e0 + k < total; ++k) dst[e0 + k] = v[k];
+#pragma unroll
+    for (int k = 0; k < VE; ++k)
+      if (e0 + k < total) dst[e0 + k] = v[k];
   }
 }
 
