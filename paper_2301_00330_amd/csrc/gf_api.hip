@@ -187,7 +187,7 @@ static size_t ws_need(const Geom& g, int op, bool reduced_out) {
     case GF_OP_BWD_FILTERED_Q8:
       return ws_filtered_q8(g, true, nullptr, nullptr, nullptr);
     case GF_OP_BWD_WEIGHT:
-      return g.r == 1 ? ws_exact(g, true, false) : gemm_ok(g) ? ws_dense(g, true, false, false, false) : ws_bwd_weight(g);
+      return g.r == 1 ? ws_exact(g, true, false) : dense_weight_ok(g) ? ws_dense(g, true, false, false, false) : ws_bwd_weight(g);
     case GF_OP_BWD_INPUT:
       return g.r == 1 ? ws_exact(g, false, true) : gemm_ok(g) ? std::max(ws_dense(g, false, true, false, false), ws_dense(g, false, true, true, false)) : ws_bwd_input(g, reduced_out);
     default:
@@ -425,7 +425,7 @@ gf_status gf_conv_bwd_weight(const gf_conv_desc* desc, const void* x_u, const vo
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (g.r == 1) return dev(launch_exact(g, x_u, nullptr, gy_u, g_w, nullptr, ws, ws_bytes, st));
-  if (gemm_ok(g)) return dev(launch_dense(g, gy_u, false, x_u, nullptr, nullptr, g_w, nullptr, false, nullptr, ws, st));
+  if (dense_weight_ok(g)) return dev(launch_dense(g, gy_u, false, x_u, nullptr, nullptr, g_w, nullptr, false, nullptr, ws, st));
   return dev(launch_gf_bwd_weight(g, x_u, gy_u, g_w, ws, st));
 }
 

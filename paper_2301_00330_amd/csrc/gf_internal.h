@@ -267,6 +267,7 @@ bool mfma_dgrad_writes_full(const Geom& g);
 bool gemm_ok(const Geom& g);
 bool gemm_maps_ok(const Geom& g);
 bool dense_ok(const Geom& g);
+bool dense_weight_ok(const Geom& g);   // ... the layers whose weight gradient alone it takes
 size_t ws_dense(const Geom& g, bool want_w, bool want_d, bool reduced, bool own_gyu);
 hipError_t launch_dense(const Geom& g, const void* src, bool src_is_gy, const void* x_u, const void* w,
                         void* gy_u_out, float* g_w, void* g_x, bool reduced, const void* mask_u, void* ws,

@@ -384,3 +384,21 @@ def test_pointwise_input_gradient_without_workspace(oracle, case, dtype):
         out = torch.empty(sh["x"], dtype=gy.dtype, device="cuda")
         call(int(out.data_ptr()))
         assert rel_err(out, ref) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", [
+    (1, 40, 30, 18, 18, 1, 1, 2),      # K of a few chunks: one launch
+    (1, 8, 16, 24, 44, 3, 1, 2),       # ... and 3 x 3 taps: 5 chunks in bf16, past the rule's edge; 9 in fp32
+    (1, 24, 40, 16, 32, 3, 1, 2),      # 2 and 4 chunks
+    (8, 64, 128, 56, 56, 3, 2, 2),     # several slabs, aligned planes: contraction and slab sums apart
+    (3, 5, 9, 30, 34, 3, 1, 2),        # ... planes and channels that are no whole vectors
+    (4, 296, 8, 52, 52, 1, 1, 2),
+])
+def test_weight_gradient_alone(oracle, case, dtype):
+    N, Ci, Co, H, W, K, s, r = case
+    d = mk(N, Ci, Co, H, W, K, s, K // 2, r=r, dtype=dtype)
+    sh = T.shapes(d)
+    x_u, gy_u = randn(sh["x_u"], 1, dtype), randn(sh["gy_u"], 2, dtype)
+    g_w = T.conv_bwd_weight(d, x_u.cuda(), gy_u.cuda())
+    assert rel_err(g_w, oracle.bwd_weight(odesc(oracle, d), to64(x_u), to64(gy_u))) <= 1e-5   # fp32 sums of either type
