@@ -8,6 +8,7 @@
 //  * other grouped layers: shape-generic direct kernels, one lane per g_x element
 //    (gather over the taps that reach it) and one block per weight-gradient element.
 #include "gf_internal.h"
+#include <algorithm>
 
 namespace gf {
 
@@ -307,7 +308,20 @@ ExactArgs make_args(const Geom& g) {
 
 }  // namespace
 
+// The weight gradient of a layer with few input channels that are no whole vectors (the first layer of a network): the
+// implicit GEMM gives every tap a tile of 64 columns of which C_in are used; over the column tensor one tile or a
+// few hold all taps.  Alone: 3 -> 32 channels, 3 x 3, 224 x 224, stride 2, n = 8 88 -> 42 us in fp32, 38 -> 31 in bf16; 4 ->
+// 27, 5 x 5, 120 x 120, n = 6, bf16 76 -> 26; 7 -> 4, 5 x 5, 77 x 77, n = 84, fp32 842 -> 346.  Both gradients share one
+// implicit launch, which wins until the weights alone take several rounds of blocks (3 -> 32 in bf16 69 / 77, 6 -> 64,
+// 25 x 31, n = 2 19 / 32; 7 -> 4 1059 / 743).
+static bool wgrad_by_columns(const Geom& g, bool want_gx) {
+  if (g.Ci >= 8 || g.KK == 1 || g.Ci * g.KK > 192 || g.Ci % (16 / g.b) == 0 || !gemm_path(g) || !implicit_ok(g)) return false;
+  return !want_gx || (long)g.KK * g.N * g.Hy * g.Wy * g.b / 128 > 65536;
+}
+
 size_t ws_exact(const Geom& g, bool want_gw, bool want_gx) {
+  if (want_gw && wgrad_by_columns(g, want_gx))
+    return std::max(col_bytes(g, true, false) + aux_bytes(g, true, false), want_gx ? ws_implicit(g, false, true) : 0);
   if (implicit_ok(g)) return ws_implicit(g, want_gw, want_gx);
   if (!gemm_path(g)) return want_gw && (dw_exact_wgrad_ok(g) || dw_exact_onepass_ok(g)) ? ws_dw_exact_wgrad(g) : 0;
   return col_bytes(g, want_gw, want_gx) + aux_bytes(g, want_gw, want_gx);
@@ -394,7 +408,7 @@ hipError_t launch_exact_dgrad(const Geom& g, const void* w, const void* g_y, voi
 hipError_t launch_exact(const Geom& g, const void* x, const void* w, const void* g_y, float* g_w, void* g_x, void* ws,
                         size_t ws_bytes, hipStream_t st) {
   if (!g_w) return launch_exact_dgrad(g, w, g_y, g_x, ws, ws_bytes, st);
-  if (implicit_ok(g)) return launch_implicit(g, x, w, g_y, g_w, g_x, ws, st);
+  if (implicit_ok(g) && !wgrad_by_columns(g, g_x != nullptr)) return launch_implicit(g, x, w, g_y, g_w, g_x, ws, st);
   if (dw_exact_onepass_ok(g)) return launch_dw_exact_onepass(g, x, w, g_y, g_w, g_x, ws, st);
   const hipError_t e = launch_exact_wgrad(g, x, g_y, g_w, ws, st);
   if (e != hipSuccess || !g_x) return e;

@@ -103,6 +103,10 @@ EXACT_CASES = [
     (1, 9, 7, 131, 77, 3, 2, 1, 1),     # ... of odd extents, pixels that are no whole vectors
     (1, 8, 16, 200, 198, 5, 4, 2, 1),   # ... 16 phases
     (3, 16, 24, 57, 57, 1, 2, 0, 1),    # ... pointwise
+    (2, 3, 32, 40, 38, 3, 2, 1, 1),     # few input channels: weights over the column tensor
+    (2, 7, 9, 21, 23, 5, 1, 2, 1),      # ... 175 columns
+    (2, 3, 8, 512, 560, 3, 1, 1, 1),    # ... with both gradients as well
+    (1, 7, 12, 20, 20, 7, 1, 3, 1),     # ... 343: implicit
 ]
 
 
