@@ -167,12 +167,18 @@ static size_t ws_unique(const Geom& g, const Geom& red, bool want_gw, bool want_
   return o;
 }
 
+// vanilla BP of whichever gradients a call asks for (one alone may take another path, and more, than both)
+static size_t ws_exact_any(const Geom& g) {
+  return std::max(ws_exact(g, true, true), std::max(ws_exact(g, true, false), ws_exact(g, false, true)));
+}
+
 static size_t ws_need(const Geom& g, int op, bool reduced_out) {
   switch (op) {
     case GF_OP_BWD_UNIQUE: {
       Geom red;
-      if (g.r == 1 || g.s != 1 || unique_geom(g, &red) != GF_OK) return ws_exact(g, true, true);
-      return ws_unique(g, red, true, true, false, nullptr);
+      if (g.r == 1 || g.s != 1 || unique_geom(g, &red) != GF_OK) return ws_exact_any(g);
+      return std::max(ws_unique(g, red, true, true, false, nullptr),
+                      std::max(ws_unique(g, red, true, false, false, nullptr), ws_unique(g, red, false, true, false, nullptr)));
     }
     case GF_OP_BWD_FILTERED:
       return ws_filtered(g, true, nullptr, nullptr);
@@ -191,7 +197,7 @@ static size_t ws_need(const Geom& g, int op, bool reduced_out) {
     case GF_OP_BWD_INPUT:
       return g.r == 1 ? ws_exact(g, false, true) : gemm_ok(g) ? std::max(ws_dense(g, false, true, false, false), ws_dense(g, false, true, true, false)) : ws_bwd_input(g, reduced_out);
     default:
-      return ws_exact(g, true, true);
+      return ws_exact_any(g);
   }
 }
 

@@ -355,6 +355,20 @@ def test_strided_vanilla_layers_take_no_column_tensor(lib, dtype, b):
         assert B.gf_workspace_bytes(d, B.GF_OP_BWD_EXACT) < maps + slabs, (N, Ci, Co, H, K, s)
 
 
+def test_workspace_covers_each_gradient_alone(lib):
+    """The size named for vanilla BP is enough for either gradient alone, whichever path each takes (random layers)."""
+    import random
+    rng = random.Random(4)
+    for _ in range(20000):
+        g = rng.choice([1, 1, 1, 2])
+        ci, co = g * rng.choice([1, 3, 4, 7, 8, 9, 64, 130]), g * rng.choice([1, 4, 8, 15, 64, 200])
+        K = rng.choice([1, 3, 5])
+        d = B.ConvDesc(N=rng.choice([1, 3, 16, 90]), C_in=ci, C_out=co, H_in=rng.randint(5, 120), W_in=rng.randint(5, 120), K_h=K, K_w=K,
+                       stride=rng.choice([1, 1, 2, 3]), pad=K // 2, groups=g, r=1, dtype=rng.choice([0, 1]))
+        both = B.gf_workspace_bytes(d, B.GF_OP_BWD_EXACT)
+        assert both >= max(B.gf_workspace_bytes(d, B.GF_OP_BWD_WEIGHT), B.gf_workspace_bytes(d, B.GF_OP_BWD_INPUT)), d
+
+
 def test_unique_elements_entry_host_checks(lib):
     """gf_conv_bwd_unique: stride-1 layers whose padding keeps the map size; workspace = vanilla BP on
     the patch grid plus the reduced g_x."""
