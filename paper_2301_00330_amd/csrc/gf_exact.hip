@@ -308,19 +308,21 @@ ExactArgs make_args(const Geom& g) {
 
 }  // namespace
 
-// The weight gradient of a layer with few input channels that are no whole vectors (the first layer of a network): the
-// implicit GEMM gives every tap a tile of 64 columns of which C_in are used; over the column tensor one tile or a
-// few hold all taps.  Alone: 3 -> 32 channels, 3 x 3, 224 x 224, stride 2, n = 8 88 -> 42 us in fp32, 38 -> 31 in bf16; 4 ->
-// 27, 5 x 5, 120 x 120, n = 6, bf16 76 -> 26; 7 -> 4, 5 x 5, 77 x 77, n = 84, fp32 842 -> 346.  Both gradients share one
-// implicit launch, which wins until the weights alone take several rounds of blocks (3 -> 32 in bf16 69 / 77, 6 -> 64,
-// 25 x 31, n = 2 19 / 32; 7 -> 4 1059 / 743).
-static bool wgrad_by_columns(const Geom& g, bool want_gx) {
+// The weight gradient of a layer with few input channels that are no whole vectors: the implicit GEMM gives every tap a
+// tile of 64 columns of which C_in are used; over the column tensor one tile or a few hold all taps.  The implicit launch
+// does both gradients side by side and wins until the weights take several rounds of blocks, the sooner the fewer the
+// channels.  Both gradients / g_w alone, us, implicit and over columns: 7 -> 4 channels, 5 x 5, 77 x 77, n = 84, fp32 1059 /
+// 842 and 743 / 346; 3 -> 32, 3 x 3, 224 x 224, stride 2, n = 8, fp32 126 / 88 and 102 / 42, bf16 69 / 38 and 77 / 31;
+// 4 -> 27, 5 x 5, 120 x 120, n = 6, bf16 109 / 76 and 87 / 26; 6 -> 56, 3 x 3, 17 x 101, n = 117, bf16 109 / 73 and 120 / 63.
+// (The same path whether or not g_x is wanted: g_w has the same bits either way.)
+static bool wgrad_by_columns(const Geom& g) {
   if (g.Ci >= 8 || g.KK == 1 || g.Ci * g.KK > 192 || g.Ci % (16 / g.b) == 0 || !gemm_path(g) || !implicit_ok(g)) return false;
-  return !want_gx || (long)g.KK * g.N * g.Hy * g.Wy * g.b / 128 > 65536;
+  const long steps = (long)g.KK * g.N * g.Hy * g.Wy * g.b / 128;   // chunks of K over all taps
+  return steps * (8 - g.Ci) > 80000;
 }
 
 size_t ws_exact(const Geom& g, bool want_gw, bool want_gx) {
-  if (want_gw && wgrad_by_columns(g, want_gx))
+  if (want_gw && wgrad_by_columns(g))
     return std::max(col_bytes(g, true, false) + aux_bytes(g, true, false), want_gx ? ws_implicit(g, false, true) : 0);
   if (implicit_ok(g)) return ws_implicit(g, want_gw, want_gx);
   if (!gemm_path(g)) return want_gw && (dw_exact_wgrad_ok(g) || dw_exact_onepass_ok(g)) ? ws_dw_exact_wgrad(g) : 0;
@@ -408,7 +410,7 @@ hipError_t launch_exact_dgrad(const Geom& g, const void* w, const void* g_y, voi
 hipError_t launch_exact(const Geom& g, const void* x, const void* w, const void* g_y, float* g_w, void* g_x, void* ws,
                         size_t ws_bytes, hipStream_t st) {
   if (!g_w) return launch_exact_dgrad(g, w, g_y, g_x, ws, ws_bytes, st);
-  if (implicit_ok(g) && !wgrad_by_columns(g, g_x != nullptr)) return launch_implicit(g, x, w, g_y, g_w, g_x, ws, st);
+  if (implicit_ok(g) && !wgrad_by_columns(g)) return launch_implicit(g, x, w, g_y, g_w, g_x, ws, st);
   if (dw_exact_onepass_ok(g)) return launch_dw_exact_onepass(g, x, w, g_y, g_w, g_x, ws, st);
   const hipError_t e = launch_exact_wgrad(g, x, g_y, g_w, ws, st);
   if (e != hipSuccess || !g_x) return e;

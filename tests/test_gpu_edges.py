@@ -103,10 +103,9 @@ EXACT_CASES = [
     (1, 9, 7, 131, 77, 3, 2, 1, 1),     # ... of odd extents, pixels that are no whole vectors
     (1, 8, 16, 200, 198, 5, 4, 2, 1),   # ... 16 phases
     (3, 16, 24, 57, 57, 1, 2, 0, 1),    # ... pointwise
-    (2, 3, 32, 40, 38, 3, 2, 1, 1),     # few input channels: weights over the column tensor
-    (2, 7, 9, 21, 23, 5, 1, 2, 1),      # ... 175 columns
-    (2, 3, 8, 512, 560, 3, 1, 1, 1),    # ... with both gradients as well
-    (1, 7, 12, 20, 20, 7, 1, 3, 1),     # ... 343: implicit
+    (2, 3, 32, 40, 38, 3, 2, 1, 1),     # few input channels, a small map
+    (1, 3, 8, 512, 560, 3, 1, 1, 1),    # ... a large one: weights over the column tensor
+    (9, 7, 4, 150, 149, 5, 1, 2, 1),    # ... 175 columns
 ]
 
 
@@ -122,7 +121,7 @@ def test_vanilla_products(oracle, case, dtype):
     _, o_x = T.conv_bwd_exact(d, x.cuda(), w.cuda(), gy.cuda(), want_gw=False)
     r_w, r_x = oracle.bwd_exact(odesc(oracle, d), to64(x), to64(w), to64(gy))
     for a, b, r in ((g_w, o_w, r_w), (g_x, o_x, r_x)):
-        assert rel_err(a, r) <= TOL[dtype] and rel_err(b, r) <= TOL[dtype]
+        assert rel_err(a, r) <= TOL[dtype] and torch.equal(a, b)
 
 
 # N, C, H, W, K, padding: both gradients of a depthwise layer in one pass (ragged groups of pixels, frames, image runs)
