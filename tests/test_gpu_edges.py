@@ -252,7 +252,8 @@ def test_reductions_of_long_runs_of_planes(C, H, W):
 @pytest.mark.parametrize("case", [
     (3, 72, 40, 61, 47, 3, 1, 8),      # few tiles of large planes: bands of one patch row, ragged in both directions
     (2, 16, 24, 64, 48, 1, 2, 8),      # strided
-    (256, 8, 8, 40, 40, 1, 1, 8),      # as many tiles as CUs: whole images
+    (256, 8, 8, 40, 40, 1, 1, 8),      # more tiles, still bands
+    (400, 8, 8, 40, 40, 1, 1, 8),      # enough of them: whole images
 ])
 def test_large_patches_of_few_images(oracle, case, dtype):
     check_filtered(oracle, case, dtype)
