@@ -77,6 +77,14 @@ def test_static_scratch_entry_host_checks(lib):
     assert m and int(m.group(1)) << int(m.group(2)) == B.GF_STATIC_SCRATCH_BYTES
 
 
+def test_one_call_backward_within_the_static_scratch(lib):
+    """Layers whose gy_u leaves little of the library's scratch: fewer slabs of the weight gradient, not a refusal."""
+    for N, Ci, Co, H, W, K, s, r, dtype in ((64, 8, 64, 56, 245, 3, 1, 2, 0), (4, 24, 1280, 100, 100, 3, 1, 2, 0), (256, 4, 512, 33, 33, 3, 1, 3, 0),
+                                            (128, 4, 256, 65, 65, 3, 1, 3, 0), (64, 64, 512, 8, 140, 5, 1, 2, 0), (2, 144, 512, 112, 161, 3, 1, 2, 0)):
+        d = B.ConvDesc(N=N, C_in=Ci, C_out=Co, H_in=H, W_in=W, K_h=K, K_w=K, stride=s, pad=K // 2, r=r, dtype=dtype)
+        assert B.gf_workspace_bytes(d, B.GF_OP_BWD_FILTERED) <= B.GF_STATIC_SCRATCH_BYTES, d
+
+
 OK = dict(N=2, C_in=4, C_out=8, H_in=8, W_in=8, K_h=3, K_w=3, pad=1, r=2)
 FAKE = 0x1000  # non-null, 16-byte aligned; never dereferenced because validation fails first
 
