@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import glob
 import os
+import shutil
 import subprocess
 import sys
 from concurrent.futures import ThreadPoolExecutor
@@ -37,10 +38,13 @@ def sources():
 
 def _torch_module_cmds(cc: str):
     """Compile and link commands of the host module (no device code): torch's headers and libraries, and libgf.so
-    beside it."""
+    beside it.  None where torch is not installed: the C library stands without it."""
     import sysconfig
-    import torch
-    from torch.utils import cpp_extension as ext
+    try:
+        import torch
+        from torch.utils import cpp_extension as ext
+    except ImportError:
+        return None
     obj = os.path.join(OBJ, "gf_torch.o")
     inc = [f"-I{p}" for p in ext.include_paths() + [os.path.join(ROOT, "include"), sysconfig.get_paths()["include"]]]
     inc += ["-isystem", "/opt/rocm/include"]
@@ -68,22 +72,30 @@ def build(verbose: bool = False) -> str:
             print(err, file=sys.stderr)
         return obj
 
-    torch_compile, torch_link = _torch_module_cmds("g++")
-
     def run(cmd, what):
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:
             raise RuntimeError(f"{what} failed:\n{r.stderr}")
 
+    host_cc = os.environ.get("CXX") or shutil.which("g++") or cc   # (hipcc compiles host code as well)
+
+    def torch_unit():   # -> the link command
+        cmds = _torch_module_cmds(host_cc)
+        if cmds:
+            run(cmds[0], f"compiler for {TORCH_SRC}")
+        return cmds and cmds[1]
+
     with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as ex:
-        host = ex.submit(run, torch_compile, f"compiler for {TORCH_SRC}")
+        torch_link = ex.submit(torch_unit)
         objs = list(ex.map(one, sources()))
-        host.result()
     r = subprocess.run([cc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB],
                        capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)
-    run(torch_link, "link of the torch module")
+    if torch_link.result():
+        run(torch_link.result(), "link of the torch module")
+    else:
+        print("torch is not installed: libgf.so alone, without the module behind torch_api", file=sys.stderr)
     # the measurement probes of bench.py --ceilings: a library of their own, never loaded by the product path
     r = subprocess.run([cc, *HIPCC_FLAGS, "-shared", PROBE_SRC, "-o", PROBE_LIB], capture_output=True, text=True)
     if r.returncode != 0:

@@ -377,6 +377,27 @@ def test_workspace_covers_each_gradient_alone(lib):
         assert both >= max(B.gf_workspace_bytes(d, B.GF_OP_BWD_WEIGHT), B.gf_workspace_bytes(d, B.GF_OP_BWD_INPUT)), d
 
 
+def test_c_library_builds_without_torch(tmp_path):
+    """The build of libgf.so asks neither for torch nor for a host compiler of its own: with torch missing and stand-ins
+    for the compilers, every unit is compiled, the library linked, and the torch module left out."""
+    import stat
+    import subprocess
+    import sys
+    log = tmp_path / "log"
+    cc = tmp_path / "hipcc"
+    cc.write_text(f'#!/bin/sh\necho "$@" >> {log}\n')
+    cc.chmod(cc.stat().st_mode | stat.S_IXUSR)
+    code = ("import sys; sys.modules['torch'] = None\n"
+            "import paper_2301_00330_amd.build as b\n"
+            f"b.OBJ, b.LIB, b.PROBE_LIB, b.TORCH_LIB = [{str(tmp_path)!r} + '/' + n for n in ('obj', 'l.so', 'p.so', 't.so')]\n"
+            "b.build()\nprint(len(b.sources()))\n")
+    env = {**os.environ, "HIPCC": str(cc), "PATH": str(tmp_path)}
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=ROOT, env=env)
+    assert r.returncode == 0, r.stderr
+    calls = log.read_text().splitlines()
+    assert len(calls) == int(r.stdout) + 2 and not any("torch" in c for c in calls)   # units, link, probes
+
+
 def test_unique_elements_entry_host_checks(lib):
     """gf_conv_bwd_unique: stride-1 layers whose padding keeps the map size; workspace = vanilla BP on
     the patch grid plus the reduced g_x."""
