@@ -8,7 +8,7 @@ filtered input gradient in one call (gf_conv_bwd_filtered).  The default run
 times ALL five benchmark configurations (each dtype and patch size of each) and
 prints one JSON line: the headline is the largest workload (configuration 5:
 the last conv layers of a MobileNetV2-shaped net, N=128, fp32, r=2), the others
-are listed under "per_config".  Inputs are seeded synthetic tensors resident in
+are summed up under "per_config" (--details FILE writes all of it).  Inputs are seeded synthetic tensors resident in
 HBM before the timed region; buffer sets rotate so that no step finds its
 tensors in the last-level cache.
 
@@ -50,6 +50,8 @@ def parse():
     ap.add_argument("--miopen", action="store_true", help="also time torch's conv backward (MIOpen) as context")
     ap.add_argument("--extras", action="store_true",
                     help="also time the chained block (configuration 2) and the step on 8-bit codes")
+    ap.add_argument("--details", default="", metavar="FILE",
+                    help="also write the JSON object with every configuration's per-kernel and per-layer figures there")
     ap.add_argument("--step-only", default="",
                     help="CFG:DTYPE:R -- run only warm-up + steps of that step with plain launches and print a\n"
                          "short JSON line (the command the rocprofv3 summaries under profiles/ are made with)")
@@ -333,9 +335,23 @@ def main():
         "step_roofline": head["step_roofline"],
         "cpu_baseline": cpu,
         "speedup_vs_exact_bp": head.get("speedup_vs_exact_bp"),
-        "per_config": results,
+        "per_config": [compact(r) for r in results],
     }
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump({**out, "per_config": results}, f)
     print(json.dumps(out), flush=True)
+
+
+def compact(result):
+    """One configuration's share of the JSON line.  The line is read from the end of the output, a few thousand
+    characters of it; per-kernel and per-layer figures go to the file --details names."""
+    keep = {k: result[k] for k in ("cfg", "dtype", "r", "N", "ms_per_step", "images_per_s", "launch")}
+    keep["step_hbm_frac"] = result["step_roofline"]["frac"]
+    keep["dominant"] = {k: result["roofline"][k] for k in ("kernel", "bound", "frac", "avg_launch_us")}
+    if "speedup_vs_exact_bp" in result:
+        keep["speedup_vs_exact_bp"] = result["speedup_vs_exact_bp"]
+    return keep
 
 
 def build_sets(args, cfg, dtype, r, torch, B, T, WL):

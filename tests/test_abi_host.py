@@ -221,6 +221,23 @@ def test_bench_refuses_more_than_one_gpu():
     assert "ONE GPU" in (r.stderr + r.stdout)
 
 
+def test_bench_line_is_short():
+    """What a configuration adds to bench.py's JSON line does not grow with its layers and kernels: the whole line of all
+    configurations stays within the last few thousand characters that are kept of the output."""
+    import json
+    import sys
+    sys.path.insert(0, ROOT)
+    import bench
+    from paper_2301_00330_amd import workloads as WL
+    combos = [(c, dt, r) for c in (5, 1, 2, 3, 4) for dt in WL.CONFIGS[c].dtypes for r in WL.CONFIGS[c].rs]
+    long = [{"layer": "x" * 40, "kernels": ["k" * 30] * 4}] * 30
+    full = [{"cfg": c, "dtype": dt, "r": r, "N": 128, "ms_per_step": 0.37231, "images_per_s": 343789.1, "launch": "hip-graph replay",
+             "step_roofline": {"frac": 0.3612, "note": "n" * 200}, "speedup_vs_exact_bp": 3.93, "kernels": long, "per_layer": long,
+             "roofline": {"kernel": "patch_reduce_batch_k", "bound": "hbm", "frac": 0.5123, "avg_launch_us": 36.12, "method": "m" * 300}}
+            for c, dt, r in combos]
+    assert len(json.dumps([bench.compact(f) for f in full])) < 4000 and len(combos) >= 10
+
+
 def test_header_is_plain_c(tmp_path):
     """include/gf.h must compile as C99 on its own (the boundary is a C ABI) and a C program that
     only takes the addresses of the declared entry points must link against libgf.so."""
