@@ -87,11 +87,6 @@ static size_t ws_filtered(const Geom& g, bool own_gyu, size_t* off_w, size_t* of
     return ws_exact(g, true, true);
   }
   int nz = 0;
-  if (dense_ok(g)) {
-    if (off_w) *off_w = 0;
-    if (off_i) *off_i = 0;
-    return ws_dense(g, true, true, false, own_gyu);
-  }
   if (dw_fused_ok(g, &nz)) {
     if (off_w) *off_w = 0;
     if (off_i) *off_i = 0;
@@ -518,8 +513,6 @@ static gf_status filtered_body(const gf_conv_desc* desc, const void* g_y, const 
     }
     return dev(launch_exact(g, x_u, w, g_y, g_w, g_x, ws, ws_bytes, st));
   }
-  if (dense_ok(g))
-    return dev(launch_dense(g, g_y, true, x_u, w, gy_u, g_w, g_x, false, nullptr, ws, st));
   int nz = 0;
   if (dw_fused_ok(g, &nz)) {
     float* part = static_cast<float*>(ws);

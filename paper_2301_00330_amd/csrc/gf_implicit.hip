@@ -405,6 +405,7 @@ __device__ __forceinline__ void xw_mainloop(const XArgs& a, int t, int m0, int n
 template <class T, int TM, int TN>
 __device__ __forceinline__ void xwgrad_block(const XArgs& a, int L, unsigned char* smem) {
   using X = XTile<T, TM, TN>;
+  static_assert(XTile<raw_f32, TM, TN>::kOp <= X::kBytes || !is_split<T>(), "the second pass works in the same LDS");
   // The hardware hands consecutive blocks to the eight XCDs in turn; with eight or more K slabs block L works on
   // slab (L % 8) + 8 * (..), so that all taps and tiles of a slab share one XCD's L2 and each XCD touches an eighth
   // of x and g_y.
