@@ -406,3 +406,28 @@ def test_weight_gradient_alone(oracle, case, dtype):
     x_u, gy_u = randn(sh["x_u"], 1, dtype), randn(sh["gy_u"], 2, dtype)
     g_w = T.conv_bwd_weight(d, x_u.cuda(), gy_u.cuda())
     assert rel_err(g_w, oracle.bwd_weight(odesc(oracle, d), to64(x_u), to64(gy_u))) <= 1e-5   # fp32 sums of either type
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", [
+    (1, 40, 24, 32, 32, 3, 1, 2),      # two slabs in fp32: added inside the launch
+    (6, 24, 40, 32, 32, 3, 1, 2),      # three in bf16, 12 in fp32: apart
+    (9, 70, 72, 40, 34, 3, 1, 2),      # four tiles with ragged edges
+    (3, 5, 9, 150, 134, 5, 2, 2),      # channels that are no whole vectors
+    (33, 12, 20, 30, 30, 1, 1, 2),     # 1 x 1: 59 and 15 slabs, inside
+    (40, 12, 20, 30, 30, 1, 1, 2),     # ... 71 and 18, apart
+])
+def test_slab_sums_inside_and_apart(oracle, case, dtype):
+    check_filtered(oracle, case, dtype)
+    N, Ci, Co, H, W, K, s, r = case
+    d = mk(N, Ci, Co, H, W, K, s, K // 2, r=r, dtype=dtype)
+    sh = T.shapes(d)
+    x_u, gy_u, w = randn(sh["x_u"], 1, dtype), randn(sh["gy_u"], 2, dtype), randn(sh["w"], 3, dtype)
+    ref = oracle.bwd_weight(odesc(oracle, d), to64(x_u), to64(gy_u))
+    for reduced in (True, False):
+        g_w, g_x = T.conv_bwd_chained(d, gy_u.cuda(), x_u.cuda(), w.cuda(), reduced_out=reduced)
+        assert rel_err(g_w, ref) <= 1e-5   # fp32 sums of either type
+        assert rel_err(g_x, to64(T.conv_bwd_input(d, gy_u.cuda(), w.cuda(), reduced_out=reduced))) <= TOL[dtype]
+    gy_u[0, 0, 0, 0] = float("inf")       # in one slab of one row
+    g_w, _ = T.conv_bwd_chained(d, gy_u.cuda(), x_u.cuda(), w.cuda())
+    assert not torch.isfinite(g_w[0]).any() and rel_err(g_w[1:], ref[1:]) <= 1e-5
