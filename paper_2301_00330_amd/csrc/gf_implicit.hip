@@ -802,11 +802,17 @@ struct XPlan {
 
 // Tile sides in units of 64: 128 x 128 where every block slot of the chip has at least eight steps of such tiles (two
 // blocks per CU: registers), 128 x 64 below that, and 64 x 64 where a side of the layer has no more than 64 channels.
-void tile_shape(const Geom& g, const XGeo& q, int* tm, int* tn, long* slots) {
+// An input gradient alone has its few channels in K: 128 x 128 (c_i, pixels) from 384 such tiles on, where K is one slab
+// with either tile (bf16: the bits of the call for both; fp32: 16 instead of 32 k before a sum goes to the total).  64 x 64 / 128 x 128 in us, 3 x 3: 512 -> 64
+// channels, 48 x 48, n = 40 bf16 160 / 103, fp32 453 / 358; 192 -> 64, 120 x 160, n = 8 107 / 87, 303 / 298; 320 -> 40, 33 x
+// 33, n = 16 (408 tiles) 31.9 / 28.6, 68.8 / 67.3; 128 -> 64, 60 x 80, n = 8 (300) 28.5 / 25.2, 62 / 63.5; 192 -> 64, 30 x 40,
+// n = 8 (150) 18.4 / 21.4, 34 / 50.
+void tile_shape(const Geom& g, const XGeo& q, bool want_gw, int* tm, int* tn, long* slots) {
   const bool wide = g.Co > 64 && g.Ci > 64;
   const long w_steps = (long)cdiv(g.Co, 128) * cdiv(g.Ci, 128) * g.KK * cdiv((long)g.N * up8(q.PY), g.b == 2 ? 64 : 32);
   *tm = wide ? 2 : 1;
   *tn = wide && w_steps >= 4 * 512 ? 2 : 1;
+  if (!want_gw && !wide && g.Ci > 64 && (long)cdiv(g.Ci, 128) * cdiv((long)g.N * up8(q.PQ), 128) * q.nph >= 384) *tm = *tn = 2;
   *slots = *tn == 2 ? 512 : 768;
 }
 // Chunks per slab for about z slabs.  Slabs go to the XCDs in turn (each L2 then keeps its own part of the maps), so
@@ -825,7 +831,7 @@ XPlan make_plan(const Geom& g, bool want_gw, bool want_gx) {
   p.nvw = up8(q.PY) / 8;
   p.nvd = up8(q.PQ) / 8;
   long slots;
-  tile_shape(g, q, &p.tm, &p.tn, &slots);
+  tile_shape(g, q, want_gw, &p.tm, &p.tn, &slots);
   p.Cip = cdiv(g.Ci, VE) * VE;
   p.qv = up8(q.PY) / VE;
   p.nchunks = cdiv((long)g.N * p.qv, 8);

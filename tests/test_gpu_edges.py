@@ -431,3 +431,19 @@ def test_slab_sums_inside_and_apart(oracle, case, dtype):
     gy_u[0, 0, 0, 0] = float("inf")       # in one slab of one row
     g_w, _ = T.conv_bwd_chained(d, gy_u.cuda(), x_u.cuda(), w.cuda())
     assert not torch.isfinite(g_w[0]).any() and rel_err(g_w[1:], ref[1:]) <= 1e-5
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", [(6, 130, 24, 64, 130, 3, 1), (8, 72, 8, 78, 78, 3, 1), (8, 72, 8, 79, 80, 3, 1), (9, 200, 16, 131, 66, 3, 2)])
+def test_vanilla_input_gradient_alone(oracle, case, dtype):
+    """Few output channels, on both sides of the size from which g_x alone has larger tiles: the bits of the call for both in
+    bf16, in fp32 the same products in partial sums of 16 instead of 32."""
+    N, Ci, Co, H, W, K, s = case
+    d = mk(N, Ci, Co, H, W, K, s, 1, r=1, dtype=dtype)
+    sh = T.shapes(d)
+    x, w, gy = randn(sh["x"], 1, dtype), randn(sh["w"], 2, dtype, scale=0.1), randn(sh["g_y"], 3, dtype)
+    _, only = T.conv_bwd_exact(d, x.cuda(), w.cuda(), gy.cuda(), want_gw=False)
+    _, both = T.conv_bwd_exact(d, x.cuda(), w.cuda(), gy.cuda())
+    _, ref = oracle.bwd_exact(odesc(oracle, d), to64(x), to64(w), to64(gy))
+    assert rel_err(only, ref) <= TOL[dtype] and rel_err(both, ref) <= TOL[dtype]
+    assert torch.equal(only, both) if dtype == "bf16" else rel_err(only, to64(both)) <= 1e-6
