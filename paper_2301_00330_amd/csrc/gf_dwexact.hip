@@ -391,9 +391,9 @@ __global__ __launch_bounds__(kThreads) void dw_exact_wgrad_k(DwExactArgs a) {
 // time, so the K x K sums stay in registers until the end and the launch that adds the slabs has npb times less to
 // read.  Blocks of one XCD (block index mod 8) take neighbouring channels, whose planes share cache lines.
 // Measured, both gradients, against the two launches below (us; x, g_y and g_x from memory):
-//   fp32  144 channels, 56 x 56, n = 32: 79 -> 39 (4.4 TB/s)   576, 14 x 14, n = 128: 144 -> 46   960, 7 x 7, n = 128: 110 -> 27
-//         192, 28 x 28, n = 32: 44 -> 17   72, 28 x 28, 5 x 5 taps, n = 32: 42 -> 16   16, 7 x 7, n = 1: 13 -> 8
-//   bf16  144, 56 x 56, n = 64: 133 -> 69    96, 112 x 112, n = 64: 280 -> 185    144, 65 x 65, n = 32: 92 -> 54
+//   fp32  144 channels, 56 x 56, n = 32: 79 -> 41 (4.2 TB/s)   576, 14 x 14, n = 128: 144 -> 47   960, 7 x 7, n = 128: 110 -> 24
+//         192, 28 x 28, n = 32: 44 -> 17   72, 28 x 28, 5 x 5 taps, n = 32: 42 -> 17   16, 7 x 7, n = 1: 13 -> 9.6
+//   bf16  144, 56 x 56, n = 64: 133 -> 64    96, 112 x 112, n = 64: 280 -> 184    144, 65 x 65, n = 32: 92 -> 52
 // bf16 is bound by vector instructions (18 multiply-adds per pixel, the same as in fp32 on half the bytes).
 // ---------------------------------------------------------------------------
 constexpr int kQ = 4;

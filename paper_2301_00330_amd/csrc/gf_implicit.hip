@@ -29,10 +29,11 @@
 // operand fragments from LDS per four matrix instructions, one of the smallest four per two, and LDS is what bounds bf16
 // (a 64 x 64 x 64 step moves 48 KB through it, 384 clocks, for 128 clocks of matrix instructions).  Measured, both
 // products, against separate kernels per product before (us, tensors of three rotating sets):
-//   bf16  256 -> 256, 14 x 14, n = 64: 112 -> 76     512 -> 512, 7 x 7: 121 -> 81     256 -> 512, stride 2: 90 -> 66
-//         256 -> 256, 64 x 64, n = 8, dilation 12: 162 -> 147 (527 TFLOP/s)
-//   fp32  512 -> 512, 30 x 40, n = 8: 968 -> 612     128 -> 128, 28 x 28, n = 32: 177 -> 108 (138 TFLOP/s)
-//         256 -> 512, 14 x 14, n = 4, stride 2: 132 -> 49
+//   bf16  256 -> 256, 14 x 14, n = 64: 112 -> 74     512 -> 512, 7 x 7: 121 -> 79     256 -> 512, stride 2: 90 -> 63
+//         256 -> 256, 64 x 64, n = 8, dilation 12: 162 -> 146 (528 TFLOP/s)
+//   fp32  512 -> 512, 30 x 40, n = 8: 968 -> 636 (142 TFLOP/s)     128 -> 128, 28 x 28, n = 32: 177 -> 114 (130 TFLOP/s)
+//         256 -> 512, 14 x 14, n = 4, stride 2: 132 -> 52
+// (fp32 sums every 16 or 32 k from zero and changes the sign from chunk to chunk, see mul_all: 2 - 4 % of these times.)
 #include "gf_gemm.h"
 
 #include <algorithm>
@@ -803,10 +804,10 @@ struct XPlan {
 // Tile sides in units of 64: 128 x 128 where every block slot of the chip has at least eight steps of such tiles (two
 // blocks per CU: registers), 128 x 64 below that, and 64 x 64 where a side of the layer has no more than 64 channels.
 // An input gradient alone has its few channels in K: 128 x 128 (c_i, pixels) from 384 such tiles on, where K is one slab
-// with either tile (bf16: the bits of the call for both; fp32: 16 instead of 32 k before a sum goes to the total).  64 x 64 / 128 x 128 in us, 3 x 3: 512 -> 64
-// channels, 48 x 48, n = 40 bf16 160 / 103, fp32 453 / 358; 192 -> 64, 120 x 160, n = 8 107 / 87, 303 / 298; 320 -> 40, 33 x
-// 33, n = 16 (408 tiles) 31.9 / 28.6, 68.8 / 67.3; 128 -> 64, 60 x 80, n = 8 (300) 28.5 / 25.2, 62 / 63.5; 192 -> 64, 30 x 40,
-// n = 8 (150) 18.4 / 21.4, 34 / 50.
+// with either tile (bf16: the bits of the call for both; fp32: 16 instead of 32 k before a sum goes to the total).
+// 64 x 64 / 128 x 128 in us, 3 x 3: 512 -> 64 channels, 48 x 48, n = 40 bf16 160 / 103, fp32 453 / 358; 192 -> 64,
+// 120 x 160, n = 8 107 / 87, 303 / 298; 320 -> 40, 33 x 33, n = 16 (408 tiles) 31.9 / 28.6, 68.8 / 67.3; 128 -> 64,
+// 60 x 80, n = 8 (300) 28.5 / 25.2, 62 / 63.5; 192 -> 64, 30 x 40, n = 8 (150) 18.4 / 21.4, 34 / 50.
 void tile_shape(const Geom& g, const XGeo& q, bool want_gw, int* tm, int* tn, long* slots) {
   const bool wide = g.Co > 64 && g.Ci > 64;
   const long w_steps = (long)cdiv(g.Co, 128) * cdiv(g.Ci, 128) * g.KK * cdiv((long)g.N * up8(q.PY), g.b == 2 ? 64 : 32);
