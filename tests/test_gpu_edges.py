@@ -413,9 +413,10 @@ def test_weight_gradient_alone(oracle, case, dtype):
     (1, 40, 24, 32, 32, 3, 1, 2),      # two slabs in fp32: added inside the launch
     (6, 24, 40, 32, 32, 3, 1, 2),      # three in bf16, 12 in fp32: apart
     (9, 70, 72, 40, 34, 3, 1, 2),      # four tiles with ragged edges
+    (2, 130, 129, 40, 34, 3, 1, 2),    # nine tiles of five slabs in fp32: inside
     (3, 5, 9, 150, 134, 5, 2, 2),      # channels that are no whole vectors
-    (33, 12, 20, 30, 30, 1, 1, 2),     # 1 x 1: 59 and 15 slabs, inside
-    (40, 12, 20, 30, 30, 1, 1, 2),     # ... 71 and 18, apart
+    (33, 12, 20, 30, 30, 1, 1, 2),     # 1 x 1: 59 slabs in fp32 apart with a reduced map only, 15 in bf16 inside
+    (40, 12, 20, 30, 30, 1, 1, 2),     # ... 71 apart, 18 apart with a reduced map only
 ])
 def test_slab_sums_inside_and_apart(oracle, case, dtype):
     check_filtered(oracle, case, dtype)
