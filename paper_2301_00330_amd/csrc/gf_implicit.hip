@@ -33,7 +33,7 @@
 //         256 -> 256, 64 x 64, n = 8, dilation 12: 162 -> 146 (528 TFLOP/s)
 //   fp32  512 -> 512, 30 x 40, n = 8: 968 -> 636 (142 TFLOP/s)     128 -> 128, 28 x 28, n = 32: 177 -> 114 (130 TFLOP/s)
 //         256 -> 512, 14 x 14, n = 4, stride 2: 132 -> 52
-// (fp32 sums every 16 or 32 k from zero and changes the sign from chunk to chunk, see mul_all: 2 - 4 % of these times.)
+// (fp32 sums every 16 or 32 k from zero and changes the sign from chunk to chunk, see mul_all: 2 - 8 % of these times.)
 #include "gf_gemm.h"
 
 #include <algorithm>
