@@ -212,6 +212,28 @@ def test_dense_products_on_codes(oracle, case, dtype):
     check_codes(oracle, case, dtype)
 
 
+# N, C_in, C_out, H, W, K, stride, r: weight gradients on 32 x 32 tiles -- their edges, chunks for one wave, for all four and
+# for a second round, slabs -- and the 64 x 64 tiles from the same rule's other side on
+SHORT_K_CASES = [
+    (1, 32, 32, 8, 8, 1, 1, 2),        # one tile, less than a chunk
+    (1, 33, 31, 8, 8, 3, 1, 2),        # a row and a column past the tile
+    (3, 17, 97, 6, 6, 1, 1, 2),        # nine patches: every vector ends inside its plane
+    (5, 65, 96, 7, 7, 3, 1, 4),        # four patches: planes shorter than a vector of 16-bit values or codes
+    (17, 48, 40, 8, 8, 1, 1, 2),       # chunks for more than four waves, a last one that is not full
+    (64, 64, 61, 12, 12, 1, 1, 2),     # slabs
+    (30, 16, 48, 17, 16, 5, 1, 2),     # 25 taps
+    (90, 20, 24, 14, 14, 3, 2, 3),     # slabs of ragged planes, stride 2
+    (24, 512, 512, 16, 16, 1, 1, 2),   # 64 x 64 tiles, slabs of both products
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", SHORT_K_CASES)
+def test_short_k_weight_gradient(oracle, case, dtype):
+    check_filtered(oracle, case, dtype)
+    check_codes(oracle, case, dtype)
+
+
 # N, C, H, W, stride, r: edges of the fused depthwise launches
 DW_CASES = [
     (1, 1, 2, 2, 1, 2),                # runs shorter than a vector
