@@ -79,12 +79,19 @@ static gf_status dev(hipError_t e) { return e == hipSuccess ? GF_OK : GF_ERR_DEV
 
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
+// vanilla BP behind the one-call entry, which also runs on the library's own scratch and then returns the same bits
+static Geom filtered_exact_geom(const Geom& g) {
+  Geom e = g;
+  e.own_scratch = true;
+  return e;
+}
+
 // layout of the fused call's workspace: [gy_u when the caller passes none][weight ws][input ws]
 static size_t ws_filtered(const Geom& g, bool own_gyu, size_t* off_w, size_t* off_i) {
   if (g.r == 1) {
     if (off_w) *off_w = 0;
     if (off_i) *off_i = 0;
-    return ws_exact(g, true, true);
+    return ws_exact(filtered_exact_geom(g), true, true);
   }
   int nz = 0;
   if (dw_fused_ok(g, &nz)) {
@@ -511,7 +518,7 @@ static gf_status filtered_body(const gf_conv_desc* desc, const void* g_y, const 
                               hipMemcpyDeviceToDevice, st));
       if (rc) return rc;
     }
-    return dev(launch_exact(g, x_u, w, g_y, g_w, g_x, ws, ws_bytes, st));
+    return dev(launch_exact(filtered_exact_geom(g), x_u, w, g_y, g_w, g_x, ws, ws_bytes, st));
   }
   int nz = 0;
   if (dw_fused_ok(g, &nz)) {

@@ -294,7 +294,7 @@ __device__ __forceinline__ uint64_t slab_load(const float* p) {
 
 // element pair q of the lane's 16 of tile (i, j): slab[((i TN + j) 8 + q) 512 + 2 lane]
 // (mw, nw: rows and columns of the matrix from this wave's first ones on; tiles wholly outside are left out)
-template <int TM, int TN, class A>
+template <int TM, int TN, int NT = kT, class A>
 __device__ __forceinline__ void put_slab(const A (&acc)[TM][TN], float* slab, int mw, int nw) {
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -303,7 +303,7 @@ __device__ __forceinline__ void put_slab(const A (&acc)[TM][TN], float* slab, in
       if (64 * i < mw && 64 * j < nw)   // (uniform for the wave)
 #pragma unroll
       for (int q = 0; q < 8; ++q)
-        slab_store(slab + (((i * TN + j) * 8 + q) * kT + threadIdx.x) * 2, acc[i][j][2 * q], acc[i][j][2 * q + 1]);
+        slab_store(slab + (((i * TN + j) * 8 + q) * NT + threadIdx.x) * 2, acc[i][j][2 * q], acc[i][j][2 * q + 1]);
 }
 
 // one block's ticket of `count`: true in the block that takes the last one (all stores made before it are complete)
@@ -323,9 +323,9 @@ __device__ __forceinline__ bool last_ticket(int* ticket, int count, int* s_flag)
 
 // acc = slab 0 + slab 1 + ... in slab order, a few slabs' loads in flight at a time.  Integer slabs are added in 64
 // bits; a final sum leaves as the bits of the nearest float.
-template <int TM, int TN, class A>
+template <int TM, int TN, int NT = kT, class A>
 __device__ __forceinline__ void sum_slabs(A (&acc)[TM][TN], const float* slabs, int nz, int mw, int nw, bool final) {
-  constexpr int SZ = 4096 * TM * TN, ZB = 4;
+  constexpr int SZ = 16 * NT * TM * TN, ZB = 4;
   constexpr bool INT = __is_same(A, i32x16);
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -335,13 +335,13 @@ __device__ __forceinline__ void sum_slabs(A (&acc)[TM][TN], const float* slabs, 
       typename std::conditional<INT, long long, float>::type s[16];
 #pragma unroll
       for (int e = 0; e < 16; ++e) s[e] = 0;
-      const float* p0 = slabs + ((i * TN + j) * 8 * kT + threadIdx.x) * 2;
+      const float* p0 = slabs + ((i * TN + j) * 8 * NT + threadIdx.x) * 2;
       for (int z0 = 0; z0 < nz; z0 += ZB) {
         uint64_t t[ZB][8];
 #pragma unroll
         for (int zz = 0; zz < ZB; ++zz)
 #pragma unroll
-          for (int q = 0; q < 8; ++q) t[zz][q] = slab_load(p0 + (long)min(z0 + zz, nz - 1) * SZ + q * (2 * kT));   // clamped: always issued
+          for (int q = 0; q < 8; ++q) t[zz][q] = slab_load(p0 + (long)min(z0 + zz, nz - 1) * SZ + q * (2 * NT));   // clamped: always issued
 #pragma unroll
         for (int zz = 0; zz < ZB; ++zz)
 #pragma unroll
@@ -365,19 +365,19 @@ __device__ __forceinline__ void sum_slabs(A (&acc)[TM][TN], const float* slabs, 
 // it into the group's own slab, the block that completes the last group adds those (one level where there is one
 // group: a block adds a slab of 16 KB in 0.2 - 0.4 us, so 128 slabs one after the other would take longer than the
 // launch).  True in that block, with acc = the sum.  tickets: one for the tile, one per group.
-template <int TM, int TN, class A>
+template <int TM, int TN, int NT = kT, class A>
 __device__ __forceinline__ bool reduce_slabs(A (&acc)[TM][TN], float* slabs, int z, int* tickets, int nz, int grp,
                                              int ngrp, int* s_flag, int mw, int nw) {
-  constexpr long SZ = 4096 * TM * TN;
+  constexpr long SZ = 16 * NT * TM * TN;
   const int gi = z / grp, in_grp = min(grp, nz - gi * grp);
-  put_slab<TM, TN>(acc, slabs + z * SZ, mw, nw);
+  put_slab<TM, TN, NT>(acc, slabs + z * SZ, mw, nw);
   if (!last_ticket(tickets + 1 + gi, in_grp, s_flag)) return false;
-  sum_slabs<TM, TN>(acc, slabs + gi * grp * SZ, in_grp, mw, nw, ngrp == 1);
+  sum_slabs<TM, TN, NT>(acc, slabs + gi * grp * SZ, in_grp, mw, nw, ngrp == 1);
   if (ngrp == 1) return true;
   float* sums = slabs + nz * SZ;
-  put_slab<TM, TN>(acc, sums + gi * SZ, mw, nw);
+  put_slab<TM, TN, NT>(acc, sums + gi * SZ, mw, nw);
   if (!last_ticket(tickets, ngrp, s_flag)) return false;
-  sum_slabs<TM, TN>(acc, sums, ngrp, mw, nw, true);
+  sum_slabs<TM, TN, NT>(acc, sums, ngrp, mw, nw, true);
   return true;
 }
 

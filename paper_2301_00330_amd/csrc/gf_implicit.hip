@@ -34,6 +34,7 @@
 //   fp32  512 -> 512, 30 x 40, n = 8: 968 -> 636 (142 TFLOP/s)     128 -> 128, 28 x 28, n = 32: 177 -> 114 (130 TFLOP/s)
 //         256 -> 512, 14 x 14, n = 4, stride 2: 132 -> 52
 // (fp32 sums every 16 or 32 k from zero and changes the sign from chunk to chunk, see mul_all: 2 - 8 % of these times.)
+// bf16 layers of kernels larger than 1 x 1 with enough channels take the same three steps on staged operands (sgemm_k, below).
 #include "gf_gemm.h"
 
 #include <algorithm>
@@ -268,6 +269,13 @@ struct XArgs {
   int* tickD;
   int d_first;            // the input-gradient blocks lead the grid
   FastDiv d_qv, d_qd, d_r, d_tiles, d_tx;
+  // staged operands (stage_k): rows of 32 channels, one per pixel of g_y / x and one of zeros at the end
+  const void* gt;         // [Cop / 32][N PY + 1][32]
+  const void* xt;         // [Cix / 32][N H W + 1][32]
+  const void* wr;         // [KK][Cop / 32][Ci][32]
+  const int4* taps;       // [phase][KK]: {tap, row and column offset of the g_y pixel that position 0 reads}
+  int Cop, Cix, H, W, Hy, Wy, Wq, Kw, s, d, p;
+  FastDiv d_py, d_wy, d_wq;
 };
 
 template <class T, int TM, int TN>
@@ -403,27 +411,418 @@ __device__ __forceinline__ void xw_mainloop(const XArgs& a, int t, int m0, int n
   k_loop<xsets_of<T, TM, TN>(), Set>(kc0, kc1, fetch, stage, mul);
 }
 
+// ---------------------------------------------------------------------------
+// Staged operands (bf16, kernels larger than 1 x 1).  stage_k writes g_y, x and the kernel once more in planes of 32
+// channels, channels innermost, so that every 16 bytes a tap reads are aligned and whole: no masks -- a pixel outside the image
+// is the row of zeros -- and the loads go straight to LDS (global_load_lds_dwordx4), four buffers of 32 k, a barrier per buffer.
+//   weight gradient: K = pixels; both operands are rows of k = pixel and go through the transposing reads
+//   input gradient:  K = (tap, c_o); both operands are K-major rows of 32 c_o
+// xgemm_k on the same maps spends its steps on masks, unaligned loads and the way through registers into LDS, and splits each
+// image's planes of 8 ceil(HW / 8) pixels; here a step is loads, transposing or plain reads of LDS and matrix instructions, of
+// which none alone bounds it (256 -> 256, 14 x 14, n = 64: 54 us; with the matrix instructions left out 39, with the loads 49).
+// Both gradients, xgemm_k / staged, whole call (us, three rotating sets; the staging launch 6 - 8 of it, prep_k took 7 - 11):
+//   256 -> 256, 14 x 14, n = 64: 74 / 54    512 -> 512, 7 x 7: 81 / 57    256 -> 512, stride 2: 63 / 46
+//   64 -> 64, 8 x 8, n = 1: 18 / 14    256 -> 256, 60 x 80, n = 8: 176 / 124; 64 x 64, dilation 12: 148 / 117
+//   512 -> 512, 32 x 32, n = 8: 160 / 112    5 x 5, 64 -> 64, 56 x 56, n = 16: 81 / 59
+//   128 -> 256, 60 x 80, n = 128: 1131 / 935    512 -> 512, 30 x 40, n = 128: 2240 / 1652 (1.03 PFLOP/s)
+// Also timed, first layer above: four waves of 64 x 64 and two buffers of 64 k 54.6 (the three first layers 55 / 48 / 59, with
+// eight waves 55 / 45 / 56), 128 x 64 tiles 70, the operands of step k + 1 read during step k 55.
+// ---------------------------------------------------------------------------
+struct StageJob {   // src [N][C][PX] -> dst [Cp / 32][N PX + 1][32], channels past C and the last row zero; kernel: see stage_k
+  const void* src;
+  void* dst;
+  int N, C, PX, Cp, pb, cb, blocks;   // blocks of 64 pixels per image, of 64 channels, all
+};
+struct StageArgs {
+  StageJob job[3];
+  int4* taps;
+  int* ntap;
+  int* tickets;
+  int ntickets, KK, Kw, s, d, p;
+};
+
+// A block transposes 64 channels x 64 pixels: a lane loads eight pixels of two channels and writes eight channel pairs, in an
+// order of 16-byte units within a pixel's row that spreads them over the banks.
+__global__ __launch_bounds__(kT) void stage_k(StageArgs a) {
+  __shared__ __attribute__((aligned(16))) uint32_t tile[64 * 32];
+  int b = blockIdx.x;
+  const int tid = threadIdx.x;
+  if (b == 0) {   // tap lists of the phases, tickets, rows of zeros
+    const int nph = a.s * a.s;
+    if (a.taps && tid < nph) {
+      const int pa = tid / a.s, pb = tid - pa * a.s;
+      int cnt = 0;
+      for (int t = 0; t < a.KK; ++t) {
+        const int u = t / a.Kw, v = t - u * a.Kw;
+        const int ea = pa + a.p - u * a.d, eb = pb + a.p - v * a.d;
+        const int qa = floor_div(ea, a.s), qb = floor_div(eb, a.s);
+        if (qa * a.s == ea && qb * a.s == eb) a.taps[tid * a.KK + cnt++] = make_int4(t, qa, qb, 0);
+      }
+      a.ntap[tid] = cnt;
+    }
+    for (int i = tid; i < a.ntickets; i += kT) a.tickets[i] = 0;
+    for (int j = 0; j < 3; ++j) {
+      const StageJob& q = a.job[j];
+      if (!q.blocks) continue;
+      uint32_t* z = static_cast<uint32_t*>(q.dst);
+      const long rows = (long)q.N * q.PX + 1;
+      if (j < 2)
+        for (int i = tid; i < q.Cp / 2; i += kT) z[((i >> 4) * rows + rows - 1) * 16 + (i & 15)] = 0;
+    }
+    return;
+  }
+  b -= 1;
+  int j = 0;
+  while (j < 2 && b >= a.job[j].blocks) b -= a.job[j++].blocks;   // (uniform)
+  const StageJob q = a.job[j];
+  const int c64 = b % q.cb, rest = b / q.cb;
+  const int n = rest / q.pb, p0 = (rest - n * q.pb) * 64;
+  const int pv = tid & 7, cp = tid >> 3;   // eight pixels, channel pair
+  const int px = p0 + pv * 8, c = c64 * 64 + cp * 2;
+  const bf16_t* src = static_cast<const bf16_t*>(q.src);
+  uint32_t v[2][4];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const bf16_t* s = src + ((long)n * q.C + min(c + h, q.C - 1)) * q.PX;
+    if (px + 8 <= q.PX) {
+      const uint4 w = load_vec<bf16_t>(s + px);
+      v[h][0] = w.x; v[h][1] = w.y; v[h][2] = w.z; v[h][3] = w.w;
+    } else {
+      uint16_t e[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) e[i] = __builtin_bit_cast(uint16_t, s[min(px + i, q.PX - 1)]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[h][i] = (uint32_t)e[2 * i] | ((uint32_t)e[2 * i + 1] << 16);
+    }
+    if (c + h >= q.C)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[h][i] = 0;
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const uint32_t lo = v[0][i >> 1] >> (16 * (i & 1)) & 0xffffu, hi = v[1][i >> 1] >> (16 * (i & 1)) & 0xffffu;
+    tile[(pv * 8 + i) * 32 + (((cp >> 2) ^ pv) << 2 | (cp & 3))] = lo | hi << 16;
+  }
+  __syncthreads();
+  bf16_t* dst = static_cast<bf16_t*>(q.dst);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int r = i * 32 + (tid >> 3), un = tid & 7;
+    if (p0 + r >= q.PX) continue;
+    const int plane = c64 * 2 + (un >> 2);
+    long row;
+    if (j < 2) {
+      row = plane * ((long)q.N * q.PX + 1) + (long)n * q.PX + p0 + r;
+    } else {   // "pixels" are (c_i, tap): [tap][c_o / 32][c_i][32]
+      const int ci = (p0 + r) / a.KK, t = p0 + r - ci * a.KK;
+      row = ((long)t * (q.Cp >> 5) + plane) * (q.PX / a.KK) + ci;
+    }
+    const uint4 u = *reinterpret_cast<const uint4*>(tile + r * 32 + ((un ^ (r >> 3)) << 2));
+    *reinterpret_cast<uint4*>(dst + row * 32 + (un & 3) * 8) = u;
+  }
+}
+
+// 16 bytes per lane from base + off to LDS, lane i to lds + 16 i (both uniform).  Behind the compiler's back: it would wait for
+// every such load at the next read of LDS; the loops below wait themselves.
+__device__ __forceinline__ void dma16(const void* base, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
+}
+__device__ __forceinline__ uint32_t lds_of(const unsigned char* p) {
+  return (uint32_t)(size_t)(__attribute__((address_space(3))) const unsigned char*)p;
+}
+// Block tile of 64 TM x 64 TN, NT lanes: waves of 32 x 32 TNW, WN of them side by side.  Eight waves on the largest tile: their
+// address arithmetic and reads of LDS hide behind each other's matrix instructions (four waves of 64 x 64: one per SIMD and
+// block, 1100 clocks for a step of 256 clocks of matrix instructions).
+template <int TM, int TN>
+struct STile {
+  static constexpr int BM = 64 * TM, BN = 64 * TN;
+  static constexpr int NT = TM * TN == 4 ? 512 : 256;
+  static constexpr int WN = TM > TN ? 1 : 2, TNW = BN / (32 * WN);
+  static constexpr int A = 4096 * TM, B = 4096 * TN, kStage = A + B;   // a buffer of 32 k
+  static constexpr int LA = A / (16 * NT), LB = B / (16 * NT);         // 16-byte loads of a lane
+  static constexpr int SC = BN + 8;                                     // element stride of the staged result
+  static constexpr int kOp = 4 * kStage, kE = BM * SC * 2;
+  static constexpr int kBytes = kOp > kE ? kOp : kE;
+  static_assert(BM == 32 * (NT / 64 / WN), "the waves cover the tile");
+  static_assert(kOp <= 65536, "16-bit LDS addresses of the loads");
+};
+
+// Steps [0, n) of 32 k through four buffers: three are on their way or read while the fourth is filled.  A step waits until this
+// wave's loads of its buffer have landed (those of at most two later buffers are still out) and its reads of the last one
+// are done; after the barrier the same holds for all waves.  The operands are read before the next loads are issued (their
+// address arithmetic then covers the latency of LDS).
+template <int LOADS, class F, class R, class M>
+__device__ __forceinline__ void stage_loop(int n, F&& fetch, R&& read, M&& mul) {
+  fetch(0);
+  if (n > 1) fetch(1);   // (uniform)
+  if (n > 2) fetch(2);
+  for (int k = 0; k < n; ++k) {
+    if (k + 2 < n) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * LOADS) : "memory");
+    else if (k + 1 < n) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LOADS) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    read(k & 3);
+    if (k + 3 < n) fetch(k + 3 & 3);
+    mul();
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// The operand of one MFMA from a plane of 32 k x 32 channels -- lane: channel lane % 32, k = 16 ks + 8 (lane / 32) .. + 7 --
+// with transposing reads (see frag_tr); four rows of 64 bytes are read together, all banks once.
+__device__ __forceinline__ uint4 frag_plane(const unsigned char* plane, int ks, int lane) {
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+  const unsigned char* p = plane + (ks * 16 + 8 * (lane >> 5) + ((lane & 15) >> 2)) * 64 + (lane & 16) * 2 + 8 * (lane & 3);
+  const uint2 a = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p));
+  const uint2 b = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * 64)));
+  return make_uint4(a.x, a.y, b.x, b.y);
+}
+
+// A pixel of g_y in a walk over all pixels in steps of 32, and the row of x under a tap, by additions only.
+struct PixelWalk {
+  int q, hs, ws, xr;   // pixel; row and column of x; row of the staged x
+};
+
+// acc += g_y[pixels][c_o]^T * x[pixels moved by tap t][c_i] over the chunks of 64 pixels of a K slab
+template <int TM, int TN>
+__device__ __forceinline__ void sw_mainloop(const XArgs& a, int t, int m0, int n0, int kc0, int kc1, unsigned char* smem,
+                                            f32x16 (&acc)[1][STile<TM, TN>::TNW]) {
+  using S = STile<TM, TN>;
+  constexpr int LA = S::LA, LB = S::LB;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / S::WN, wn = wave % S::WN;
+  const int u = t / a.Kw, e = u * a.d - a.p, f = (t - u * a.Kw) * a.d - a.p;
+  const int K = a.N * a.HWy, zg = K, zx = a.N * a.H * a.W;
+  // LDS: planes of 32 channels x 32 k; all of a lane's loads lie in row tid / 4 % 32, planes tid / 128 + (NT / 128) i
+  uint32_t ca[LA], cb[LB];
+#pragma unroll
+  for (int i = 0; i < LA; ++i)
+    ca[i] = (uint32_t)min(m0 / 32 + (tid >> 7) + S::NT / 128 * i, a.Cop / 32 - 1) * (uint32_t)(zg + 1) * 64u + (tid & 3) * 16;
+#pragma unroll
+  for (int i = 0; i < LB; ++i)
+    cb[i] = (uint32_t)min(n0 / 32 + (tid >> 7) + S::NT / 128 * i, a.Cix / 32 - 1) * (uint32_t)(zx + 1) * 64u + (tid & 3) * 16;
+  const uint32_t lds0 = lds_of(smem) + wave * 1024;
+  // 32 pixels on: dh rows and dw columns (and dn images), then the wraps
+  const int dn = (int)a.d_py.div(32u), dr = 32 - dn * a.HWy, dh = (int)a.d_wy.div((uint32_t)dr), dw = dr - dh * a.Wy;
+  const int step_x = (dn * a.H + dh * a.s) * a.W + dw * a.s, wrap_w = a.s * (a.W - a.Wy), wrap_h = (a.H - a.Hy * a.s) * a.W;
+  const int end_w = a.Wy * a.s + f, end_h = a.Hy * a.s + e;
+  PixelWalk p;
+  {
+    p.q = kc0 * 64 + (tid >> 2 & 31);
+    const int n = (int)a.d_py.div((uint32_t)p.q), r = p.q - n * a.HWy;
+    const int h = (int)a.d_wy.div((uint32_t)r), w = r - h * a.Wy;
+    p.hs = h * a.s + e; p.ws = w * a.s + f;
+    p.xr = (n * a.H + p.hs) * a.W + p.ws;
+  }
+  auto fetch = [&](int buf) __attribute__((always_inline)) {
+    const uint32_t lds = lds0 + buf * S::kStage;
+    const bool ok = p.q < K && (uint32_t)p.hs < (uint32_t)a.H && (uint32_t)p.ws < (uint32_t)a.W;
+    const uint32_t g = (uint32_t)(ok ? p.q : zg) * 64u, x = (uint32_t)(ok ? p.xr : zx) * 64u;
+#pragma unroll
+    for (int i = 0; i < LA; ++i) dma16(a.gt, g + ca[i], lds + i * (16 * S::NT));
+#pragma unroll
+    for (int i = 0; i < LB; ++i) dma16(a.xt, x + cb[i], lds + S::A + i * (16 * S::NT));
+    p.q += 32; p.ws += dw * a.s; p.hs += dh * a.s; p.xr += step_x;
+    if (p.ws >= end_w) { p.ws -= a.Wy * a.s; p.hs += a.s; p.xr += wrap_w; }
+    if (p.hs >= end_h) { p.hs -= a.Hy * a.s; p.xr += wrap_h; }
+  };
+  uint4 fa[2], fb[2][S::TNW];
+  auto read = [&](int buf) __attribute__((always_inline)) {
+    const unsigned char* As = smem + buf * S::kStage;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      fa[ks] = frag_plane(As + wm * 2048, ks, lane);
+#pragma unroll
+      for (int j = 0; j < S::TNW; ++j) fb[ks][j] = frag_plane(As + S::A + (S::WN * j + wn) * 2048, ks, lane);
+    }
+  };
+  auto mul = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int j = 0; j < S::TNW; ++j) acc[0][j] = mma32(fa[ks], fb[ks][j], acc[0][j]);
+  };
+  stage_loop<LA + LB>(2 * (kc1 - kc0), fetch, read, mul);
+}
+
+// acc += w[rows m0 ..][steps] * g_y[columns of the tile, moved by the tap][steps]^T over steps (tap of the phase, 64 c_o)
+template <int TM, int TN>
+__device__ __forceinline__ void sd_mainloop(const XArgs& a, int m0, int tni, int it0, int iters, unsigned char* smem,
+                                            const int4* taps, f32x16 (&acc)[1][STile<TM, TN>::TNW]) {
+  using S = STile<TM, TN>;
+  constexpr int LA = S::LA, LB = S::LB, RP = S::NT / 4;   // RP: rows between a lane's loads
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / S::WN, wn = wave % S::WN;
+  const int row0 = tid >> 2;                                  // rows row0 + RP i
+  const uint32_t unit = 16 * ((tid & 3) ^ (row0 >> 2 & 3));   // the lane's 16 bytes of the 64 of a row
+  const uint32_t lds0 = lds_of(smem) + wave * 1024;
+  const int zg = a.N * a.HWy, np = a.Cop >> 5;                // planes of 32 c_o
+  uint32_t offa[LA], offb[LB];
+  int ph[LB], pw[LB], pn[LB];   // pixel of a column
+#pragma unroll
+  for (int i = 0; i < LB; ++i) {
+    const int jp = tni * S::BN + row0 + RP * i;
+    const int n = (int)a.d_qd.div((uint32_t)(jp >> 3)), q = jp - n * a.qd * 8;
+    ph[i] = (int)a.d_wq.div((uint32_t)q);
+    pw[i] = q - ph[i] * a.Wq;
+    pn[i] = n < a.N && q < a.PQ ? n * a.Hy : -1;
+  }
+  int kk = 2 * it0 / np, kc = 2 * it0 - kk * np;   // tap of the list and plane the next fetch takes
+  bool new_tap = true;
+  auto fetch = [&](int buf) __attribute__((always_inline)) {
+    if (new_tap) {   // (uniform)
+      const int t = __builtin_amdgcn_readfirstlane(taps[kk].x), qa = __builtin_amdgcn_readfirstlane(taps[kk].y);
+      const int qb = __builtin_amdgcn_readfirstlane(taps[kk].z);
+#pragma unroll
+      for (int i = 0; i < LA; ++i) offa[i] = (uint32_t)(t * np * a.Ci + min(m0 + row0 + RP * i, a.Ci - 1)) * 64u + unit;
+#pragma unroll
+      for (int i = 0; i < LB; ++i) {
+        const int h = ph[i] + qa, w = pw[i] + qb;
+        const bool ok = pn[i] >= 0 && (uint32_t)h < (uint32_t)a.Hy && (uint32_t)w < (uint32_t)a.Wy;
+        offb[i] = (uint32_t)(ok ? (pn[i] + h) * a.Wy + w : zg) * 64u + unit;
+      }
+    }
+    const uint32_t lds = lds0 + buf * S::kStage;
+    const uint32_t ka = (uint32_t)(kc * a.Ci) * 64u, kb = (uint32_t)kc * (uint32_t)(zg + 1) * 64u;
+#pragma unroll
+    for (int i = 0; i < LA; ++i) dma16(a.wr, offa[i] + ka, lds + i * (16 * S::NT));
+#pragma unroll
+    for (int i = 0; i < LB; ++i) dma16(a.gt, offb[i] + kb, lds + S::A + i * (16 * S::NT));
+    new_tap = ++kc == np;
+    if (new_tap) { kc = 0; ++kk; }
+  };
+  uint4 fa[2], fb[2][S::TNW];
+  auto read = [&](int buf) __attribute__((always_inline)) {
+    const unsigned char* As = smem + buf * S::kStage;
+    const int r = lane & 31, kg = lane >> 5, x = r >> 2 & 3;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      const int o = r * 64 + ((2 * ks + kg) ^ x) * 16;
+      fa[ks] = *reinterpret_cast<const uint4*>(As + 32 * wm * 64 + o);
+#pragma unroll
+      for (int j = 0; j < S::TNW; ++j) fb[ks][j] = *reinterpret_cast<const uint4*>(As + S::A + 32 * (S::WN * j + wn) * 64 + o);
+    }
+  };
+  auto mul = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int j = 0; j < S::TNW; ++j) acc[0][j] = mma32(fa[ks], fb[ks][j], acc[0][j]);
+  };
+  stage_loop<LA + LB>(2 * (iters - it0), fetch, read, mul);
+}
+
+// weight-gradient block L: K slab, tap and tile (see xwgrad_block)
+struct WTileAt {
+  int z, t, m0, n0;
+};
+__device__ __forceinline__ WTileAt wtile_at(const XArgs& a, int L, int bm, int bn) {
+  WTileAt w;
+  int rest;
+  // The hardware hands consecutive blocks to the eight XCDs in turn; with eight or more K slabs block L works on
+  // slab (L % 8) + 8 * (..), so that all taps and tiles of a slab share one XCD's L2 and each XCD touches an eighth
+  // of x and g_y.
+  if (a.xcd_slabs) {
+    const int idx = L >> 3;
+    const int zl = (int)a.d_r.div((uint32_t)idx);
+    w.z = (L & 7) + 8 * zl;
+    rest = idx - zl * a.R;
+  } else {
+    w.z = (int)a.d_r.div((uint32_t)L);
+    rest = L - w.z * a.R;
+  }
+  w.t = (int)a.d_tiles.div((uint32_t)rest);
+  const int tile = rest - w.t * a.tiles;
+  const int by = (int)a.d_tx.div((uint32_t)tile), bx = tile - by * a.tx;
+  w.m0 = by * bm;
+  w.n0 = bx * bn;
+  return w;
+}
+
+template <int TM, int TN>
+__global__ __launch_bounds__((STile<TM, TN>::NT), 4) void sgemm_k(XArgs a) {
+  using S = STile<TM, TN>;
+  struct Lds {   // (the operands first: the loads address the first 64 KB)
+    __attribute__((aligned(16))) unsigned char op[S::kBytes];
+    int4 taps[kTapsLds];
+    int flag;
+  };
+  __shared__ Lds lds;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave / S::WN, wn = wave % S::WN;
+  f32x16 acc[1][S::TNW];
+  zero_acc(acc);
+  int L = blockIdx.x;
+  if (a.d_first ? L >= a.nD : L < a.nW) {
+    if (a.d_first) L -= a.nD;
+    const WTileAt w = wtile_at(a, L, S::BM, S::BN);
+    if (w.z >= a.nz) return;   // (uniform)
+    sw_mainloop<TM, TN>(a, w.t, w.m0, w.n0, w.z * a.cpz, min(w.z * a.cpz + a.cpz, a.nchunks), lds.op, acc);
+    float* dst = a.part + ((long)w.z * a.KK + w.t) * a.Co * a.Ci;
+#pragma unroll
+    for (int j = 0; j < S::TNW; ++j) {
+      const int ci = w.n0 + 32 * (S::WN * j + wn) + (lane & 31);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int co = w.m0 + 32 * wm + acc_row(lane, v);
+        if (co < a.Co && ci < a.Ci) dst[(long)co * a.Ci + ci] = acc[0][j][v];
+      }
+    }
+    return;
+  }
+  // input gradient: rows c_i of one column tile (positions of the padded planes, counted over the batch) of one phase
+  if (!a.d_first) L -= a.nW;
+  const int per_ph = a.d_tm * a.d_tn;
+  const int tile = L / a.d_nz, z = L - tile * a.d_nz;
+  const int ph = tile / per_ph, rest = tile - ph * per_ph;
+  const int tni = rest / a.d_tm, tmi = rest - tni * a.d_tm;   // row tiles of one column tile run side by side
+  const int m0 = tmi * S::BM;
+  const int ntap = a.ntap[ph], nck = a.Cop >> 6;
+  const int it0 = z * a.d_its, iters = min(ntap * nck, it0 + a.d_its);   // steps of this slab
+  if (tid < min(ntap, kTapsLds)) lds.taps[tid] = a.taps[(long)ph * a.KK + tid];
+  __syncthreads();
+  if (it0 < iters) sd_mainloop<TM, TN>(a, m0, tni, it0, iters, lds.op, lds.taps, acc);
+  if (a.d_nz > 1 && !reduce_slabs<1, S::TNW, S::NT>(acc, a.partD + (long)tile * (a.d_nz + a.d_ngrp) * (4096 * TM * TN), z,
+                                                    a.tickD + tile * (1 + a.d_ngrp), a.d_nz, a.d_grp, a.d_ngrp, &lds.flag,
+                                                    a.Ci - m0 - 32 * wm, 64 * S::TNW))   // (all column tiles of the wave)
+    return;
+  // through LDS (rounded once to the storage type), out as 16-byte runs of pixels
+  bf16_t* Cs = reinterpret_cast<bf16_t*>(lds.op);
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < S::TNW; ++j)
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      Cs[(32 * wm + acc_row(lane, v)) * S::SC + 32 * (S::WN * j + wn) + (lane & 31)] = from_f32<bf16_t>(acc[0][j][v]);
+  __syncthreads();
+  constexpr int VB = S::BN / 8;
+  const int jv = tni * VB + tid % VB;               // this lane's column vector
+  const int nimg = (int)a.d_qd.div((uint32_t)jv), q = (jv - nimg * a.qd) * 8;
+  if (nimg >= a.N || q >= a.PQ) return;
+  bf16_t* out = static_cast<bf16_t*>(a.gx) + ((long)(ph * a.N + nimg) * a.Ci + m0) * a.PQ + q;
+  const int nr = min(S::BM, a.Ci - m0);
+#pragma unroll 4
+  for (int row = tid / VB; row < nr; row += S::NT / VB) {
+    bf16_t* d = out + (long)row * a.PQ;
+    const bf16_t* src = Cs + row * S::SC + tid % VB * 8;
+    if (q + 8 <= a.PQ) {
+      const uint4 val = *reinterpret_cast<const uint4*>(src);
+      Unal<bf16_t> o;
+      o.w[0] = val.x; o.w[1] = val.y; o.w[2] = val.z; o.w[3] = val.w;
+      *reinterpret_cast<Unal<bf16_t>*>(d) = o;
+    } else {
+      for (int e = 0; q + e < a.PQ; ++e) d[e] = src[e];
+    }
+  }
+}
+
 template <class T, int TM, int TN>
 __device__ __forceinline__ void xwgrad_block(const XArgs& a, int L, unsigned char* smem) {
   using X = XTile<T, TM, TN>;
   static_assert(XTile<raw_f32, TM, TN>::kOp <= X::kBytes || !is_split<T>(), "the second pass works in the same LDS");
-  // The hardware hands consecutive blocks to the eight XCDs in turn; with eight or more K slabs block L works on
-  // slab (L % 8) + 8 * (..), so that all taps and tiles of a slab share one XCD's L2 and each XCD touches an eighth
-  // of x and g_y.
-  int z, rest;
-  if (a.xcd_slabs) {
-    const int idx = L >> 3;
-    const int zl = (int)a.d_r.div((uint32_t)idx);
-    z = (L & 7) + 8 * zl;
-    rest = idx - zl * a.R;
-  } else {
-    z = (int)a.d_r.div((uint32_t)L);
-    rest = L - z * a.R;
-  }
+  const WTileAt w = wtile_at(a, L, X::BM, X::BN);
+  const int z = w.z, t = w.t, m0 = w.m0, n0 = w.n0;
   if (z >= a.nz) return;  // uniform for the block
-  const int t = (int)a.d_tiles.div((uint32_t)rest), tile = rest - t * a.tiles;
-  const int by = (int)a.d_tx.div((uint32_t)tile), bx = tile - by * a.tx;
-  const int m0 = by * X::BM, n0 = bx * X::BN;
   const int kc0 = z * a.cpz, kc1 = min(kc0 + a.cpz, a.nchunks);
   f32x16 acc[TM][TN];
   uint32_t low = 0;
@@ -795,6 +1194,9 @@ long max_shift(const Geom& g, const XGeo& q) {
 }
 
 struct XPlan {
+  bool staged;
+  int Cop, Cix;   // channels of a staged row
+  size_t off_gt, off_xt, off_wr;
   size_t off_tabw, off_tabd, off_taps, off_tick, off_wt, off_xq, off_gxq, off_part, off_pd, total;
   int nvw, nvd, tm, tn, Cip, ntickets;
   int d_nz, d_its, d_grp, d_ngrp, d_first;
@@ -825,7 +1227,11 @@ int slab_chunks(int nchunks, long z) {
   }
   return cdiv(nchunks, z);
 }
-XPlan make_plan(const Geom& g, bool want_gw, bool want_gx) {
+// Slabs dealt to the XCDs: also a number that is no multiple of eight while no XCD gets more than a tenth above its share (its
+// last round of block numbers is partly empty).  64 -> 64 channels, 200 x 200, n = 4, 87 slabs: both gradients 94 -> 69 us,
+// 120 x 160, n = 8 (86): 90 -> 65; 128 -> 128, 60 x 80, n = 8 (50): 59 -> 51.
+bool deal_slabs(int nz) { return 10 * (cdiv(nz, 8) * 8) <= 11 * nz; }
+XPlan make_plan(const Geom& g, bool want_gw, bool want_gx, bool staged) {
   const XGeo q = make_xgeo(g);
   const int VE = 16 / g.b;
   XPlan p = {};
@@ -835,7 +1241,10 @@ XPlan make_plan(const Geom& g, bool want_gw, bool want_gx) {
   tile_shape(g, q, want_gw, &p.tm, &p.tn, &slots);
   p.Cip = cdiv(g.Ci, VE) * VE;
   p.qv = up8(q.PY) / VE;
-  p.nchunks = cdiv((long)g.N * p.qv, 8);
+  p.staged = staged;
+  p.Cop = (g.Co + 63) / 64 * 64;
+  p.Cix = (g.Ci + 63) / 64 * 64;
+  p.nchunks = staged ? cdiv((long)g.N * q.PY, 64) : cdiv((long)g.N * p.qv, 8);
   p.w_tm = cdiv(g.Co, 64 * p.tm);
   p.w_tn = cdiv(g.Ci, 64 * p.tn);
   p.qd = up8(q.PQ) / VE;
@@ -865,6 +1274,19 @@ XPlan make_plan(const Geom& g, bool want_gw, bool want_gx) {
   p.nz = cdiv(p.nchunks, p.cpz);
   p.d_first = (p.d_nz == 1 ? d_steps : p.d_its) > p.cpz ? 1 : 0;   // the longer blocks start first
   size_t off = 0;
+  if (staged) {
+    p.off_taps = off; off += align256(sizeof(int4) * (size_t)q.nph * g.KK + sizeof(int) * q.nph);
+    p.off_tick = off; off += align256(sizeof(int) * (size_t)p.ntickets);
+    p.off_gt = off; off += align256(((size_t)g.N * q.PY + 1) * p.Cop * g.b);
+    p.off_xt = off; if (want_gw) off += align256(((size_t)g.N * g.H * g.W + 1) * p.Cix * g.b);
+    p.off_wr = off; if (want_gx) off += align256(((size_t)g.Ci * g.KK + 1) * p.Cop * g.b);
+    p.off_gxq = off; if (want_gx && g.s > 1) off += align256((size_t)q.nph * g.N * g.Ci * q.PQ * g.b);
+    p.off_part = off; if (want_gw) off += align256((size_t)p.nz * g.KK * g.Co * g.Ci * sizeof(float));
+    p.off_pd = off;
+    if (want_gx && p.d_nz > 1) off += align256((size_t)d_tiles * (p.d_nz + p.d_ngrp) * 4096 * p.tm * p.tn * sizeof(float));
+    p.total = off;
+    return p;
+  }
   p.off_tabw = off; off += align256((size_t)g.KK * p.nvw);
   p.off_tabd = off; off += align256((size_t)q.nph * g.KK * p.nvd);
   p.off_taps = off; off += align256(sizeof(int) * ((size_t)g.KK + 2 * (size_t)q.nph * g.KK + q.nph));
@@ -895,60 +1317,75 @@ int interleave_planes(const Geom& g, const XGeo& q) {
   return (int)(ppb < VE ? VE : ppb);
 }
 
-template <class T>
-hipError_t implicit_t(const Geom& g, const void* x, const void* w, const void* g_y, float* g_w, void* g_x,
-                      void* ws, hipStream_t st) {
-  const bool want_gw = g_w != nullptr, want_gx = g_x != nullptr;
+// Calls whose operands are staged: bf16, kernels larger than 1 x 1, channels that fill most of the rows they are padded to
+// (64), offsets of staged rows within 32 bits; not where the copies alone would take a call out of the library's own scratch.
+// Not either where the copies cost a weight gradient alone more than the products gain: 128 x 128 tiles, few operations per
+// element, maps past 64 MiB.  3 x 3, unstaged / staged in us: 128 -> 128, 60 x 80, n = 32 (79 MB) 81 / 86, n = 128 270 / 319;
+// 96 -> 96, 112 x 112, n = 128 629 / 783; 128 -> 256, 60 x 80, n = 128 552 / 594; but 128 -> 128, 28 x 28, n = 64 43.7 / 42.2,
+// 256 -> 256, 60 x 80, n = 128 1613 / 1210; 5 x 5, 128 -> 128, 56 x 56, n = 64 275 / 237.  With planes of whole vectors either
+// form returns the same weight gradient; with others all calls take the same one (57 x 81, n = 64, both gradients 274 / 269).
+bool staged_ok(const Geom& g, bool want_gx) {
+  if (g.dtype != GF_BF16 || g.KK == 1 || g.KK > kTapsLds) return false;
   const XGeo q = make_xgeo(g);
-  const XPlan p = make_plan(g, want_gw, want_gx);
+  const long cop = (g.Co + 63) / 64 * 64, cix = (g.Ci + 63) / 64 * 64, lim = (1L << 31) - 4096;
+  if (4 * g.Co < 3 * cop || 4 * g.Ci < 3 * cix) return false;
+  if (((long)g.N * q.PY + 1) * cop * 2 > lim || ((long)g.N * g.H * g.W + 1) * cix * 2 > lim ||
+      ((long)g.Ci * g.KK + 1) * cop * 2 > lim)
+    return false;
+  if (g.s == 1 && g.Co > 64 && g.Ci > 64 && (long)g.KK * g.Co * g.Ci <= 800L * (g.Co + g.Ci) &&
+      ((long)g.N * q.PY * g.Co + (long)g.N * g.H * g.W * g.Ci) * 2 >= (64L << 20) && !(want_gx && q.PY % 8 == 0))
+    return false;
+  return !g.own_scratch || make_plan(g, true, true, true).total <= GF_STATIC_SCRATCH_BYTES ||
+         make_plan(g, true, true, false).total > GF_STATIC_SCRATCH_BYTES;
+}
+
+// the product launch and the last one (x: the map itself or its phase planes; staged layers: in the workspace)
+template <class T>
+hipError_t implicit_products(const Geom& g, const XGeo& q, const XPlan& p, const void* x, const void* g_y, float* g_w, void* g_x,
+                             char* wsb, hipStream_t st) {
+  const bool want_gw = g_w != nullptr, want_gx = g_x != nullptr;
   constexpr int VE = El<T>::VE;
-  char* wsb = static_cast<char*>(ws);
   int2* tapd = reinterpret_cast<int2*>(wsb + p.off_taps);   // 8-byte aligned: first in the region
   int* tapw = reinterpret_cast<int*>(tapd + (size_t)q.nph * g.KK);
-  int* ntap = tapw + g.KK;
-  // ---- set-up
-  PrepArgs t;
-  t.tabw = reinterpret_cast<uint8_t*>(wsb + p.off_tabw);
-  t.tabd = reinterpret_cast<uint8_t*>(wsb + p.off_tabd);
-  t.tapw = tapw; t.tapd = tapd; t.ntap = ntap;
-  t.N = g.N; t.Ci = g.Ci; t.H = g.H; t.W = g.W; t.Hy = g.Hy; t.Wy = g.Wy; t.Hq = q.Hq; t.Wq = q.Wq;
-  t.Kw = g.Kw; t.KK = g.KK; t.s = g.s; t.d = g.dl; t.p = g.p; t.nvw = p.nvw; t.nvd = p.nvd;
-  t.tickets = reinterpret_cast<int*>(wsb + p.off_tick); t.ntickets = want_gx ? p.ntickets : 0;
-  const int nmax = p.nvw > p.nvd * q.nph ? p.nvw : p.nvd * q.nph;
-  const int tab_blocks = cdiv(std::max((long)g.KK * nmax, (long)t.ntickets), kT);
-  const int w_blocks = want_gx ? g.Co * cdiv(p.Cip, kWPairs) : 0;
-  const int x_blocks = (want_gw && g.s > 1) ? cdiv(cdiv((long)q.nph * g.N * g.Ci * q.PQ, VE), kT) : 0;
-  GF_LAUNCH(prep_k<T>, dim3(tab_blocks + w_blocks + x_blocks), dim3(kT), 0, st, t, tab_blocks, w_blocks,
-            static_cast<const T*>(w), reinterpret_cast<T*>(wsb + p.off_wt), g.Co, p.Cip, static_cast<const T*>(x),
-            reinterpret_cast<T*>(wsb + p.off_xq));
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
   // ---- both products
   XArgs a = {};
   a.N = g.N; a.Ci = g.Ci; a.Co = g.Co; a.KK = g.KK;
   a.gy = g_y; a.HWy = q.PY; a.tot_gy = g.N * g.Co * q.PY;
-  a.x = g.s > 1 ? static_cast<const void*>(wsb + p.off_xq) : x;
+  a.x = x;
   a.part = reinterpret_cast<float*>(wsb + p.off_part);
-  a.tabw = t.tabw; a.tapw = tapw;
+  a.tabw = reinterpret_cast<uint8_t*>(wsb + p.off_tabw); a.tapw = tapw;
   a.HW = q.PQ; a.tot_x = q.nph * g.N * g.Ci * q.PQ;
   a.qv = p.qv; a.kvecs = g.N * p.qv; a.nvw = p.nvw;
   a.nchunks = p.nchunks; a.cpz = p.cpz; a.nz = p.nz;
   a.tx = p.w_tn; a.tiles = p.w_tm * p.w_tn; a.R = a.tiles * g.KK;
-  a.xcd_slabs = p.nz % 8 == 0 ? 1 : 0;
+  a.xcd_slabs = deal_slabs(p.nz) ? 1 : 0;
   a.nW = !want_gw ? 0 : a.xcd_slabs ? 8 * a.R * cdiv(p.nz, 8) : a.R * p.nz;
   a.wt = wsb + p.off_wt; a.gx = g.s > 1 ? static_cast<void*>(wsb + p.off_gxq) : g_x;
-  a.tabd = t.tabd; a.tapd = tapd; a.ntap = ntap;
+  a.tabd = reinterpret_cast<uint8_t*>(wsb + p.off_tabd); a.tapd = tapd;
+  a.ntap = p.staged ? reinterpret_cast<int*>(wsb + p.off_taps + sizeof(int4) * (size_t)q.nph * g.KK) : tapw + g.KK;
   a.Cip = p.Cip; a.PQ = q.PQ; a.qd = p.qd; a.nvd = p.nvd;
-  a.d_tm = p.d_tm; a.d_tn = p.d_tn; a.nck = cdiv(g.Co, El<T>::KB);
+  a.d_tm = p.d_tm; a.d_tn = p.d_tn; a.nck = cdiv(g.Co, El<T>::KB);   // (a staged row's chunks are as many)
   a.nD = want_gx ? p.d_tm * p.d_tn * q.nph * p.d_nz : 0;
   a.d_nz = p.d_nz; a.d_its = p.d_its; a.d_grp = p.d_grp; a.d_ngrp = p.d_ngrp; a.d_first = p.d_first;
-  a.partD = reinterpret_cast<float*>(wsb + p.off_pd); a.tickD = t.tickets;
+  a.partD = reinterpret_cast<float*>(wsb + p.off_pd); a.tickD = reinterpret_cast<int*>(wsb + p.off_tick);
   a.d_qv = FastDiv((uint32_t)p.qv); a.d_qd = FastDiv((uint32_t)p.qd);
   a.d_r = FastDiv((uint32_t)a.R); a.d_tiles = FastDiv((uint32_t)a.tiles); a.d_tx = FastDiv((uint32_t)a.tx);
-  if (p.tn == 2) GF_LAUNCH((xgemm_k<T, 2, 2>), dim3(a.nW + a.nD), dim3(kT), 0, st, a);
-  else if (p.tm == 2) GF_LAUNCH((xgemm_k<T, 2, 1>), dim3(a.nW + a.nD), dim3(kT), 0, st, a);
-  else GF_LAUNCH((xgemm_k<T, 1, 1>), dim3(a.nW + a.nD), dim3(kT), 0, st, a);
-  e = hipGetLastError();
+  if (p.staged) {
+    a.gt = wsb + p.off_gt; a.xt = wsb + p.off_xt; a.wr = wsb + p.off_wr;
+    a.taps = reinterpret_cast<const int4*>(wsb + p.off_taps);
+    a.Cop = p.Cop; a.Cix = p.Cix;
+    a.H = g.H; a.W = g.W; a.Hy = g.Hy; a.Wy = g.Wy; a.Wq = q.Wq; a.Kw = g.Kw; a.s = g.s; a.d = g.dl; a.p = g.p;
+    a.d_py = FastDiv((uint32_t)q.PY); a.d_wy = FastDiv((uint32_t)g.Wy); a.d_wq = FastDiv((uint32_t)q.Wq);
+  }
+  const dim3 grid(a.nW + a.nD);
+  if (p.staged) {
+    if (p.tn == 2) GF_LAUNCH((sgemm_k<2, 2>), grid, dim3(STile<2, 2>::NT), 0, st, a);
+    else if (p.tm == 2) GF_LAUNCH((sgemm_k<2, 1>), grid, dim3(STile<2, 1>::NT), 0, st, a);
+    else GF_LAUNCH((sgemm_k<1, 1>), grid, dim3(STile<1, 1>::NT), 0, st, a);
+  } else if (p.tn == 2) GF_LAUNCH((xgemm_k<T, 2, 2>), grid, dim3(kT), 0, st, a);
+  else if (p.tm == 2) GF_LAUNCH((xgemm_k<T, 2, 1>), grid, dim3(kT), 0, st, a);
+  else GF_LAUNCH((xgemm_k<T, 1, 1>), grid, dim3(kT), 0, st, a);
+  hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // ---- slab sums, interleave
   const bool inter = want_gx && g.s > 1;
@@ -974,6 +1411,53 @@ hipError_t implicit_t(const Geom& g, const void* x, const void* w, const void* g
   return hipGetLastError();
 }
 
+template <class T>
+hipError_t implicit_t(const Geom& g, const void* x, const void* w, const void* g_y, float* g_w, void* g_x,
+                      void* ws, hipStream_t st) {
+  const bool want_gw = g_w != nullptr, want_gx = g_x != nullptr;
+  const XGeo q = make_xgeo(g);
+  const bool staged = staged_ok(g, want_gx);
+  const XPlan p = make_plan(g, want_gw, want_gx, staged);
+  constexpr int VE = El<T>::VE;
+  char* wsb = static_cast<char*>(ws);
+  if (staged) {
+    StageArgs t = {};
+    t.taps = want_gx ? reinterpret_cast<int4*>(wsb + p.off_taps) : nullptr;
+    t.ntap = reinterpret_cast<int*>(wsb + p.off_taps + sizeof(int4) * (size_t)q.nph * g.KK);
+    t.tickets = reinterpret_cast<int*>(wsb + p.off_tick); t.ntickets = want_gx ? p.ntickets : 0;
+    t.KK = g.KK; t.Kw = g.Kw; t.s = g.s; t.d = g.dl; t.p = g.p;
+    auto job = [](const void* src, void* dst, int N, int C, int PX, int Cp) {
+      return StageJob{src, dst, N, C, PX, Cp, cdiv(PX, 64), Cp / 64, N * cdiv(PX, 64) * (Cp / 64)};
+    };
+    t.job[0] = job(g_y, wsb + p.off_gt, g.N, g.Co, q.PY, p.Cop);
+    if (want_gw) t.job[1] = job(x, wsb + p.off_xt, g.N, g.Ci, g.H * g.W, p.Cix);
+    if (want_gx) t.job[2] = job(w, wsb + p.off_wr, 1, g.Co, g.Ci * g.KK, p.Cop);   // [c_o][c_i taps] -> [c_i taps][c_o]
+    GF_LAUNCH(stage_k, dim3(1 + t.job[0].blocks + t.job[1].blocks + t.job[2].blocks), dim3(kT), 0, st, t);
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : implicit_products<T>(g, q, p, nullptr, g_y, g_w, g_x, wsb, st);
+  }
+  int2* tapd = reinterpret_cast<int2*>(wsb + p.off_taps);   // 8-byte aligned: first in the region
+  int* tapw = reinterpret_cast<int*>(tapd + (size_t)q.nph * g.KK);
+  int* ntap = tapw + g.KK;
+  // ---- set-up
+  PrepArgs t;
+  t.tabw = reinterpret_cast<uint8_t*>(wsb + p.off_tabw);
+  t.tabd = reinterpret_cast<uint8_t*>(wsb + p.off_tabd);
+  t.tapw = tapw; t.tapd = tapd; t.ntap = ntap;
+  t.N = g.N; t.Ci = g.Ci; t.H = g.H; t.W = g.W; t.Hy = g.Hy; t.Wy = g.Wy; t.Hq = q.Hq; t.Wq = q.Wq;
+  t.Kw = g.Kw; t.KK = g.KK; t.s = g.s; t.d = g.dl; t.p = g.p; t.nvw = p.nvw; t.nvd = p.nvd;
+  t.tickets = reinterpret_cast<int*>(wsb + p.off_tick); t.ntickets = want_gx ? p.ntickets : 0;
+  const int nmax = p.nvw > p.nvd * q.nph ? p.nvw : p.nvd * q.nph;
+  const int tab_blocks = cdiv(std::max((long)g.KK * nmax, (long)t.ntickets), kT);
+  const int w_blocks = want_gx ? g.Co * cdiv(p.Cip, kWPairs) : 0;
+  const int x_blocks = (want_gw && g.s > 1) ? cdiv(cdiv((long)q.nph * g.N * g.Ci * q.PQ, VE), kT) : 0;
+  GF_LAUNCH(prep_k<T>, dim3(tab_blocks + w_blocks + x_blocks), dim3(kT), 0, st, t, tab_blocks, w_blocks,
+            static_cast<const T*>(w), reinterpret_cast<T*>(wsb + p.off_wt), g.Co, p.Cip, static_cast<const T*>(x),
+            reinterpret_cast<T*>(wsb + p.off_xq));
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return implicit_products<T>(g, q, p, g.s > 1 ? static_cast<const void*>(wsb + p.off_xq) : x, g_y, g_w, g_x, wsb, st);
+}
 // K slabs of the plain contraction part[z][co][ci] = sum_{n, p} a[n, co, p] * b[n, ci, p] over maps of P pixels
 void plain_plan(const Geom& g, int* nz, int* cpz, int* nchunks) {
   *nchunks = cdiv((long)g.N * cdiv(g.P, 16 / g.b), 8);
@@ -995,7 +1479,7 @@ hipError_t plain_wgrad_t(const Geom& g, const void* x_u, const void* gy_u, float
   a.tx = cdiv(g.Ci, 128);
   a.tiles = a.tx * cdiv(g.Co, 128);
   a.R = a.tiles;
-  a.xcd_slabs = a.nz % 8 == 0 ? 1 : 0;
+  a.xcd_slabs = deal_slabs(a.nz) ? 1 : 0;
   a.tot_x = g.N * g.Ci * g.P;
   a.tot_gy = g.N * g.Co * g.P;
   a.nW = a.xcd_slabs ? 8 * a.R * cdiv(a.nz, 8) : a.R * a.nz;
@@ -1067,7 +1551,7 @@ static bool plain_pointwise(const Geom& g, Geom* e) {
 size_t ws_implicit(const Geom& g, bool want_gw, bool want_gx) {
   Geom e;
   if (plain_pointwise(g, &e)) return ws_dense(e, want_gw, want_gx, true, false);
-  return make_plan(g, want_gw, want_gx).total;
+  return make_plan(g, want_gw, want_gx, staged_ok(g, want_gx)).total;
 }
 
 // g_w and / or g_x (either may be null): one set-up launch, then the GEMM launches

@@ -17,6 +17,7 @@ struct Geom {
   int Cg, Og;   // channels per group on the input / output side
   int KK, P;    // taps, patches per plane
   int dtype, b; // gf_dtype, bytes per element
+  bool own_scratch = false;   // the entry also exists on the library's own scratch, with the same bits
 };
 
 gf_status make_geom(const gf_conv_desc* d, Geom* g);

@@ -124,6 +124,63 @@ def test_vanilla_products(oracle, case, dtype):
         assert rel_err(a, r) <= TOL[dtype] and torch.equal(a, b)
 
 
+# N, C_in, C_out, H, W, K, stride, padding, dilation: bf16 layers whose operands are staged -- tiles and chunks of 64 channels
+# and pixels that are not full, phases, slabs of either product -- and the edges of the rule
+STAGED_CASES = [
+    (1, 64, 64, 1, 1, 3, 1, 1, 1),       # one pixel
+    (1, 48, 64, 5, 7, 3, 1, 1, 1),       # fewest channels on one side, less than a chunk of pixels
+    (3, 47, 64, 8, 8, 3, 1, 1, 1),       # one channel fewer: not staged
+    (3, 64, 96, 9, 9, 5, 1, 2, 1),       # 128 x 64 tiles that are not full on either side
+    (2, 97, 127, 13, 11, 3, 2, 1, 1),    # odd channels, phase planes of odd extents
+    (2, 50, 61, 16, 20, 3, 3, 1, 1),     # stride 3
+    (2, 64, 64, 14, 14, 4, 2, 1, 1),     # even kernel, stride 2
+    (2, 144, 192, 12, 10, 3, 1, 2, 2),   # dilation
+    (4, 64, 64, 10, 12, 11, 1, 5, 1),    # 121 taps
+    (1, 512, 256, 4, 4, 3, 1, 1, 1),     # K slabs of the input gradient, summed inside the launch
+    (2, 320, 128, 5, 5, 3, 2, 1, 1),     # ... over phases with different numbers of taps
+    (16, 192, 255, 28, 28, 3, 1, 1, 1),  # 128 x 128 tiles, a last one of 127 rows
+    (33, 64, 64, 30, 30, 3, 1, 1, 1),    # many slabs, no multiple of eight
+]
+
+
+@pytest.mark.parametrize("case", STAGED_CASES)
+def test_vanilla_staged_operands(oracle, case):
+    test_vanilla_products(oracle, case, "bf16")
+    N, Ci, Co, H, W, K, s, p, dl = case
+    d = mk(N, Ci, Co, H, W, K, s, p, dl, r=1, dtype="bf16")
+    sh = T.shapes(d)
+    x, w, gy = (randn(sh[k], i, "bf16") for i, k in enumerate(("x", "w", "g_y"), 1))
+    e_w, e_x = T.conv_bwd_exact(d, x.cuda(), w.cuda(), gy.cuda())
+    f_w, f_x, _ = T.conv_bwd_filtered(d, gy.cuda(), x.cuda(), w.cuda())   # patches of one pixel: the same products
+    assert torch.equal(e_w, f_w) and torch.equal(e_x, f_x)
+    if H * W == 1:
+        return   # (no finite value would be left)
+    gy[0, Co - 1, 0, 0], x[N - 1, 0, H - 1, W - 1] = float("inf"), float("-inf")
+    g_w, g_x = T.conv_bwd_exact(d, x.cuda(), w.cuda(), gy.cuda())
+    with np.errstate(invalid="ignore", over="ignore"):
+        r_w, r_x = oracle.bwd_exact(odesc(oracle, d), to64(x), to64(w), to64(gy))
+    same_values(g_w, r_w, TOL["bf16"]), same_values(g_x, r_x, TOL["bf16"])
+
+
+@pytest.mark.parametrize("case", [(38, 96, 128, 64, 64, 3, 1, 1, 1), (40, 128, 96, 63, 61, 3, 1, 1, 1)])
+def test_vanilla_weight_gradient_alone_on_a_large_map(oracle, case):
+    """Past 64 MiB the weight gradient alone of such a layer reads the maps themselves: the bits of the call for both."""
+    N, Ci, Co, H, W, K, s, p, dl = case
+    d = mk(*case, r=2, dtype="bf16")
+    sh = T.shapes(d)
+    x, w, gy = (randn(sh[k], i, "bf16") for i, k in enumerate(("x", "w", "g_y"), 1))
+    g_w, g_x = T.conv_bwd_exact(d, x.cuda(), w.cuda(), gy.cuda())
+    o_w, _ = T.conv_bwd_exact(d, x.cuda(), None, gy.cuda(), want_gx=False)
+    _, o_x = T.conv_bwd_exact(d, None, w.cuda(), gy.cuda(), want_gw=False)
+    assert torch.equal(g_w, o_w) and torch.equal(g_x, o_x)
+    od = odesc(oracle, mk(N, 2, 1, H, W, K, s, p, dl, r=2, dtype="bf16"))
+    r_w, _ = oracle.bwd_exact(od, to64(x[:, 31:33]), None, to64(gy[:, Co - 1:]), want_gx=False)
+    assert rel_err(g_w[Co - 1:, 31:33], r_w) <= TOL["bf16"]
+    od = odesc(oracle, mk(1, Ci, Co, H, W, K, s, p, dl, r=2, dtype="bf16"))
+    _, r_x = oracle.bwd_exact(od, None, to64(w), to64(gy[N - 1:]), want_gw=False)
+    assert rel_err(g_x[N - 1:], r_x) <= TOL["bf16"]
+
+
 # N, C, H, W, K, padding: both gradients of a depthwise layer in one pass (ragged groups of pixels, frames, image runs)
 DW_EXACT_CASES = [
     (3, 5, 20, 20, 3, 1),
