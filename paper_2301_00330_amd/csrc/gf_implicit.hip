@@ -1536,7 +1536,8 @@ bool implicit_ok(const Geom& g) {
 }
 
 // A 1 x 1 stride-1 layer without padding has no taps to shift: its maps are reduced maps of one-pixel patches, and the
-// two-product launch of the filtered path computes both gradients from them (24 -> 144 channels, 56 x 56, fp32).
+// two-product launch of the filtered path computes both gradients from them, or where few channels meet many pixels one pass
+// over the maps (gf_pixel.hip).
 static bool plain_pointwise(const Geom& g, Geom* e) {
   if (g.KK != 1 || g.s != 1 || g.p != 0) return false;
   // (bf16 from 6 GFLOP per product on: 128-row tiles, 140 against 183 us for 2048 -> 256 channels, 64 x 64, N = 8)
@@ -1550,7 +1551,7 @@ static bool plain_pointwise(const Geom& g, Geom* e) {
 
 size_t ws_implicit(const Geom& g, bool want_gw, bool want_gx) {
   Geom e;
-  if (plain_pointwise(g, &e)) return ws_dense(e, want_gw, want_gx, true, false);
+  if (plain_pointwise(g, &e)) return pointwise_ok(e) ? ws_pointwise(e, want_gw) : ws_dense(e, want_gw, want_gx, true, false);
   return make_plan(g, want_gw, want_gx, staged_ok(g, want_gx)).total;
 }
 
@@ -1558,7 +1559,10 @@ size_t ws_implicit(const Geom& g, bool want_gw, bool want_gx) {
 hipError_t launch_implicit(const Geom& g, const void* x, const void* w, const void* g_y, float* g_w, void* g_x,
                            void* ws, hipStream_t st) {
   Geom e;
-  if (plain_pointwise(g, &e)) return launch_dense(e, g_y, false, x, w, nullptr, g_w, g_x, true, nullptr, ws, st);
+  if (plain_pointwise(g, &e)) {
+    if (pointwise_ok(e)) return launch_pointwise(e, g_y, x, w, g_w, g_x, ws, st);
+    return launch_dense(e, g_y, false, x, w, nullptr, g_w, g_x, true, nullptr, ws, st);
+  }
   return g.dtype == GF_BF16 ? implicit_t<bf16_t>(g, x, w, g_y, g_w, g_x, ws, st)
                             : implicit_t<float>(g, x, w, g_y, g_w, g_x, ws, st);
 }

@@ -274,6 +274,13 @@ hipError_t launch_dense(const Geom& g, const void* src, bool src_is_gy, const vo
                         void* gy_u_out, float* g_w, void* g_x, bool reduced, const void* mask_u, void* ws,
                         hipStream_t st);
 
+// Both gradients (or one: g_w or g_x null) of a pointwise fp32 layer with at most 32 channels on one side, one pass over maps
+// of g.P pixels (gf_pixel.hip).
+bool pointwise_ok(const Geom& g);
+size_t ws_pointwise(const Geom& g, bool want_w);
+hipError_t launch_pointwise(const Geom& g, const void* gy, const void* x, const void* w, float* g_w, void* g_x, void* ws,
+                            hipStream_t st);
+
 // One-pass filtered backward of a depthwise stride-1 layer (gf_fused.hip): filter, weight
 // gradient partials ([nz, C] in `part`, to be finalized) and input gradient.
 bool dw_fused_ok(const Geom& g, int* nz);

@@ -1,0 +1,429 @@
+// Both gradients of a pointwise layer with few channels on one side, in ONE pass over the maps:
+//   g_w[co][ci]     = sum_{n, p} gy[n][co][p] x[n][ci][p]
+//   g_x[n][ci][p]   = sum_co     w[co][ci]    gy[n][co][p]
+// for fp32 1 x 1 stride-1 layers without the filter.
+//
+// Bound: memory, if every map is touched once.  As two products on 64 x 64 tiles (dense_gemm_k) such a layer reads gy
+// twice, splits every fp32 operand once per tile that uses it and multiplies 64 columns of which 24 exist: 17 000 chunks of
+// 64 x 64 x 32 for 24 -> 144 channels, 56 x 56, n = 32, which take a CU 0.6 us each.  Here a block walks over runs of
+// KB pixels of ALL channels (128 bytes a row), splits each value once on its way into LDS and multiplies it from there
+// twice: rows [channel][pixel] are K-major for the weight gradient and rows of k for the input gradient (transposing
+// reads).  The weight gradient stays in registers until the block's last run; a slab per block, added by
+// a launch of their own.  The kernel's fragments are split once per block.
+#include "gf_gemm.h"
+
+#include <algorithm>
+
+namespace gf {
+
+namespace {
+
+constexpr int KB = El<float>::KB, VE = El<float>::VE;   // pixels of a run, of a 16-byte vector
+
+struct PixArgs {
+  int N, Ci, Co, PX;
+  int cpi, chunks, cpb;       // runs of KB pixels per image, all, per block
+  int tot_gy, tot_x;
+  const float *gy, *x, *w;
+  float* part;                // [block][Co][Ci]; null: no weight gradient
+  float* gx;                  // null: no input gradient
+  FastDiv d_cpi;
+};
+
+// MT, NC: tiles of 32 output and input channels, one of them 1
+template <int MT, int NC>
+struct PixTile {
+  static constexpr int RW = 64 + 16;                 // bytes of a row of a term: eight rows read together cover all banks
+  static constexpr int ROWS = 32 * (MT + NC), kTerm = ROWS * RW;
+  static constexpr int S = 33;                       // element stride of the staged sums
+  static constexpr int kOp = 3 * kTerm, kSum = 4 * 32 * S * 4;
+  static constexpr bool EXPAND = MT > 1;             // the waves share K = c_o of the input gradient, else its tiles of c_i
+  static constexpr int WT = (MT * NC + 3) / 4;       // weight-gradient tiles of a wave
+  static constexpr int DT = EXPAND ? 1 : (NC + 3) / 4;            // input-gradient tiles of a wave
+  static constexpr int KW = EXPAND ? (2 * MT + 3) / 4 : 2;        // its steps of 16 c_o
+};
+
+// The block's pixels again with fp32 multiplications, for operands that three bf16 terms do not hold (split_failed):
+// infinities, NaN, values past the largest bf16 or below 2^-110.
+__device__ __forceinline__ void pixels_again(const PixArgs& a, int c0, int c1) {
+  if (a.part)
+    for (int i = threadIdx.x; i < a.Co * a.Ci; i += kT) {
+      const int co = i / a.Ci, ci = i - co * a.Ci;
+      float s = 0.f;
+      for (int c = c0; c < c1; ++c) {
+        const int n = (int)a.d_cpi.div((uint32_t)c), p0 = (c - n * a.cpi) * KB;
+        const float *g = a.gy + ((long)n * a.Co + co) * a.PX, *h = a.x + ((long)n * a.Ci + ci) * a.PX;
+        float t = 0.f;
+#pragma unroll 1
+        for (int p = p0; p < min(p0 + KB, a.PX); ++p) t = __builtin_fmaf(g[p], h[p], t);
+        s += t;
+      }
+      a.part[(long)blockIdx.x * a.Co * a.Ci + i] = s;
+    }
+  if (a.gx)
+    for (int c = c0; c < c1; ++c) {
+      const int n = (int)a.d_cpi.div((uint32_t)c), p0 = (c - n * a.cpi) * KB;
+      for (int i = threadIdx.x; i < a.Ci * KB; i += kT) {
+        const int ci = i / KB, p = p0 + i % KB;
+        if (p >= a.PX) continue;
+        float s = 0.f;
+#pragma unroll 1
+        for (int co = 0; co < a.Co; ++co) s = __builtin_fmaf(a.w[co * a.Ci + ci], a.gy[((long)n * a.Co + co) * a.PX + p], s);
+        a.gx[((long)n * a.Ci + ci) * a.PX + p] = s;
+      }
+    }
+}
+
+template <int MT, int NC, bool RAG>
+__global__ __launch_bounds__(kT, 2) void pointwise_k(PixArgs a) {
+  using L = PixTile<MT, NC>;
+  constexpr int RV = MT + NC;   // vectors of a lane per run
+  __shared__ __attribute__((aligned(16))) unsigned char smem[L::kOp + L::kSum];
+  float* sums = reinterpret_cast<float*>(smem + L::kOp);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int vi = tid & 7, row0 = tid >> 3, r = lane & 31, kg = lane >> 5;
+  const int c0 = blockIdx.x * a.cpb, c1 = min(c0 + a.cpb, a.chunks);
+  const bool want_w = a.part != nullptr, want_d = a.gx != nullptr;
+  const int wtiles = L::EXPAND ? (a.Co + 31) >> 5 : (a.Ci + 31) >> 5, nks = (a.Co + 15) >> 4;
+  uint32_t low = 0;
+  float bad = 0.f;
+
+  u32x4_t v[RV];
+  int keep = 0, n = 0, p0 = 0, off = 0;
+  auto fetch = [&](int c) __attribute__((always_inline)) {
+    n = (int)a.d_cpi.div((uint32_t)c);
+    p0 = (c - n * a.cpi) * KB;
+    const int p = p0 + vi * VE;
+    keep = a.PX - p;
+    const int q = RAG ? p : min(p, a.PX - VE);
+    if constexpr (RAG) off = 0;
+#pragma unroll
+    for (int i = 0; i < RV; ++i) {
+      const bool g = i < MT;
+      if (!g && !want_w) break;   // (uniform)
+      int o = (g ? n * a.Co + min(row0 + 32 * i, a.Co - 1) : n * a.Ci + min(row0 + 32 * (i - MT), a.Ci - 1)) * a.PX + q;
+      if constexpr (RAG) {
+        const int hi = (g ? a.tot_gy : a.tot_x) - VE;
+        off |= o > hi;
+        o = min(o, hi);
+      }
+      v[i] = load16<float, RAG>((g ? a.gy : a.x) + o);
+    }
+  };
+  auto stage = [&](auto neg) __attribute__((always_inline)) {
+    const u32x4_t m = keep_mask<float>(RAG ? keep : keep > 0 ? VE : 0);
+#pragma unroll
+    for (int i = 0; i < RV; ++i) {
+      const bool g = i < MT;
+      if (!g && !want_w) break;
+      const int c = row0 + 32 * (g ? i : i - MT);
+      if (8 * wave + 32 * (g ? i : i - MT) >= (g ? a.Co : a.Ci)) continue;   // (uniform for the wave)
+      if constexpr (RAG) {
+        if (off) {   // the vector at the very end of a tensor
+          const int cc = min(c, (g ? a.Co : a.Ci) - 1), hi = (g ? a.tot_gy : a.tot_x) - VE;
+          v[i] = shifted<float>(v[i], max(0, (n * (g ? a.Co : a.Ci) + cc) * a.PX + p0 + vi * VE - hi));
+        }
+      }
+      if (c >= (g ? a.Co : a.Ci)) continue;
+      const u32x4_t u = v[i] & m;
+      unsigned char* d = smem + (row0 + 32 * i) * L::RW;
+      uint2 t[3];
+      if (g) split3<decltype(neg)::value>(u, t, low);
+      else split3<false>(u, t, low);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) *reinterpret_cast<uint2*>(d + k * L::kTerm + vi * 8) = t[k];
+    }
+  };
+  // rows of channels that do not exist: zeros, once
+  for (int i = tid; i < 3 * L::ROWS * 8; i += kT) {
+    const int row = i / 8 % L::ROWS, c = row < 32 * MT ? row : row - 32 * MT;
+    if (c < (row < 32 * MT ? a.Co : a.Ci)) continue;
+    *reinterpret_cast<uint2*>(smem + i / 8 / L::ROWS * L::kTerm + row * L::RW + i % 8 * 8) = make_uint2(0, 0);
+  }
+  if (c0 < c1) fetch(c0);
+
+  // The kernel's fragments: lane holds c_i = lane % 32, c_o = 16 ks + 8 (lane / 32) .. + 7.  Where the waves share K, every
+  // other one takes -w and is subtracted (the lean of the instruction's sums cancels, see mul_all).
+  const int back = 3 - wave;   // the order of the waves here: wave 0 has a weight-gradient tile more
+  uint4 fw[L::DT][L::KW][3];
+#pragma unroll
+  for (int i = 0; i < L::DT; ++i)
+#pragma unroll
+    for (int k = 0; k < L::KW; ++k) {
+      const int ci = (L::EXPAND ? 0 : back + 4 * i) * 32 + r, co = (L::EXPAND ? back + 4 * k : k) * 16 + 8 * kg;
+      __attribute__((aligned(16))) float e[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float val = want_d ? a.w[min(co + j, a.Co - 1) * a.Ci + min(ci, a.Ci - 1)] : 0.f;
+        e[j] = ci < a.Ci && co + j < a.Co ? (L::EXPAND && (back & 1) ? -val : val) : 0.f;
+      }
+      uint2 t0[3], t1[3];
+      split3<false>(reinterpret_cast<const u32x4_t*>(e)[0], t0, low);
+      split3<false>(reinterpret_cast<const u32x4_t*>(e)[1], t1, low);
+#pragma unroll
+      for (int t = 0; t < 3; ++t) fw[i][k][t] = make_uint4(t0[t].x, t0[t].y, t1[t].x, t1[t].y);
+    }
+
+  f32x16 acc[1][L::WT];
+  zero_acc(acc);
+  auto terms = [&](const uint4 (&fa)[3], const uint4 (&fb)[3], f32x16 s) __attribute__((always_inline)) {   // smallest products first
+    s = mma32(fa[2], fb[0], s);
+    s = mma32(fa[0], fb[2], s);
+    s = mma32(fa[1], fb[1], s);
+    s = mma32(fa[1], fb[0], s);
+    s = mma32(fa[0], fb[1], s);
+    return mma32(fa[0], fb[0], s);
+  };
+  auto wgrad = [&](auto neg) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < L::WT; ++i) {
+      const int q = wave + 4 * i;
+      if (q >= wtiles) break;   // (uniform for the wave)
+      const int ra = L::EXPAND ? 32 * q : 0, rb = 32 * MT + (L::EXPAND ? 0 : 32 * q);
+      f32x16 s;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) s[e] = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        uint4 fa[3], fb[3];
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+          fa[t] = *reinterpret_cast<const uint4*>(smem + t * L::kTerm + (ra + r) * L::RW + ks * 32 + kg * 16);
+          fb[t] = *reinterpret_cast<const uint4*>(smem + t * L::kTerm + (rb + r) * L::RW + ks * 32 + kg * 16);
+        }
+        s = terms(fa, fb, s);
+      }
+      if (decltype(neg)::value) acc[0][i] -= s;
+      else acc[0][i] += s;
+      asm volatile("" : "+v"(acc[0][i]));
+    }
+  };
+  // 16 c_o x 32 pixels of gy, transposed on the way
+  auto frag_gy = [&](uint4 (&fb)[3], int ks) __attribute__((always_inline)) {
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      const unsigned char* p = smem + t * L::kTerm + (ks * 16 + 8 * kg + ((lane & 15) >> 2)) * L::RW + (lane & 16) * 2 + 8 * (lane & 3);
+      const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p));
+      const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * L::RW)));
+      fb[t] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+    }
+  };
+  // a finished vector of g_x: row ci from pixel p on
+  auto finish = [&](f32x4 f, int nn, int ci, int p, float sign) __attribute__((always_inline)) {
+    if (ci >= a.Ci || p >= a.PX) return;
+    float* d = a.gx + ((long)nn * a.Ci + ci) * a.PX + p;
+    f *= sign;
+    if (!RAG) {
+      store_stream16(d, __builtin_bit_cast(uint4, f));
+    } else if (p + VE <= a.PX) {
+      const uint4 q = __builtin_bit_cast(uint4, f);
+      *reinterpret_cast<Unal<float>*>(d) = Unal<float>{{q.x, q.y, q.z, q.w}};
+    } else {
+#pragma unroll
+      for (int e = 0; e < VE; ++e)
+        if (p + e < a.PX) d[e] = f[e];
+    }
+  };
+  auto step = [&](int c, auto neg) __attribute__((always_inline)) {
+    const int nn = n, pp = p0;
+    const float sign = decltype(neg)::value ? -1.f : 1.f;
+    stage(neg);
+    lds_barrier();
+    if (c + 1 < c1) fetch(c + 1);
+    if (want_w) wgrad(neg);
+    if constexpr (L::EXPAND) {
+      if (want_d) {
+        f32x16 s;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s[e] = 0.f;
+        // (uniform for the wave: steps past c_o; their rows may lie past the operands)
+        uint4 fb[L::KW][3];
+#pragma unroll
+        for (int k = 0; k < L::KW; ++k)
+          if (back + 4 * k < nks) frag_gy(fb[k], back + 4 * k);
+        auto all = [&](int ta, int tb) __attribute__((always_inline)) {
+#pragma unroll
+          for (int k = 0; k < L::KW; ++k)
+            if (back + 4 * k < nks) s = mma32(fw[0][k][ta], fb[k][tb], s);
+        };
+        all(2, 0); all(0, 2); all(1, 1); all(1, 0); all(0, 1); all(0, 0);   // smallest products first
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          bad = __builtin_fmaf(s[e], 0.f, bad);
+          sums[(wave * 32 + acc_row(lane, e)) * L::S + r] = s[e];
+        }
+      }
+      lds_barrier();
+      if (want_d) {
+        f32x4 f;
+        const float* src = sums + row0 * L::S + vi * VE;
+#pragma unroll
+        for (int e = 0; e < VE; ++e)   // waves 0 and 2 took -w
+          f[e] = (src[3 * 32 * L::S + e] - src[2 * 32 * L::S + e]) + (src[32 * L::S + e] - src[e]);
+        finish(f, nn, row0, pp + vi * VE, sign);
+      }
+    } else {
+      if (want_d) {
+#pragma unroll
+        for (int i = 0; i < L::DT; ++i) {
+          const int tile = back + 4 * i;
+          if (tile >= wtiles) break;   // (uniform for the wave)
+          f32x16 s;
+#pragma unroll
+          for (int e = 0; e < 16; ++e) s[e] = 0.f;
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            if (k >= nks) break;
+            uint4 fb[3];
+            frag_gy(fb, k);
+            s = terms(fw[i][k], fb, s);
+          }
+          float* cs = sums + wave * 32 * L::S;   // (this wave's own: no barrier)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            bad = __builtin_fmaf(s[e], 0.f, bad);
+            cs[acc_row(lane, e) * L::S + r] = s[e];
+          }
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+          constexpr int PV = 32 / VE;   // vectors of a row of the tile
+#pragma unroll
+          for (int h = 0; h < 32 * PV / 64; ++h) {
+            const int row = (lane + 64 * h) / PV, col = (lane + 64 * h) % PV * VE;
+            f32x4 f;
+#pragma unroll
+            for (int e = 0; e < VE; ++e) f[e] = cs[row * L::S + col + e];
+            finish(f, nn, tile * 32 + row, pp + col, sign);
+          }
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+        }
+      }
+      lds_barrier();
+    }
+  };
+  int c = c0;   // odd runs of the whole layer are multiplied with the sign changed (see mul_all)
+  if (c & 1) step(c++, std::true_type());
+  for (; c + 2 <= c1; c += 2) {
+    step(c, std::false_type());
+    step(c + 1, std::true_type());
+  }
+  if (c < c1) step(c, std::false_type());
+
+  const bool failed = split_failed(acc, low);
+  if (__syncthreads_or(failed || bad != 0.f)) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the stores of g_x so far, of every wave, before the second ones
+    __syncthreads();
+    pixels_again(a, c0, c1);
+    return;
+  }
+  if (want_w) {
+    float* d = a.part + (long)blockIdx.x * a.Co * a.Ci;
+#pragma unroll
+    for (int i = 0; i < L::WT; ++i) {
+      const int q = wave + 4 * i;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int co = (L::EXPAND ? 32 * q : 0) + acc_row(lane, e), ci = (L::EXPAND ? 0 : 32 * q) + r;
+        if (co < a.Co && ci < a.Ci) d[co * a.Ci + ci] = acc[0][i][e];
+      }
+    }
+  }
+}
+
+// g_w = sum of the slabs, in 64 bits: 512 of them, added in 32, would round as often as the runs themselves.
+// 16 values per block, 16 lanes per value with their loads in flight together.
+__global__ __launch_bounds__(kT) void pixel_slabs_k(const float* part, float* g_w, int pairs, int nz) {
+  __shared__ double red[16][17];
+  const int o = threadIdx.x & 15, zg = threadIdx.x >> 4, e = blockIdx.x * 16 + o;
+  double s = 0.;
+  if (e < pairs) {
+    for (int z = zg; z < nz; z += 8 * 16) {
+      float v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = part[(long)min(z + 16 * k, nz - 1) * pairs + e];   // clamped: always issued
+#pragma unroll
+      for (int k = 0; k < 8; ++k) s += z + 16 * k < nz ? (double)v[k] : 0.;
+    }
+  }
+  red[zg][o] = s;
+  __syncthreads();
+  if (zg == 0 && e < pairs) {
+    double t = 0.;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) t += red[k][o];
+    g_w[e] = (float)t;
+  }
+}
+
+struct PixPlan { int cpi, chunks, cpb, blocks; };
+
+// two blocks per CU (LDS); 256, 640, 768 and 1024 blocks: 37, 40, 38 and 37 us where 512 take 31 (24 -> 144, 56 x 56, n = 32)
+PixPlan make_plan(const Geom& g) {
+  PixPlan p;
+  p.cpi = cdiv(g.P, KB);
+  p.chunks = g.N * p.cpi;
+  p.cpb = cdiv(p.chunks, 512);
+  p.blocks = cdiv(p.chunks, p.cpb);
+  return p;
+}
+
+template <int MT, int NC>
+void launch_tile(const PixArgs& a, int blocks, bool rag, hipStream_t st) {
+  if (rag) GF_LAUNCH((pointwise_k<MT, NC, true>), dim3(blocks), dim3(kT), 0, st, a);
+  else GF_LAUNCH((pointwise_k<MT, NC, false>), dim3(blocks), dim3(kT), 0, st, a);
+}
+
+}  // namespace
+
+// Layers the pass above takes: fp32, at most 32 channels on one side and 33 to 192 on the other, and enough pixels for a
+// few runs per block.  g: the layer with its pixels as P, sizes as gemm_maps_ok wants them.  Both gradients, us,
+// dense_gemm_k / one pass:
+//   24 -> 144, 56 x 56, n = 32 53 / 31, n = 16 (1568 runs) 32.5 / 22.8; 144 -> 24 57 / 41, n = 16 34.1 / 29.3; 3 -> 64,
+//   112 x 112, n = 16 44 / 29; 32 -> 192, 64 x 64, n = 24 57 / 41; 192 -> 32 62 / 53; 8 -> 72, 80 x 80, n = 16 38 / 24
+//   planes at any alignment: 24 -> 144, 57 x 55, n = 25 (2475 runs) 47 / 31, 144 -> 24 47 / 45; 96 -> 32, 39 x 41, n = 64 46 / 37
+// and on the other side
+//   24 -> 144, 28 x 28, n = 32 (800) 17.2 / 19.8; 144 -> 24 18.3 / 24.2; 96 -> 32, 39 x 41, n = 32 (1600) 25.2 / 27.4;
+//   32 -> 32, 80 x 80, n = 16 21.7 / 22.4; bf16, whose products need no split: 144 -> 24, 56 x 56, n = 32 27 / 31
+bool pointwise_ok(const Geom& g) {
+  const int mt = cdiv(g.Co, 32), nc = cdiv(g.Ci, 32);
+  if (g.dtype != GF_F32 || std::min(mt, nc) != 1 || std::max(mt, nc) < 2 || std::max(mt, nc) > 6) return false;
+  return make_plan(g).chunks >= (g.P % VE == 0 ? 1536 : 2048);
+}
+
+size_t ws_pointwise(const Geom& g, bool want_w) {
+  // (never 0: a caller that passes no workspace is told so)
+  return std::max<size_t>(want_w ? (size_t)make_plan(g).blocks * g.Co * g.Ci * sizeof(float) : 0, 256);
+}
+
+hipError_t launch_pointwise(const Geom& g, const void* gy, const void* x, const void* w, float* g_w, void* g_x, void* ws,
+                            hipStream_t st) {
+  const PixPlan p = make_plan(g);
+  PixArgs a = {};
+  a.N = g.N; a.Ci = g.Ci; a.Co = g.Co; a.PX = g.P;
+  a.cpi = p.cpi; a.chunks = p.chunks; a.cpb = p.cpb;
+  a.tot_gy = g.N * g.Co * g.P; a.tot_x = g.N * g.Ci * g.P;
+  a.gy = static_cast<const float*>(gy); a.x = static_cast<const float*>(x); a.w = static_cast<const float*>(w);
+  a.part = g_w ? static_cast<float*>(ws) : nullptr;
+  a.gx = static_cast<float*>(g_x);
+  a.d_cpi = FastDiv((uint32_t)p.cpi);
+  const bool rag = g.P % VE != 0;
+  const int mt = cdiv(g.Co, 32), nc = cdiv(g.Ci, 32);
+  if (mt > 5) launch_tile<6, 1>(a, p.blocks, rag, st);
+  else if (mt > 4) launch_tile<5, 1>(a, p.blocks, rag, st);
+  else if (mt > 2) launch_tile<4, 1>(a, p.blocks, rag, st);
+  else if (mt > 1) launch_tile<2, 1>(a, p.blocks, rag, st);
+  else if (nc > 5) launch_tile<1, 6>(a, p.blocks, rag, st);
+  else if (nc > 4) launch_tile<1, 5>(a, p.blocks, rag, st);
+  else if (nc > 2) launch_tile<1, 4>(a, p.blocks, rag, st);
+  else launch_tile<1, 2>(a, p.blocks, rag, st);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !g_w) return e;
+  const int pairs = g.Co * g.Ci;
+  GF_LAUNCH(pixel_slabs_k, dim3(cdiv(pairs, 16)), dim3(kT), 0, st, a.part, g_w, pairs, p.blocks);
+  return hipGetLastError();
+}
+
+}  // namespace gf

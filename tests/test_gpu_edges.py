@@ -124,6 +124,36 @@ def test_vanilla_products(oracle, case, dtype):
         assert rel_err(a, r) <= TOL[dtype] and torch.equal(a, b)
 
 
+# N, C_in, C_out, H, W: fp32 pointwise layers of few channels on one side, one pass over the maps -- every tile, rows and runs
+# that are not full, planes at any alignment, the last vectors of a tensor -- and the edges of the rule
+PIXEL_CASES = [
+    (12, 24, 144, 64, 64),     # 1536 runs of 32 pixels: the fewest
+    (12, 24, 144, 64, 63),     # one run fewer per image: two products
+    (3, 32, 33, 128, 160),     # one channel more than a tile
+    (24, 3, 97, 47, 61),       # odd planes
+    (6, 31, 192, 104, 80),     # the most channels
+    (6, 31, 193, 104, 80),     # one more: two products
+    (2, 34, 32, 200, 130),     # and the other way round
+    (700, 128, 5, 9, 11),      # less than a vector in the last run of every image
+    (1, 160, 9, 223, 331),     # one image
+    (5, 161, 17, 100, 100),    # a run of 16 pixels at the end of an image
+    (1, 192, 1, 250, 200),     # one output channel
+]
+
+
+@pytest.mark.parametrize("case", PIXEL_CASES)
+def test_vanilla_pointwise_one_pass(oracle, case):
+    N, Ci, Co, H, W = case
+    test_vanilla_products(oracle, (N, Ci, Co, H, W, 1, 1, 0, 1), "f32")
+
+
+@pytest.mark.parametrize("kind", ["tiny", "large", "infinite"])
+@pytest.mark.parametrize("case", [(12, 24, 144, 64, 64), (24, 65, 31, 47, 61)])
+def test_vanilla_pointwise_of_extreme_values(oracle, case, kind):
+    N, Ci, Co, H, W = case
+    test_fp32_products_of_extreme_values(oracle, (N, Ci, Co, H, W, 1, 1, 0), kind)
+
+
 # N, C_in, C_out, H, W, K, stride, padding, dilation: bf16 layers whose operands are staged -- tiles and chunks of 64 channels
 # and pixels that are not full, phases, slabs of either product -- and the edges of the rule
 STAGED_CASES = [
