@@ -22,7 +22,7 @@ constexpr int KB = El<float>::KB, VE = El<float>::VE;   // pixels of a run, of a
 
 struct PixArgs {
   int N, Ci, Co, PX;
-  int cpi, chunks, cpb;       // runs of KB pixels per image, all, per block
+  int cpi, chunks;            // runs of KB pixels per image, all
   int tot_gy, tot_x;
   const float *gy, *x, *w;
   float* part;                // [block][Co][Ci]; null: no weight gradient
@@ -74,6 +74,13 @@ __device__ __forceinline__ void pixels_again(const PixArgs& a, int c0, int c1) {
     }
 }
 
+// one run's vectors of a lane
+template <int RV>
+struct PixSet {
+  u32x4_t v[RV];
+  int keep, n, p0, off;   // elements inside the plane, image, first pixel; off: a load had to be moved into its tensor
+};
+
 template <int MT, int NC, bool RAG>
 __global__ __launch_bounds__(kT, 2) void pointwise_k(PixArgs a) {
   using L = PixTile<MT, NC>;
@@ -82,21 +89,20 @@ __global__ __launch_bounds__(kT, 2) void pointwise_k(PixArgs a) {
   float* sums = reinterpret_cast<float*>(smem + L::kOp);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int vi = tid & 7, row0 = tid >> 3, r = lane & 31, kg = lane >> 5;
-  const int c0 = blockIdx.x * a.cpb, c1 = min(c0 + a.cpb, a.chunks);
+  const int c0 = (int)((long)blockIdx.x * a.chunks / gridDim.x), c1 = (int)((long)(blockIdx.x + 1) * a.chunks / gridDim.x);
   const bool want_w = a.part != nullptr, want_d = a.gx != nullptr;
   const int wtiles = L::EXPAND ? (a.Co + 31) >> 5 : (a.Ci + 31) >> 5, nks = (a.Co + 15) >> 4;
   uint32_t low = 0;
   float bad = 0.f;
 
-  u32x4_t v[RV];
-  int keep = 0, n = 0, p0 = 0, off = 0;
-  auto fetch = [&](int c) __attribute__((always_inline)) {
-    n = (int)a.d_cpi.div((uint32_t)c);
-    p0 = (c - n * a.cpi) * KB;
-    const int p = p0 + vi * VE;
-    keep = a.PX - p;
+  PixSet<RV> set;   // the next run, on its way
+  auto fetch = [&](PixSet<RV>& s, int c) __attribute__((always_inline)) {
+    const int n = s.n = (int)a.d_cpi.div((uint32_t)c);
+    s.p0 = (c - n * a.cpi) * KB;
+    const int p = s.p0 + vi * VE;
+    s.keep = a.PX - p;
     const int q = RAG ? p : min(p, a.PX - VE);
-    if constexpr (RAG) off = 0;
+    if constexpr (RAG) s.off = 0;
 #pragma unroll
     for (int i = 0; i < RV; ++i) {
       const bool g = i < MT;
@@ -104,14 +110,14 @@ __global__ __launch_bounds__(kT, 2) void pointwise_k(PixArgs a) {
       int o = (g ? n * a.Co + min(row0 + 32 * i, a.Co - 1) : n * a.Ci + min(row0 + 32 * (i - MT), a.Ci - 1)) * a.PX + q;
       if constexpr (RAG) {
         const int hi = (g ? a.tot_gy : a.tot_x) - VE;
-        off |= o > hi;
+        s.off |= o > hi;
         o = min(o, hi);
       }
-      v[i] = load16<float, RAG>((g ? a.gy : a.x) + o);
+      s.v[i] = load16<float, RAG>((g ? a.gy : a.x) + o);
     }
   };
-  auto stage = [&](auto neg) __attribute__((always_inline)) {
-    const u32x4_t m = keep_mask<float>(RAG ? keep : keep > 0 ? VE : 0);
+  auto stage = [&](PixSet<RV>& s, uint32_t flip) __attribute__((always_inline)) {
+    const u32x4_t m = keep_mask<float>(RAG ? s.keep : s.keep > 0 ? VE : 0);
 #pragma unroll
     for (int i = 0; i < RV; ++i) {
       const bool g = i < MT;
@@ -119,17 +125,17 @@ __global__ __launch_bounds__(kT, 2) void pointwise_k(PixArgs a) {
       const int c = row0 + 32 * (g ? i : i - MT);
       if (8 * wave + 32 * (g ? i : i - MT) >= (g ? a.Co : a.Ci)) continue;   // (uniform for the wave)
       if constexpr (RAG) {
-        if (off) {   // the vector at the very end of a tensor
+        if (s.off) {   // the vector at the very end of a tensor
           const int cc = min(c, (g ? a.Co : a.Ci) - 1), hi = (g ? a.tot_gy : a.tot_x) - VE;
-          v[i] = shifted<float>(v[i], max(0, (n * (g ? a.Co : a.Ci) + cc) * a.PX + p0 + vi * VE - hi));
+          s.v[i] = shifted<float>(s.v[i], max(0, (s.n * (g ? a.Co : a.Ci) + cc) * a.PX + s.p0 + vi * VE - hi));
         }
       }
       if (c >= (g ? a.Co : a.Ci)) continue;
-      const u32x4_t u = v[i] & m;
+      u32x4_t u = s.v[i] & m;
+      if (g) u ^= flip;
       unsigned char* d = smem + (row0 + 32 * i) * L::RW;
       uint2 t[3];
-      if (g) split3<decltype(neg)::value>(u, t, low);
-      else split3<false>(u, t, low);
+      split3<false>(u, t, low);
 #pragma unroll
       for (int k = 0; k < 3; ++k) *reinterpret_cast<uint2*>(d + k * L::kTerm + vi * 8) = t[k];
     }
@@ -140,7 +146,7 @@ __global__ __launch_bounds__(kT, 2) void pointwise_k(PixArgs a) {
     if (c < (row < 32 * MT ? a.Co : a.Ci)) continue;
     *reinterpret_cast<uint2*>(smem + i / 8 / L::ROWS * L::kTerm + row * L::RW + i % 8 * 8) = make_uint2(0, 0);
   }
-  if (c0 < c1) fetch(c0);
+  if (c0 < c1) fetch(set, c0);
 
   // The kernel's fragments: lane holds c_i = lane % 32, c_o = 16 ks + 8 (lane / 32) .. + 7.  Where the waves share K, every
   // other one takes -w and is subtracted (the lean of the instruction's sums cancels, see mul_all).
@@ -174,7 +180,7 @@ __global__ __launch_bounds__(kT, 2) void pointwise_k(PixArgs a) {
     s = mma32(fa[0], fb[1], s);
     return mma32(fa[0], fb[0], s);
   };
-  auto wgrad = [&](auto neg) __attribute__((always_inline)) {
+  auto wgrad = [&](float sign) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < L::WT; ++i) {
       const int q = wave + 4 * i;
@@ -193,9 +199,8 @@ __global__ __launch_bounds__(kT, 2) void pointwise_k(PixArgs a) {
         }
         s = terms(fa, fb, s);
       }
-      if (decltype(neg)::value) acc[0][i] -= s;
-      else acc[0][i] += s;
-      asm volatile("" : "+v"(acc[0][i]));
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[0][i][e] = __builtin_fmaf(s[e], sign, acc[0][i][e]);
     }
   };
   // 16 c_o x 32 pixels of gy, transposed on the way
@@ -226,13 +231,17 @@ __global__ __launch_bounds__(kT, 2) void pointwise_k(PixArgs a) {
         if (p + e < a.PX) d[e] = f[e];
     }
   };
-  auto step = [&](int c, auto neg) __attribute__((always_inline)) {
-    const int nn = n, pp = p0;
-    const float sign = decltype(neg)::value ? -1.f : 1.f;
-    stage(neg);
+  // One copy of the step, with a sign that changes at run time: the code of a block that lives for six runs is fetched more
+  // often than it is repeated (13 KB; with copies for the two signs and for the ends, 24 - 31 KB, 144 -> 24 channels took 38 - 41 us instead of 36; a
+  // second run on its way in registers changed nothing).
+#pragma unroll 1
+  for (int c = c0; c < c1; ++c) {   // odd runs of the whole layer are multiplied with the sign changed (see mul_all)
+    const int nn = set.n, pp = set.p0;
+    const float sign = c & 1 ? -1.f : 1.f;
+    stage(set, (uint32_t)c << 31);
     lds_barrier();
-    if (c + 1 < c1) fetch(c + 1);
-    if (want_w) wgrad(neg);
+    if (c + 1 < c1) fetch(set, c + 1);
+    if (want_w) wgrad(sign);
     if constexpr (L::EXPAND) {
       if (want_d) {
         f32x16 s;
@@ -303,14 +312,7 @@ __global__ __launch_bounds__(kT, 2) void pointwise_k(PixArgs a) {
       }
       lds_barrier();
     }
-  };
-  int c = c0;   // odd runs of the whole layer are multiplied with the sign changed (see mul_all)
-  if (c & 1) step(c++, std::true_type());
-  for (; c + 2 <= c1; c += 2) {
-    step(c, std::false_type());
-    step(c + 1, std::true_type());
   }
-  if (c < c1) step(c, std::false_type());
 
   const bool failed = split_failed(acc, low);
   if (__syncthreads_or(failed || bad != 0.f)) {
@@ -358,15 +360,15 @@ __global__ __launch_bounds__(kT) void pixel_slabs_k(const float* part, float* g_
   }
 }
 
-struct PixPlan { int cpi, chunks, cpb, blocks; };
+struct PixPlan { int cpi, chunks, blocks; };
 
-// two blocks per CU (LDS); 256, 640, 768 and 1024 blocks: 37, 40, 38 and 37 us where 512 take 31 (24 -> 144, 56 x 56, n = 32)
+// two blocks per CU, what LDS holds; 384, 640, 768 and 1024 blocks: 35, 40, 41 and 40 us where 512 take 31 (24 -> 144, 56 x 56,
+// n = 32)
 PixPlan make_plan(const Geom& g) {
   PixPlan p;
   p.cpi = cdiv(g.P, KB);
   p.chunks = g.N * p.cpi;
-  p.cpb = cdiv(p.chunks, 512);
-  p.blocks = cdiv(p.chunks, p.cpb);
+  p.blocks = std::min(p.chunks, 512);
   return p;
 }
 
@@ -381,11 +383,11 @@ void launch_tile(const PixArgs& a, int blocks, bool rag, hipStream_t st) {
 // Layers the pass above takes: fp32, at most 32 channels on one side and 33 to 192 on the other, and enough pixels for a
 // few runs per block.  g: the layer with its pixels as P, sizes as gemm_maps_ok wants them.  Both gradients, us,
 // dense_gemm_k / one pass:
-//   24 -> 144, 56 x 56, n = 32 53 / 31, n = 16 (1568 runs) 32.5 / 22.8; 144 -> 24 57 / 41, n = 16 34.1 / 29.3; 3 -> 64,
-//   112 x 112, n = 16 44 / 29; 32 -> 192, 64 x 64, n = 24 57 / 41; 192 -> 32 62 / 53; 8 -> 72, 80 x 80, n = 16 38 / 24
-//   planes at any alignment: 24 -> 144, 57 x 55, n = 25 (2475 runs) 47 / 31, 144 -> 24 47 / 45; 96 -> 32, 39 x 41, n = 64 46 / 37
+//   24 -> 144, 56 x 56, n = 32 52 / 32, n = 16 (1568 runs) 31 / 23; 144 -> 24 55 / 36, n = 16 32 / 26; 3 -> 64, 112 x 112,
+//   n = 16 43 / 27; 32 -> 192, 64 x 64, n = 24 57 / 37; 192 -> 32 58 / 46; 8 -> 72, 80 x 80, n = 16 37 / 22
+//   planes at any alignment: 24 -> 144, 57 x 55, n = 25 (2475 runs) 45 / 30, 144 -> 24 47 / 39; 96 -> 32, 39 x 41, n = 64 43 / 35
 // and on the other side
-//   24 -> 144, 28 x 28, n = 32 (800) 17.2 / 19.8; 144 -> 24 18.3 / 24.2; 96 -> 32, 39 x 41, n = 32 (1600) 25.2 / 27.4;
+//   24 -> 144, 28 x 28, n = 32 (800) 17.0 / 20.5; 144 -> 24 18.0 / 21.4; 96 -> 32, 39 x 41, n = 32 (1600) 24.9 / 24.5;
 //   32 -> 32, 80 x 80, n = 16 21.7 / 22.4; bf16, whose products need no split: 144 -> 24, 56 x 56, n = 32 27 / 31
 bool pointwise_ok(const Geom& g) {
   const int mt = cdiv(g.Co, 32), nc = cdiv(g.Ci, 32);
@@ -403,7 +405,7 @@ hipError_t launch_pointwise(const Geom& g, const void* gy, const void* x, const 
   const PixPlan p = make_plan(g);
   PixArgs a = {};
   a.N = g.N; a.Ci = g.Ci; a.Co = g.Co; a.PX = g.P;
-  a.cpi = p.cpi; a.chunks = p.chunks; a.cpb = p.cpb;
+  a.cpi = p.cpi; a.chunks = p.chunks;
   a.tot_gy = g.N * g.Co * g.P; a.tot_x = g.N * g.Ci * g.P;
   a.gy = static_cast<const float*>(gy); a.x = static_cast<const float*>(x); a.w = static_cast<const float*>(w);
   a.part = g_w ? static_cast<float*>(ws) : nullptr;
