@@ -1,6 +1,6 @@
 // Vanilla back-propagation (Sec. 3.1) of depthwise layers: every (image, channel) plane is a
-// small 2-D problem of its own.  Undilated stride-1 layers, whose padded plane fits LDS, take one pass for both
-// gradients (dw_exact_onepass_k below).  The others: a block stages a run of whole planes in LDS with coalesced
+// small 2-D problem of its own.  Undilated layers of stride 1 or 2, whose padded plane fits LDS, take one pass for both
+// gradients (dw_exact_onepass_k and dw_exact_stride2_k below).  The others: a block stages a run of whole planes in LDS with coalesced
 // 16-byte loads (NCHW planes of consecutive channels are one contiguous stream) and all tap
 // arithmetic runs from LDS.  Both kernels move each tensor through HBM once.
 //   input gradient   g_x[h, w]  = sum_taps theta[c, u, v] * g_y[(h + p - u d) / s, (w + p - v d) / s]
@@ -406,24 +406,89 @@ struct DwBothArgs {
   float* part;   // [slabs][C][K * K]; null: g_theta not wanted
   int N, C, H, W, Hy, Wy, p, npb, ipp, blocks;
   int PH, PW;    // frame: H + K - 1 rows; columns: whole groups of kQ and the window of the last one
-  int groups;    // of kQ pixels per row
+  int hr, hc;    // g_y stands at that row and column of it
+  int groups;    // of kQ pixels per row (stride 2: of a pair of rows)
+  int rows;      // stride 2: pairs of rows
   FastDiv d_wy, d_grp, d_vec, d_tail, d_items, d_c;
 };
 
 template <class T> struct __attribute__((packed, aligned(sizeof(T)))) Quad { T v[kQ]; };
 
+// g_y of ni images of a channel into their frames
+template <class T>
+__device__ __forceinline__ void stage_frames(const DwBothArgs& a, const T* gy, int ni, float* fr, int tid) {
+  constexpr int VE = 16 / (int)sizeof(T);
+  const int HWy = a.Hy * a.Wy, FR = a.PH * a.PW, nvec = HWy / VE, ntail = HWy - nvec * VE;
+  const long cHWy = (long)a.C * HWy;
+  const bool whole = a.Wy % VE == 0;   // no vector runs over the end of a row
+  const int vecs = ni * nvec;
+  for (int v0 = tid; v0 < vecs; v0 += 4 * kThreads) {   // four loads of a lane in flight, clamped
+    uint4 rg[4];
+    int im[4], ve[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int v = min(v0 + k * kThreads, vecs - 1);
+      im[k] = (int)a.d_vec.div((uint32_t)v);
+      ve[k] = (v - im[k] * nvec) * VE;
+      rg[k] = load_vec<T>(gy + im[k] * cHWy + ve[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (v0 + k * kThreads >= vecs) continue;
+      const int row = (int)a.d_wy.div((uint32_t)ve[k]);
+      int col = ve[k] - row * a.Wy;
+      float* d = fr + im[k] * FR + (row + a.hr) * a.PW + col + a.hc;
+      const T* el = reinterpret_cast<const T*>(&rg[k]);
+      if (whole) {
+#pragma unroll
+        for (int i = 0; i < VE; ++i) d[i] = to_f32(el[i]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < VE; ++i) {
+          *d++ = to_f32(el[i]);
+          if (++col == a.Wy) { col = 0; d += a.PW - a.Wy; }
+        }
+      }
+    }
+  }
+  for (int t = tid; t < ni * ntail; t += kThreads) {   // the last elements of the planes
+    const int im = (int)a.d_tail.div((uint32_t)t), e = nvec * VE + t - im * ntail;
+    const int row = (int)a.d_wy.div((uint32_t)e), col = e - row * a.Wy;
+    fr[im * FR + (row + a.hr) * a.PW + col + a.hc] = to_f32(gy[im * cHWy + e]);
+  }
+}
+
+// the block's sums: slab z of channel c
+template <int K>
+__device__ __forceinline__ void put_taps(const DwBothArgs& a, float (&aw)[K * K], float (&red)[kThreads / 64][K * K], int z, int c) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+#pragma unroll
+  for (int t = 0; t < K * K; ++t)
+    for (int m = 32; m > 0; m >>= 1) aw[t] += __shfl_xor(aw[t], m, 64);
+  if (lane == 0) {
+#pragma unroll
+    for (int t = 0; t < K * K; ++t) red[wave][t] = aw[t];
+  }
+  __syncthreads();
+  if (tid < K * K) {
+    float sm = 0.f;
+    for (int k = 0; k < kThreads / 64; ++k) sm += red[k][tid];
+    a.part[((long)z * a.C + c) * (K * K) + tid] = sm;
+  }
+}
+
 template <class T, int K>
 __global__ __launch_bounds__(kThreads, K == 3 ? 7 : 3) void dw_exact_onepass_k(DwBothArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   __shared__ float red[kThreads / 64][K * K];
-  constexpr int VE = 16 / (int)sizeof(T), WN = (kQ + K - 1 + 3) / 4;   // window: WN 16-byte reads per row
+  constexpr int WN = (kQ + K - 1 + 3) / 4;   // window: WN 16-byte reads per row
   float* fr = reinterpret_cast<float*>(smem);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int idx = (int)(blockIdx.x & 7) * (gridDim.x >> 3) + (int)(blockIdx.x >> 3);
   if (idx >= a.blocks) return;   // (uniform)
   const int z = (int)a.d_c.div((uint32_t)idx), c = idx - z * a.C;
   const int n0 = z * a.npb, n1 = min(n0 + a.npb, a.N);
-  const int HW = a.H * a.W, HWy = a.Hy * a.Wy, halo = K - 1 - a.p, FR = a.PH * a.PW;   // (host: halo >= 0)
+  const int HW = a.H * a.W, HWy = a.Hy * a.Wy, FR = a.PH * a.PW;
   for (int i = tid; i < a.ipp * FR / 4; i += kThreads) reinterpret_cast<uint4*>(smem)[i] = make_uint4(0, 0, 0, 0);
   float wk[K * K], aw[K * K];
 #pragma unroll
@@ -431,8 +496,7 @@ __global__ __launch_bounds__(kThreads, K == 3 ? 7 : 3) void dw_exact_onepass_k(D
     wk[t] = a.gx ? to_f32(static_cast<const T*>(a.w)[c * (K * K) + t]) : 0.f;
     aw[t] = 0.f;
   }
-  const int items = a.H * a.groups, nvec = HWy / VE, ntail = HWy - nvec * VE;
-  const bool whole = a.Wy % VE == 0;   // no vector runs over the end of a row
+  const int items = a.H * a.groups;
   const long cHW = (long)a.C * HW, cHWy = (long)a.C * HWy;
   for (int n = n0; n < n1; n += a.ipp) {
     const int ni = min(a.ipp, n1 - n);
@@ -440,41 +504,7 @@ __global__ __launch_bounds__(kThreads, K == 3 ? 7 : 3) void dw_exact_onepass_k(D
     const T* x = static_cast<const T*>(a.x) + n * cHW + (long)c * HW;
     T* gx = static_cast<T*>(a.gx) + n * cHW + (long)c * HW;
     __syncthreads();   // the frames are cleared / the planes before have been read
-    const int vecs = ni * nvec;
-    for (int v0 = tid; v0 < vecs; v0 += 4 * kThreads) {   // four loads of a lane in flight, clamped
-      uint4 rg[4];
-      int im[4], ve[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int v = min(v0 + k * kThreads, vecs - 1);
-        im[k] = (int)a.d_vec.div((uint32_t)v);
-        ve[k] = (v - im[k] * nvec) * VE;
-        rg[k] = load_vec<T>(gy + im[k] * cHWy + ve[k]);
-      }
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        if (v0 + k * kThreads >= vecs) continue;
-        const int row = (int)a.d_wy.div((uint32_t)ve[k]);
-        int col = ve[k] - row * a.Wy;
-        float* d = fr + im[k] * FR + (row + halo) * a.PW + col + halo;
-        const T* el = reinterpret_cast<const T*>(&rg[k]);
-        if (whole) {
-#pragma unroll
-          for (int i = 0; i < VE; ++i) d[i] = to_f32(el[i]);
-        } else {
-#pragma unroll
-          for (int i = 0; i < VE; ++i) {
-            *d++ = to_f32(el[i]);
-            if (++col == a.Wy) { col = 0; d += a.PW - a.Wy; }
-          }
-        }
-      }
-    }
-    for (int t = tid; t < ni * ntail; t += kThreads) {   // the last elements of the planes
-      const int im = (int)a.d_tail.div((uint32_t)t), e = nvec * VE + t - im * ntail;
-      const int row = (int)a.d_wy.div((uint32_t)e), col = e - row * a.Wy;
-      fr[im * FR + (row + halo) * a.PW + col + halo] = to_f32(gy[im * cHWy + e]);
-    }
+    stage_frames<T>(a, gy, ni, fr, tid);
     __syncthreads();
     for (int g = tid; g < ni * items; g += kThreads) {
       const int im = (int)a.d_items.div((uint32_t)g), gr = g - im * items;
@@ -559,19 +589,159 @@ __global__ __launch_bounds__(kThreads, K == 3 ? 7 : 3) void dw_exact_onepass_k(D
       }
     }
   }
+  put_taps<K>(a, aw, red, z, c);
+}
+
+// The same for stride 2 (undilated).  With A = h + p, B = w + p, a pixel of x or g_x meets the taps of its parity,
+//   u = A mod 2 + 2 m, v = B mod 2 + 2 l,   at g_y[A / 2 - m, B / 2 - l],
+// so a lane owns two rows A = 2 a, 2 a + 1 of four columns B = 4 b ..: every tap is multiplied with every g_y pixel of a
+// window of (K + 1) / 2 rows and (K + 3) / 2 columns once per product, and nothing is divided or tested per tap.  In the two
+// launches above a tap costs divisions by the stride and a test, and the weight gradient a shuffle tree per plane.
+// Measured, both gradients, the two launches / one pass (us):
+//   fp32  576 channels, 14 x 14, n = 128 (130 MB): 201 / 69   96, 112 x 112, n = 32: 697 / 90   144, 56 x 56, n = 32: 101 / 48
+//         72, 56 x 56, 5 x 5 taps, n = 32: 96 / 37   576, 15 x 17, n = 8: 17.4 / 12.1   8, 200 x 200, n = 2: 55 / 37   16, 7 x 7, n = 1: 11.6 / 7.8
+//   bf16  138 / 46   150 / 68   89 / 32   98 / 33   18.2 / 12.1   63 / 35   11.7 / 9.2
+// Errors against 64-bit sums: g_theta 0.81 .. 1.04 of the former ones, g_x 0.82 .. 0.98 (fp32).  What is left of the time on
+// small maps goes into the pieces that lie partly outside a row, whose pixels move one by one.
+template <class T, int K>
+__global__ __launch_bounds__(kThreads, K == 3 ? 7 : 3) void dw_exact_stride2_k(DwBothArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  __shared__ float red[kThreads / 64][K * K];
+  constexpr int M = (K + 1) / 2;
+  float* fr = reinterpret_cast<float*>(smem);
+  const int tid = threadIdx.x;
+  const int idx = (int)(blockIdx.x & 7) * (gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+  if (idx >= a.blocks) return;   // (uniform)
+  const int z = (int)a.d_c.div((uint32_t)idx), c = idx - z * a.C;
+  const int n0 = z * a.npb, n1 = min(n0 + a.npb, a.N);
+  const int HW = a.H * a.W, HWy = a.Hy * a.Wy, FR = a.PH * a.PW;
+  for (int i = tid; i < a.ipp * FR / 4; i += kThreads) reinterpret_cast<uint4*>(smem)[i] = make_uint4(0, 0, 0, 0);
+  float wk[K * K], aw[K * K], wfin = 0.f;
 #pragma unroll
-  for (int t = 0; t < K * K; ++t)
-    for (int m = 32; m > 0; m >>= 1) aw[t] += __shfl_xor(aw[t], m, 64);
-  if (lane == 0) {
+  for (int t = 0; t < K * K; ++t) {
+    wk[t] = a.gx ? to_f32(static_cast<const T*>(a.w)[c * (K * K) + t]) : 0.f;
+    wfin = __builtin_fmaf(wk[t], 0.f, wfin);
+    aw[t] = 0.f;
+  }
+  const bool finite_w = wfin == 0.f;   // (uniform) else the frame's zeros would not be neutral in g_x
+  const int items = a.rows * a.groups;
+  const long cHW = (long)a.C * HW, cHWy = (long)a.C * HWy;
+  for (int n = n0; n < n1; n += a.ipp) {
+    const int ni = min(a.ipp, n1 - n);
+    const T* x = static_cast<const T*>(a.x) + n * cHW + (long)c * HW;
+    T* gx = static_cast<T*>(a.gx) + n * cHW + (long)c * HW;
+    __syncthreads();   // the frames are cleared / the planes before have been read
+    stage_frames<T>(a, static_cast<const T*>(a.gy) + n * cHWy + (long)c * HWy, ni, fr, tid);
+    __syncthreads();
+    for (int g = tid; g < ni * items; g += kThreads) {
+      const int im = (int)a.d_items.div((uint32_t)g), gr = g - im * items;
+      const int ar = (int)a.d_grp.div((uint32_t)gr), bc = gr - ar * a.groups;
+      // first pixel; the first row and up to three columns may lie before the map, the last ones past it
+      const int h0 = 2 * (ar + (a.p >> 1)) - a.p, w0 = 4 * (bc + (a.p >> 2)) - a.p;
+      const bool full = w0 >= 0 && w0 + kQ <= a.W;
+      Quad<T> xq[2] = {};
+      if (a.part) {
 #pragma unroll
-    for (int t = 0; t < K * K; ++t) red[wave][t] = aw[t];
+        for (int dr = 0; dr < 2; ++dr) {
+          const int h = h0 + dr;
+          if (h < 0 || h >= a.H) continue;
+          const T* xp = x + im * cHW + h * a.W + w0;
+          if (full) {
+            xq[dr] = *reinterpret_cast<const Quad<T>*>(xp);
+          } else {
+#pragma unroll
+            for (int e = 0; e < kQ; ++e)
+              if (w0 + e >= 0 && w0 + e < a.W) xq[dr].v[e] = xp[e];
+          }
+        }
+      }
+      float win[M][4];   // win[m'][l']: g_y[a - (M - 1) + m', 2 b - (M - 1) + l']
+      const float* src = fr + im * FR + ar * a.PW + 2 * bc;
+#pragma unroll
+      for (int m = 0; m < M; ++m)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const float2 q = *reinterpret_cast<const float2*>(src + m * a.PW + 2 * k);
+          win[m][2 * k] = q.x; win[m][2 * k + 1] = q.y;
+        }
+      if (a.part) {
+#pragma unroll
+        for (int u = 0; u < K; ++u)
+#pragma unroll
+          for (int v = 0; v < K; ++v)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+              aw[u * K + v] += to_f32(xq[u & 1].v[2 * j + (v & 1)]) * win[M - 1 - (u >> 1)][M - 1 - (v >> 1) + j];
+      }
+      if (a.gx) {
+        float acc[2][kQ];
+#pragma unroll
+        for (int e = 0; e < kQ; ++e) acc[0][e] = acc[1][e] = 0.f;
+        if (finite_w) {
+#pragma unroll
+          for (int u = 0; u < K; ++u)
+#pragma unroll
+            for (int v = 0; v < K; ++v)
+#pragma unroll
+              for (int j = 0; j < 2; ++j)
+                acc[u & 1][2 * j + (v & 1)] += wk[u * K + v] * win[M - 1 - (u >> 1)][M - 1 - (v >> 1) + j];
+        } else {
+          const int i0 = ar + (a.p >> 1), j0 = 2 * (bc + (a.p >> 2));
+#pragma unroll
+          for (int u = 0; u < K; ++u)
+#pragma unroll
+            for (int v = 0; v < K; ++v)
+#pragma unroll
+              for (int j = 0; j < 2; ++j) {
+                const int i = i0 - (u >> 1), jj = j0 + j - (v >> 1);
+                if (i >= 0 && i < a.Hy && jj >= 0 && jj < a.Wy)
+                  acc[u & 1][2 * j + (v & 1)] += wk[u * K + v] * win[M - 1 - (u >> 1)][M - 1 - (v >> 1) + j];
+              }
+        }
+#pragma unroll
+        for (int dr = 0; dr < 2; ++dr) {
+          const int h = h0 + dr;
+          if (h < 0 || h >= a.H) continue;
+          T* gp = gx + im * cHW + h * a.W + w0;
+          if (full) {
+            Quad<T> out;
+#pragma unroll
+            for (int e = 0; e < kQ; ++e) out.v[e] = from_f32<T>(acc[dr][e]);
+            *reinterpret_cast<Quad<T>*>(gp) = out;
+          } else {
+#pragma unroll
+            for (int e = 0; e < kQ; ++e)
+              if (w0 + e >= 0 && w0 + e < a.W) gp[e] = from_f32<T>(acc[dr][e]);
+          }
+        }
+      }
+    }
   }
-  __syncthreads();
-  if (tid < K * K) {
-    float sm = 0.f;
-    for (int k = 0; k < kThreads / 64; ++k) sm += red[k][tid];
-    a.part[((long)z * a.C + c) * (K * K) + tid] = sm;
+  if (!a.part) return;
+  // (as above: sums that are not finite are formed again from what lies inside the map)
+  float fin = 0.f;
+#pragma unroll
+  for (int t = 0; t < K * K; ++t) fin = __builtin_fmaf(aw[t], 0.f, fin);
+  if (__syncthreads_or(fin != 0.f)) {
+#pragma unroll
+    for (int t = 0; t < K * K; ++t) aw[t] = 0.f;
+    for (int n = n0; n < n1; ++n) {
+      const T* gy = static_cast<const T*>(a.gy) + n * cHWy + (long)c * HWy;
+      const T* x = static_cast<const T*>(a.x) + n * cHW + (long)c * HW;
+      for (int e = tid; e < HWy; e += kThreads) {
+        const int i = e / a.Wy, j = e - i * a.Wy;
+        const float gv = to_f32(gy[e]);
+#pragma unroll
+        for (int u = 0; u < K; ++u)
+#pragma unroll
+          for (int v = 0; v < K; ++v) {
+            const int h = 2 * i - a.p + u, w = 2 * j - a.p + v;
+            if (h >= 0 && h < a.H && w >= 0 && w < a.W) aw[u * K + v] += to_f32(x[h * a.W + w]) * gv;
+          }
+      }
+    }
   }
+  put_taps<K>(a, aw, red, z, c);
 }
 
 bool shape_ok(const Geom& g) {
@@ -706,17 +876,45 @@ hipError_t launch_dw_exact_wgrad(const Geom& g, const void* x, const void* g_y, 
   return launch_finalize(a.part, g_w, g.Ci * g.KK, g.N, 1, 1.f, st);
 }
 
-// One pass for both gradients (or either): stride 1, no dilation, padding below the kernel size, the frame of one plane in LDS.
-static size_t both_frame(const Geom& g, int* PH, int* PW) {
-  *PH = g.H + g.Kh - 1;
-  *PW = cdiv(g.W, kQ) * kQ + (g.Kh + 2) / 4 * 4;   // the window of the last group ends on a 16-byte boundary
-  return (size_t)*PH * *PW * sizeof(float);
+// One pass for both gradients (or either): stride 1 or 2, no dilation, padding below the kernel size, the frame of one plane in
+// LDS.  rows x groups: a lane's pieces of a plane.
+struct Frame { int PH, PW, hr, hc, rows, groups; size_t bytes; };
+static Frame both_frame(const Geom& g) {
+  Frame f;
+  if (g.s == 1) {
+    f.hr = f.hc = g.Kh - 1 - g.p;
+    f.rows = g.H;
+    f.groups = cdiv(g.W, kQ);
+    f.PH = g.H + g.Kh - 1;
+    f.PW = f.groups * kQ + (g.Kh + 2) / 4 * 4;   // the window of the last group ends on a 16-byte boundary
+  } else {
+    const int m = (g.Kh + 1) / 2, a0 = g.p >> 1, b0 = g.p >> 2;   // window rows; first pair of rows, group of columns
+    f.hr = m - 1 - a0;
+    f.hc = m - 1 - 2 * b0;
+    f.rows = ((g.H + g.p - 1) >> 1) - a0 + 1;
+    f.groups = ((g.W + g.p - 1) >> 2) - b0 + 1;
+    f.PH = (f.rows + m - 1 + 1) & ~1;            // (an even number: frames of 16 bytes each)
+    f.PW = 2 * f.groups + 2;                     // the last group's window of four
+  }
+  f.bytes = (size_t)f.PH * f.PW * sizeof(float);
+  return f;
 }
 
 bool dw_exact_onepass_ok(const Geom& g) {
-  int ph, pw;
-  if (g.g == 1 || !shape_ok(g) || (g.Kh != 3 && g.Kh != 5) || g.s != 1 || g.dl != 1 || g.p >= g.Kh) return false;
-  return both_frame(g, &ph, &pw) <= 60 * 1024 && (long)g.N * g.Ci < (1L << 30);
+  if (g.g == 1 || !shape_ok(g) || (g.Kh != 3 && g.Kh != 5) || g.s > 2 || g.dl != 1 || g.p >= g.Kh) return false;
+  return both_frame(g).bytes <= 60 * 1024 && (long)g.N * g.Ci < (1L << 30);
+}
+
+template <class T>
+static void launch_both(const DwBothArgs& a, int K, int s, size_t lds, hipStream_t st) {
+  const dim3 grid((a.blocks + 7) & ~7), block(kThreads);
+  if (s == 2) {
+    if (K == 3) GF_LAUNCH((dw_exact_stride2_k<T, 3>), grid, block, lds, st, a);
+    else GF_LAUNCH((dw_exact_stride2_k<T, 5>), grid, block, lds, st, a);
+  } else {
+    if (K == 3) GF_LAUNCH((dw_exact_onepass_k<T, 3>), grid, block, lds, st, a);
+    else GF_LAUNCH((dw_exact_onepass_k<T, 5>), grid, block, lds, st, a);
+  }
 }
 
 hipError_t launch_dw_exact_onepass(const Geom& g, const void* x, const void* w, const void* g_y, float* g_w, void* g_x,
@@ -724,17 +922,17 @@ hipError_t launch_dw_exact_onepass(const Geom& g, const void* x, const void* w, 
   DwBothArgs a = {};
   a.x = x; a.w = w; a.gy = g_y; a.gx = g_x; a.part = g_w ? static_cast<float*>(ws) : nullptr;
   a.N = g.N; a.C = g.Ci; a.H = g.H; a.W = g.W; a.Hy = g.Hy; a.Wy = g.Wy; a.p = g.p;
-  const size_t frame = both_frame(g, &a.PH, &a.PW);
-  a.groups = cdiv(g.W, kQ);
+  const Frame f = both_frame(g);
+  a.PH = f.PH; a.PW = f.PW; a.hr = f.hr; a.hc = f.hc; a.rows = f.rows; a.groups = f.groups;
   a.d_wy = FastDiv((uint32_t)g.Wy); a.d_grp = FastDiv((uint32_t)a.groups);
-  const int VE = 16 / g.b, HWy = g.Hy * g.Wy, items = g.H * a.groups;
+  const int VE = 16 / g.b, HWy = g.Hy * g.Wy, items = f.rows * f.groups;
   a.d_vec = FastDiv((uint32_t)std::max(HWy / VE, 1)); a.d_tail = FastDiv((uint32_t)std::max(HWy % VE, 1));
   a.d_items = FastDiv((uint32_t)items); a.d_c = FastDiv((uint32_t)g.Ci);
   // images at a time: about two groups of pixels per lane; images per block: what fills the last round of blocks best
   // (a block costs about a pass beside its passes; seven or three blocks per CU by registers)
-  a.ipp = std::max(1, std::min({g.N, 2 * kThreads / items, (int)(24 * 1024 / frame)}));
+  a.ipp = std::max(1, std::min({g.N, 2 * kThreads / items, (int)(24 * 1024 / f.bytes)}));
   a.ipp = cdiv(g.N, cdiv(g.N, a.ipp));
-  const size_t lds = frame * a.ipp;
+  const size_t lds = f.bytes * a.ipp;
   const long slots = 256L * std::min<long>(g.Kh == 5 ? 3 : 7, 160 * 1024 / (lds + 512));
   const int passes = cdiv(g.N, a.ipp);
   double best = 0;
@@ -746,14 +944,8 @@ hipError_t launch_dw_exact_onepass(const Geom& g, const void* x, const void* w, 
   a.npb = k * a.ipp;
   const int nz = cdiv(passes, k);
   a.blocks = nz * g.Ci;
-  const dim3 grid((a.blocks + 7) & ~7), block(kThreads);
-  if (g.dtype == GF_BF16) {
-    if (g.Kh == 3) GF_LAUNCH((dw_exact_onepass_k<bf16_t, 3>), grid, block, lds, st, a);
-    else GF_LAUNCH((dw_exact_onepass_k<bf16_t, 5>), grid, block, lds, st, a);
-  } else {
-    if (g.Kh == 3) GF_LAUNCH((dw_exact_onepass_k<float, 3>), grid, block, lds, st, a);
-    else GF_LAUNCH((dw_exact_onepass_k<float, 5>), grid, block, lds, st, a);
-  }
+  if (g.dtype == GF_BF16) launch_both<bf16_t>(a, g.Kh, g.s, lds, st);
+  else launch_both<float>(a, g.Kh, g.s, lds, st);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !g_w) return e;
   return launch_finalize(a.part, g_w, g.Ci * g.KK, nz, 1, 1.f, st);

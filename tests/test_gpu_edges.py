@@ -260,6 +260,52 @@ def test_vanilla_depthwise_one_pass(oracle, case, dtype):
             assert torch.equal(torch.isfinite(got.cpu()), torch.isfinite(torch.from_numpy(ref)))
 
 
+# N, C, H, W, K, padding: the same with stride 2 -- maps of either parity, first rows and columns before the map, last ones
+# past it, every padding, several images per block and planes at a time
+DW_STRIDE2_CASES = [
+    (3, 5, 20, 20, 3, 1),
+    (2, 3, 21, 23, 5, 2),
+    (3, 2, 14, 15, 3, 0),
+    (2, 4, 15, 18, 3, 2),
+    (2, 3, 17, 16, 5, 4),
+    (2, 3, 16, 19, 5, 3),
+    (2, 3, 12, 13, 5, 1),
+    (2, 3, 9, 10, 5, 0),
+    (3, 5, 1, 3, 3, 1),
+    (2, 2, 2, 1, 5, 2),
+    (37, 130, 14, 14, 3, 1),
+    (40, 160, 21, 20, 5, 2),
+    (2, 2, 200, 201, 3, 1),     # frame of 41 KB
+    (2, 2, 260, 260, 3, 1),     # a frame past the LDS budget: other kernels
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", DW_STRIDE2_CASES)
+def test_vanilla_depthwise_stride_2(oracle, case, dtype):
+    N, C, H, W, K, p = case
+    d = mk(N, C, C, H, W, K, 2, p, g=C, r=1, dtype=dtype)
+    sh = T.shapes(d)
+    x, w, gy = (randn(sh[k], i, dtype) for i, k in enumerate(("x", "w", "g_y"), 1))
+    g_w, g_x = T.conv_bwd_exact(d, x.cuda(), w.cuda(), gy.cuda())
+    o_w, _ = T.conv_bwd_exact(d, x.cuda(), None, gy.cuda(), want_gx=False)
+    _, o_x = T.conv_bwd_exact(d, None, w.cuda(), gy.cuda(), want_gw=False)
+    r_w, r_x = oracle.bwd_exact(odesc(oracle, d), to64(x), to64(w), to64(gy))
+    assert rel_err(g_w, r_w) <= TOL[dtype] and rel_err(g_x, r_x) <= TOL[dtype]
+    assert torch.equal(o_w, g_w) and torch.equal(o_x, g_x)
+    # an infinite activation, gradient or kernel value reaches what reads it and nothing else
+    Hy, Wy = sh["g_y"][2:]
+    for t, at in ((x, (0, 0, 0, 0)), (x, (N - 1, C - 1, H - 1, W - 1)), (gy, (0, 0, 0, Wy - 1)), (gy, (0, 0, Hy - 1, 0)),
+                  (w, (0, 0, 0, 0)), (w, (0, 0, K - 1, K - 1))):
+        kept = t[at].clone()
+        t[at] = float("inf")
+        g_w, g_x = T.conv_bwd_exact(d, x.cuda(), w.cuda(), gy.cuda())
+        r_w, r_x = oracle.bwd_exact(odesc(oracle, d), to64(x), to64(w), to64(gy))
+        for got, ref in ((g_w, r_w), (g_x, r_x)):
+            assert torch.equal(torch.isfinite(got.cpu()), torch.isfinite(torch.from_numpy(ref)))
+        t[at] = kept
+
+
 def check_codes(oracle, case, dtype, groups=1):
     """The one-call backward on codes against the oracle's integer contractions of the same codes, bit for bit."""
     N, Ci, Co, H, W, K, s, r = case
