@@ -598,11 +598,12 @@ __global__ __launch_bounds__(kThreads, K == 3 ? 7 : 3) void dw_exact_onepass_k(D
 // window of (K + 1) / 2 rows and (K + 3) / 2 columns once per product, and nothing is divided or tested per tap.  In the two
 // launches above a tap costs divisions by the stride and a test, and the weight gradient a shuffle tree per plane.
 // Measured, both gradients, the two launches / one pass (us):
-//   fp32  576 channels, 14 x 14, n = 128 (130 MB): 201 / 69   96, 112 x 112, n = 32: 697 / 90   144, 56 x 56, n = 32: 101 / 48
-//         72, 56 x 56, 5 x 5 taps, n = 32: 96 / 37   576, 15 x 17, n = 8: 17.4 / 12.1   8, 200 x 200, n = 2: 55 / 37   16, 7 x 7, n = 1: 11.6 / 7.8
-//   bf16  138 / 46   150 / 68   89 / 32   98 / 33   18.2 / 12.1   63 / 35   11.7 / 9.2
+//   fp32  576 channels, 14 x 14, n = 128 (130 MB): 201 / 66   96, 112 x 112, n = 32: 697 / 92   144, 56 x 56, n = 32: 101 / 47
+//         72, 56 x 56, 5 x 5 taps, n = 32: 96 / 30   576, 15 x 17, n = 8: 17.4 / 12.2   8, 200 x 200, n = 2: 55 / 36   16, 7 x 7, n = 1: 11.6 / 8.0
+//   bf16  138 / 42   150 / 60   89 / 31   98 / 30   18.2 / 11.2   63 / 33   11.7 / 7.9
 // Errors against 64-bit sums: g_theta 0.81 .. 1.04 of the former ones, g_x 0.82 .. 0.98 (fp32).  What is left of the time on
-// small maps goes into the pieces that lie partly outside a row, whose pixels move one by one.
+// small maps is the chain staging -> barrier -> x -> store that a block walks per group of images.  (x of the pieces at the
+// ends of a row element by element: bf16 46, 68, 31 and 33 us for the first four, fp32 69, 90, 48 and 37.)
 template <class T, int K>
 __global__ __launch_bounds__(kThreads, K == 3 ? 7 : 3) void dw_exact_stride2_k(DwBothArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -645,13 +646,19 @@ __global__ __launch_bounds__(kThreads, K == 3 ? 7 : 3) void dw_exact_stride2_k(D
         for (int dr = 0; dr < 2; ++dr) {
           const int h = h0 + dr;
           if (h < 0 || h >= a.H) continue;
-          const T* xp = x + im * cHW + h * a.W + w0;
-          if (full) {
-            xq[dr] = *reinterpret_cast<const Quad<T>*>(xp);
+          const T* xp = x + im * cHW + h * a.W;
+          if (a.W >= kQ) {   // (uniform) one load inside the row, shifted
+            const int wc = min(max(w0, 0), a.W - kQ), sh = w0 - wc;
+            const Quad<T> q = *reinterpret_cast<const Quad<T>*>(xp + wc);
+#pragma unroll
+            for (int e = 0; e < kQ; ++e)
+#pragma unroll
+              for (int f = 0; f < kQ; ++f)
+                if (e + sh == f) xq[dr].v[e] = q.v[f];
           } else {
 #pragma unroll
             for (int e = 0; e < kQ; ++e)
-              if (w0 + e >= 0 && w0 + e < a.W) xq[dr].v[e] = xp[e];
+              if (w0 + e >= 0 && w0 + e < a.W) xq[dr].v[e] = xp[w0 + e];
           }
         }
       }
