@@ -85,6 +85,30 @@ def test_one_call_backward_within_the_static_scratch(lib):
         assert B.gf_workspace_bytes(d, B.GF_OP_BWD_FILTERED) <= B.GF_STATIC_SCRATCH_BYTES, d
 
 
+def test_slabs_of_code_sums_fit_int32(lib):
+    """127^2 n < 2^31 up to n = 133144: the workspace of a weight gradient on codes holds a partial result of every
+    C_out x C_in pair per 133000 products, however many tiles the layer has."""
+    rng = np.random.default_rng(0)
+    layers = [(128, 1280, 1280, 65, 65, 1, 2), (100, 1280, 1280, 128, 128, 1, 2), (64, 1280, 1280, 130, 130, 1, 2), (36, 1280, 1217, 126, 126, 1, 2)]
+    for _ in range(3000):
+        n, ci, co, h, w = (int(round(np.exp(rng.uniform(np.log(lo), np.log(hi))))) for lo, hi in ((1, 512), (16, 2048), (16, 2048), (16, 600), (16, 600)))
+        layers.append((n, ci, co, h, w, int(rng.choice([1, 3, 5])), int(rng.choice([2, 2, 3, 4]))))
+    checked = 0
+    for N, Ci, Co, H, W, K, r in layers:
+        d = B.ConvDesc(N=N, C_in=Ci, C_out=Co, H_in=H, W_in=W, K_h=K, K_w=K, pad=K // 2, r=r)
+        try:
+            _, _, Hp, Wp = B.gf_out_shape(d)
+            need = B.gf_workspace_bytes(d, B.GF_OP_BWD_WEIGHT_Q8)
+        except B.GfError as e:
+            assert e.status == B.GF_ERR_UNSUPPORTED   # too large a tensor
+            continue
+        slabs = -(-N * Hp * Wp // 133000)
+        if slabs > 1:
+            checked += 1
+            assert need >= slabs * Co * Ci * 4, d
+    assert checked > 100
+
+
 OK = dict(N=2, C_in=4, C_out=8, H_in=8, W_in=8, K_h=3, K_w=3, pad=1, r=2)
 FAKE = 0x1000  # non-null, 16-byte aligned; never dereferenced because validation fails first
 

@@ -345,6 +345,22 @@ def test_dense_products_on_codes(oracle, case, dtype):
     check_codes(oracle, case, dtype)
 
 
+@pytest.mark.parametrize("case", [
+    (36, 1280, 1217, 63, 63, 1),   # 400 tiles: one slab each, were it not for what an int32 sum holds
+    (60, 64, 64, 50, 50, 3),       # one 64 x 64 tile of many slabs, added in 64 bits
+])
+def test_code_sums_past_int32(case):
+    """Codes that are constant over a plane: every sum is N P times a product of two codes, past 2^31 for most pairs."""
+    N, Ci, Co, Hp, Wp, K = case
+    d = mk(N, Ci, Co, 2 * Hp, 2 * Wp, K, 1, K // 2, r=2)
+    g = torch.Generator().manual_seed(N)
+    a, b = (torch.randint(120, 128, (c,), generator=g) * (2 * torch.randint(0, 2, (c,), generator=g) - 1) for c in (Ci, Co))
+    x_q, gy_q = (v.to(torch.int8).cuda().view(1, -1, 1, 1).expand(N, -1, Hp, Wp).contiguous() for v in (a, b))
+    want = (N * Hp * Wp * torch.outer(b, a)).to(torch.float32) * np.float32(2.5e-4)
+    g_w = T.conv_bwd_weight_q8(d, x_q, gy_q, 2.5e-4).cpu()
+    assert torch.equal(g_w, want.view(Co, Ci, 1, 1).expand(-1, -1, K, K))
+
+
 # N, C_in, C_out, H, W, K, stride, r: weight gradients on 32 x 32 tiles -- their edges, chunks for one wave, for all four and
 # for a second round, slabs -- and the 64 x 64 tiles from the same rule's other side on
 SHORT_K_CASES = [
