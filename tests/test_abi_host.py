@@ -549,3 +549,15 @@ int main() {
     assert r.returncode == 0, r.stderr
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_inline_assembly_names_what_it_writes(lib):
+    """An asm statement that writes m0 lists it, so that the compiler keeps nothing of its own there across it."""
+    import glob
+    found = 0
+    for f in glob.glob(os.path.join(ROOT, "paper_2301_00330_amd", "csrc", "*")):
+        for m in re.finditer(r"asm volatile\((.*?)\);", open(f).read(), re.S):
+            if re.search(r"\bs_\w+ m0\b", m.group(1)):
+                found += 1
+                assert '"m0"' in m.group(1).rsplit(":", 1)[1], (f, m.group(1))
+    assert found
