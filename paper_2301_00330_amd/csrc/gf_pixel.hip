@@ -34,45 +34,16 @@ struct PixArgs {
 template <int MT, int NC>
 struct PixTile {
   static constexpr int RW = 64 + 16;                 // bytes of a row of a term: eight rows read together cover all banks
+  static constexpr int RAW_RW = 128 + 16;            // ... of the values as they are
   static constexpr int ROWS = 32 * (MT + NC), kTerm = ROWS * RW;
   static constexpr int S = 33;                       // element stride of the staged sums
+  static_assert(RAW_RW <= 3 * RW, "the second pass works in the same LDS");
   static constexpr int kOp = 3 * kTerm, kSum = 4 * 32 * S * 4;
   static constexpr bool EXPAND = MT > 1;             // the waves share K = c_o of the input gradient, else its tiles of c_i
   static constexpr int WT = (MT * NC + 3) / 4;       // weight-gradient tiles of a wave
   static constexpr int DT = EXPAND ? 1 : (NC + 3) / 4;            // input-gradient tiles of a wave
   static constexpr int KW = EXPAND ? (2 * MT + 3) / 4 : 2;        // its steps of 16 c_o
 };
-
-// The block's pixels again with fp32 multiplications, for operands that three bf16 terms do not hold (split_failed):
-// infinities, NaN, values past the largest bf16 or below 2^-110.
-__device__ __forceinline__ void pixels_again(const PixArgs& a, int c0, int c1) {
-  if (a.part)
-    for (int i = threadIdx.x; i < a.Co * a.Ci; i += kT) {
-      const int co = i / a.Ci, ci = i - co * a.Ci;
-      float s = 0.f;
-      for (int c = c0; c < c1; ++c) {
-        const int n = (int)a.d_cpi.div((uint32_t)c), p0 = (c - n * a.cpi) * KB;
-        const float *g = a.gy + ((long)n * a.Co + co) * a.PX, *h = a.x + ((long)n * a.Ci + ci) * a.PX;
-        float t = 0.f;
-#pragma unroll 1
-        for (int p = p0; p < min(p0 + KB, a.PX); ++p) t = __builtin_fmaf(g[p], h[p], t);
-        s += t;
-      }
-      a.part[(long)blockIdx.x * a.Co * a.Ci + i] = s;
-    }
-  if (a.gx)
-    for (int c = c0; c < c1; ++c) {
-      const int n = (int)a.d_cpi.div((uint32_t)c), p0 = (c - n * a.cpi) * KB;
-      for (int i = threadIdx.x; i < a.Ci * KB; i += kT) {
-        const int ci = i / KB, p = p0 + i % KB;
-        if (p >= a.PX) continue;
-        float s = 0.f;
-#pragma unroll 1
-        for (int co = 0; co < a.Co; ++co) s = __builtin_fmaf(a.w[co * a.Ci + ci], a.gy[((long)n * a.Co + co) * a.PX + p], s);
-        a.gx[((long)n * a.Ci + ci) * a.PX + p] = s;
-      }
-    }
-}
 
 // one run's vectors of a lane
 template <int RV>
@@ -81,19 +52,24 @@ struct PixSet {
   int keep, n, p0, off;   // elements inside the plane, image, first pixel; off: a load had to be moved into its tensor
 };
 
-template <int MT, int NC, bool RAG>
-__global__ __launch_bounds__(kT, 2) void pointwise_k(PixArgs a) {
+struct PixLow { uint32_t gy, x, w; };   // what the splits of the operands left (see split3)
+
+// Runs [c0, c1): acc = the block's share of the weight gradient, g_x written.  RAW: the values as they are and
+// v_mfma_f32_32x32x2_f32 -- the second pass of a block that met operands which three bf16 terms do not hold (split_failed):
+// infinities, NaN, values past the largest bf16 or below 2^-110.  It forms only the gradients that such an operand enters.
+// Both gradients with one value in 10^6 of g_y below 2^-110 / with none, us: 24 -> 144, 56 x 56, n = 32 50 / 33, 144 -> 24 55 / 41
+// (dense_gemm_k 69 and 64; a product per lane and step instead of matrix instructions 812 and 562); g_x alone 32 / 21 and
+// 30 / 20 (dense_gemm_k 28 and 28); one kernel value below 2^-110: 61 and 59 (66 and 49, a tile that has the value; 1175 and 1036).
+template <int MT, int NC, bool RAG, bool RAW>
+__device__ __forceinline__ void pixel_pass(const PixArgs& a, unsigned char* smem, int c0, int c1,
+                                           bool want_w, bool want_d, f32x16 (&acc)[1][PixTile<MT, NC>::WT], PixLow& low, float& bad) {
   using L = PixTile<MT, NC>;
-  constexpr int RV = MT + NC;   // vectors of a lane per run
-  __shared__ __attribute__((aligned(16))) unsigned char smem[L::kOp + L::kSum];
+  constexpr int RV = MT + NC;                  // vectors of a lane per run
+  constexpr int RW = RAW ? L::RAW_RW : L::RW;  // bytes of a row in LDS
   float* sums = reinterpret_cast<float*>(smem + L::kOp);
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = lane_id<typename std::conditional<RAW, raw_f32, float>::type>(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int vi = tid & 7, row0 = tid >> 3, r = lane & 31, kg = lane >> 5;
-  const int c0 = (int)((long)blockIdx.x * a.chunks / gridDim.x), c1 = (int)((long)(blockIdx.x + 1) * a.chunks / gridDim.x);
-  const bool want_w = a.part != nullptr, want_d = a.gx != nullptr;
   const int wtiles = L::EXPAND ? (a.Co + 31) >> 5 : (a.Ci + 31) >> 5, nks = (a.Co + 15) >> 4;
-  uint32_t low = 0;
-  float bad = 0.f;
 
   PixSet<RV> set;   // the next run, on its way
   auto fetch = [&](PixSet<RV>& s, int c) __attribute__((always_inline)) {
@@ -133,25 +109,31 @@ __global__ __launch_bounds__(kT, 2) void pointwise_k(PixArgs a) {
       if (c >= (g ? a.Co : a.Ci)) continue;
       u32x4_t u = s.v[i] & m;
       if (g) u ^= flip;
-      unsigned char* d = smem + (row0 + 32 * i) * L::RW;
-      uint2 t[3];
-      split3<false>(u, t, low);
+      unsigned char* d = smem + (row0 + 32 * i) * RW;
+      if constexpr (RAW) {
+        *reinterpret_cast<u32x4_t*>(d + vi * 16) = u;
+      } else {
+        uint2 t[3];
+        split3<false>(u, t, g ? low.gy : low.x);
 #pragma unroll
-      for (int k = 0; k < 3; ++k) *reinterpret_cast<uint2*>(d + k * L::kTerm + vi * 8) = t[k];
+        for (int k = 0; k < 3; ++k) *reinterpret_cast<uint2*>(d + k * L::kTerm + vi * 8) = t[k];
+      }
     }
   };
   // rows of channels that do not exist: zeros, once
-  for (int i = tid; i < 3 * L::ROWS * 8; i += kT) {
+  for (int i = tid; i < (RAW ? 1 : 3) * L::ROWS * 8; i += kT) {
     const int row = i / 8 % L::ROWS, c = row < 32 * MT ? row : row - 32 * MT;
     if (c < (row < 32 * MT ? a.Co : a.Ci)) continue;
-    *reinterpret_cast<uint2*>(smem + i / 8 / L::ROWS * L::kTerm + row * L::RW + i % 8 * 8) = make_uint2(0, 0);
+    if constexpr (RAW) *reinterpret_cast<uint4*>(smem + row * RW + i % 8 * 16) = make_uint4(0, 0, 0, 0);
+    else *reinterpret_cast<uint2*>(smem + i / 8 / L::ROWS * L::kTerm + row * RW + i % 8 * 8) = make_uint2(0, 0);
   }
   if (c0 < c1) fetch(set, c0);
 
   // The kernel's fragments: lane holds c_i = lane % 32, c_o = 16 ks + 8 (lane / 32) .. + 7.  Where the waves share K, every
   // other one takes -w and is subtracted (the lean of the instruction's sums cancels, see mul_all).
   const int back = 3 - wave;   // the order of the waves here: wave 0 has a weight-gradient tile more
-  uint4 fw[L::DT][L::KW][3];
+  constexpr int NF = RAW ? 2 : 3;   // vectors of a fragment: eight values, or their terms
+  uint4 fw[L::DT][L::KW][NF];
 #pragma unroll
   for (int i = 0; i < L::DT; ++i)
 #pragma unroll
@@ -163,15 +145,19 @@ __global__ __launch_bounds__(kT, 2) void pointwise_k(PixArgs a) {
         const float val = want_d ? a.w[min(co + j, a.Co - 1) * a.Ci + min(ci, a.Ci - 1)] : 0.f;
         e[j] = ci < a.Ci && co + j < a.Co ? (L::EXPAND && (back & 1) ? -val : val) : 0.f;
       }
-      uint2 t0[3], t1[3];
-      split3<false>(reinterpret_cast<const u32x4_t*>(e)[0], t0, low);
-      split3<false>(reinterpret_cast<const u32x4_t*>(e)[1], t1, low);
+      if constexpr (RAW) {
 #pragma unroll
-      for (int t = 0; t < 3; ++t) fw[i][k][t] = make_uint4(t0[t].x, t0[t].y, t1[t].x, t1[t].y);
+        for (int t = 0; t < 2; ++t) fw[i][k][t] = reinterpret_cast<const uint4*>(e)[t];
+      } else {
+        uint2 t0[3], t1[3];
+        split3<false>(reinterpret_cast<const u32x4_t*>(e)[0], t0, low.w);
+        split3<false>(reinterpret_cast<const u32x4_t*>(e)[1], t1, low.w);
+#pragma unroll
+        for (int t = 0; t < 3; ++t) fw[i][k][t] = make_uint4(t0[t].x, t0[t].y, t1[t].x, t1[t].y);
+      }
     }
 
-  f32x16 acc[1][L::WT];
-  zero_acc(acc);
+  if (want_w) zero_acc(acc);
   auto terms = [&](const uint4 (&fa)[3], const uint4 (&fb)[3], f32x16 s) __attribute__((always_inline)) {   // smallest products first
     s = mma32(fa[2], fb[0], s);
     s = mma32(fa[0], fb[2], s);
@@ -179,6 +165,9 @@ __global__ __launch_bounds__(kT, 2) void pointwise_k(PixArgs a) {
     s = mma32(fa[1], fb[0], s);
     s = mma32(fa[0], fb[1], s);
     return mma32(fa[0], fb[0], s);
+  };
+  auto mul_raw = [&](uint32_t x, uint32_t y, f32x16 s) __attribute__((always_inline)) {
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(x), __uint_as_float(y), s, 0, 0, 0);
   };
   auto wgrad = [&](float sign) __attribute__((always_inline)) {
 #pragma unroll
@@ -190,30 +179,53 @@ __global__ __launch_bounds__(kT, 2) void pointwise_k(PixArgs a) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) s[e] = 0.f;
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        uint4 fa[3], fb[3];
+      for (int ks = 0; ks < (RAW ? 4 : 2); ++ks) {
+        if constexpr (RAW) {
+          const u32x4_t fa = *reinterpret_cast<const u32x4_t*>(smem + (ra + r) * RW + ks * 32 + kg * 16);
+          const u32x4_t fb = *reinterpret_cast<const u32x4_t*>(smem + (rb + r) * RW + ks * 32 + kg * 16);
 #pragma unroll
-        for (int t = 0; t < 3; ++t) {
-          fa[t] = *reinterpret_cast<const uint4*>(smem + t * L::kTerm + (ra + r) * L::RW + ks * 32 + kg * 16);
-          fb[t] = *reinterpret_cast<const uint4*>(smem + t * L::kTerm + (rb + r) * L::RW + ks * 32 + kg * 16);
+          for (int e = 0; e < 4; ++e) s = mul_raw(fa[e], fb[e], s);
+        } else {
+          uint4 fa[3], fb[3];
+#pragma unroll
+          for (int t = 0; t < 3; ++t) {
+            fa[t] = *reinterpret_cast<const uint4*>(smem + t * L::kTerm + (ra + r) * RW + ks * 32 + kg * 16);
+            fb[t] = *reinterpret_cast<const uint4*>(smem + t * L::kTerm + (rb + r) * RW + ks * 32 + kg * 16);
+          }
+          s = terms(fa, fb, s);
         }
-        s = terms(fa, fb, s);
       }
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[0][i][e] = __builtin_fmaf(s[e], sign, acc[0][i][e]);
     }
   };
-  // 16 c_o x 32 pixels of gy, transposed on the way
-  auto frag_gy = [&](uint4 (&fb)[3], int ks) __attribute__((always_inline)) {
+  // 16 c_o x 32 pixels of gy, transposed on the way (as they are: lane = pixel, eight rows)
+  auto frag_gy = [&](uint4 (&fb)[NF], int ks) __attribute__((always_inline)) {
     typedef short s16x4 __attribute__((ext_vector_type(4)));
     typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 #pragma unroll
-    for (int t = 0; t < 3; ++t) {
-      const unsigned char* p = smem + t * L::kTerm + (ks * 16 + 8 * kg + ((lane & 15) >> 2)) * L::RW + (lane & 16) * 2 + 8 * (lane & 3);
-      const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p));
-      const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * L::RW)));
-      fb[t] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+    for (int t = 0; t < NF; ++t) {
+      if constexpr (RAW) {
+        const uint32_t* p = reinterpret_cast<const uint32_t*>(smem + (ks * 16 + 8 * kg + 4 * t) * RW) + r;
+        fb[t] = make_uint4(p[0], p[RW / 4], p[2 * RW / 4], p[3 * RW / 4]);
+      } else {
+        const unsigned char* p = smem + t * L::kTerm + (ks * 16 + 8 * kg + ((lane & 15) >> 2)) * RW + (lane & 16) * 2 + 8 * (lane & 3);
+        const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p));
+        const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * RW)));
+        fb[t] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+      }
     }
+  };
+  auto mul_frag = [&](const uint4 (&fa)[NF], const uint4 (&fb)[NF], f32x16 s) __attribute__((always_inline)) {
+    if constexpr (!RAW) return terms(fa, fb, s);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      s = mul_raw(fa[t].x, fb[t].x, s);
+      s = mul_raw(fa[t].y, fb[t].y, s);
+      s = mul_raw(fa[t].z, fb[t].z, s);
+      s = mul_raw(fa[t].w, fb[t].w, s);
+    }
+    return s;
   };
   // a finished vector of g_x: row ci from pixel p on
   auto finish = [&](f32x4 f, int nn, int ci, int p, float sign) __attribute__((always_inline)) {
@@ -248,16 +260,22 @@ __global__ __launch_bounds__(kT, 2) void pointwise_k(PixArgs a) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) s[e] = 0.f;
         // (uniform for the wave: steps past c_o; their rows may lie past the operands)
-        uint4 fb[L::KW][3];
+        uint4 fb[L::KW][NF];
 #pragma unroll
         for (int k = 0; k < L::KW; ++k)
           if (back + 4 * k < nks) frag_gy(fb[k], back + 4 * k);
-        auto all = [&](int ta, int tb) __attribute__((always_inline)) {
+        if constexpr (RAW) {
 #pragma unroll
           for (int k = 0; k < L::KW; ++k)
-            if (back + 4 * k < nks) s = mma32(fw[0][k][ta], fb[k][tb], s);
-        };
-        all(2, 0); all(0, 2); all(1, 1); all(1, 0); all(0, 1); all(0, 0);   // smallest products first
+            if (back + 4 * k < nks) s = mul_frag(fw[0][k], fb[k], s);
+        } else {
+          auto all = [&](int ta, int tb) __attribute__((always_inline)) {
+#pragma unroll
+            for (int k = 0; k < L::KW; ++k)
+              if (back + 4 * k < nks) s = mma32(fw[0][k][ta], fb[k][tb], s);
+          };
+          all(2, 0); all(0, 2); all(1, 1); all(1, 0); all(0, 1); all(0, 0);   // smallest products first
+        }
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           bad = __builtin_fmaf(s[e], 0.f, bad);
@@ -285,9 +303,9 @@ __global__ __launch_bounds__(kT, 2) void pointwise_k(PixArgs a) {
 #pragma unroll
           for (int k = 0; k < 2; ++k) {
             if (k >= nks) break;
-            uint4 fb[3];
+            uint4 fb[NF];
             frag_gy(fb, k);
-            s = terms(fw[i][k], fb, s);
+            s = mul_frag(fw[i][k], fb, s);
           }
           float* cs = sums + wave * 32 * L::S;   // (this wave's own: no barrier)
 #pragma unroll
@@ -313,15 +331,27 @@ __global__ __launch_bounds__(kT, 2) void pointwise_k(PixArgs a) {
       lds_barrier();
     }
   }
+}
 
-  const bool failed = split_failed(acc, low);
-  if (__syncthreads_or(failed || bad != 0.f)) {
+template <int MT, int NC, bool RAG>
+__global__ __launch_bounds__(kT, 2) void pointwise_k(PixArgs a) {
+  using L = PixTile<MT, NC>;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[L::kOp + L::kSum];
+  const int c0 = (int)((long)blockIdx.x * a.chunks / gridDim.x), c1 = (int)((long)(blockIdx.x + 1) * a.chunks / gridDim.x);
+  f32x16 acc[1][L::WT];
+  zero_acc(acc);
+  PixLow low = {0, 0, 0};
+  float bad = 0.f;
+  pixel_pass<MT, NC, RAG, false>(a, smem, c0, c1, a.part != nullptr, a.gx != nullptr, acc, low, bad);
+  const bool again_w = a.part && split_failed(acc, low.gy | low.x);   // (uniform)
+  const bool again_d = a.gx && __syncthreads_or(((low.gy | low.w) & 0xffffu) != 0 || bad != 0.f);
+  if (again_w || again_d) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the stores of g_x so far, of every wave, before the second ones
     __syncthreads();
-    pixels_again(a, c0, c1);
-    return;
+    pixel_pass<MT, NC, RAG, true>(a, smem, c0, c1, again_w, again_d, acc, low, bad);
   }
-  if (want_w) {
+  if (a.part) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = lane & 31;
     float* d = a.part + (long)blockIdx.x * a.Co * a.Ci;
 #pragma unroll
     for (int i = 0; i < L::WT; ++i) {

@@ -154,6 +154,50 @@ def test_vanilla_pointwise_of_extreme_values(oracle, case, kind):
     test_fp32_products_of_extreme_values(oracle, (N, Ci, Co, H, W, 1, 1, 0), kind)
 
 
+# N, C_in, C_out, H, W: every tile of the pass, for what three bf16 terms do not hold
+@pytest.mark.parametrize("kind", ["tiny", "large", "infinite", "x", "w"])
+@pytest.mark.parametrize("case", [(24, 9, 40, 47, 61), (24, 3, 97, 47, 61), (12, 24, 130, 64, 64), (24, 31, 192, 47, 61),
+                                  (24, 40, 20, 64, 64), (12, 100, 31, 64, 64), (12, 160, 17, 64, 64), (12, 192, 9, 64, 64)])
+def test_vanilla_pointwise_second_pass(oracle, case, kind):
+    N, Ci, Co, H, W = case
+    if kind in ("tiny", "large", "infinite"):
+        return test_fp32_products_of_extreme_values(oracle, (N, Ci, Co, H, W, 1, 1, 0), kind)
+    d = mk(N, Ci, Co, H, W, 1, 1, 0)   # one operand alone: one gradient is formed again, the other stays
+    sh = T.shapes(d)
+    x, w, gy = randn(sh["x"], 1, "f32"), randn(sh["w"], 2, "f32"), randn(sh["g_y"], 3, "f32")
+    first = T.conv_bwd_exact(d, x.cuda(), w.cuda(), gy.cuda())
+    {"x": x, "w": w}[kind].mul_(2.0 ** -121)
+    g_w, g_x = T.conv_bwd_exact(d, x.cuda(), w.cuda(), gy.cuda())
+    r_w, r_x = oracle.bwd_exact(odesc(oracle, d), to64(x), to64(w), to64(gy))
+    same_values(g_w, r_w, 1e-5), same_values(g_x, r_x, 1e-5)
+    assert torch.equal(*((g_x, first[1]) if kind == "x" else (g_w, first[0])))
+
+
+@pytest.mark.parametrize("Ci,Co", [(24, 144), (144, 24)])
+def test_vanilla_pointwise_second_pass_time(Ci, Co):
+    """Gradients that underflow are ordinary data: the second pass of every block costs a few passes, not dozens (with a
+    product per lane and step instead of matrix instructions: 25 - 35)."""
+    d = mk(32, Ci, Co, 56, 56, 1, 1, 0)
+    sh = T.shapes(d)
+    x, w, gy = (randn(sh[k], i, "f32").cuda() for i, k in enumerate(("x", "w", "g_y")))
+    tiny = gy.clone()
+    tiny.view(-1)[::997] = 1e-36
+    e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+
+    def least(g):
+        out = []
+        for _ in range(8):
+            e[0].record()
+            for _ in range(8):
+                T.conv_bwd_exact(d, x, w, g)
+            e[1].record()
+            torch.cuda.synchronize()
+            out.append(e[0].elapsed_time(e[1]))
+        return min(out)
+
+    assert least(tiny) <= 8 * least(gy)
+
+
 # N, C_in, C_out, H, W, K, stride, padding, dilation: bf16 layers whose operands are staged -- tiles and chunks of 64 channels
 # and pixels that are not full, phases, slabs of either product -- and the edges of the rule
 STAGED_CASES = [
