@@ -59,7 +59,7 @@ struct PixLow { uint32_t gy, x, w; };   // what the splits of the operands left 
 // infinities, NaN, values past the largest bf16 or below 2^-110.  It forms only the gradients that such an operand enters.
 // Both gradients with one value in 10^6 of g_y below 2^-110 / with none, us: 24 -> 144, 56 x 56, n = 32 50 / 33, 144 -> 24 55 / 41
 // (dense_gemm_k 69 and 64; a product per lane and step instead of matrix instructions 812 and 562); g_x alone 32 / 21 and
-// 30 / 20 (dense_gemm_k 28 and 28); one kernel value below 2^-110: 61 and 59 (66 and 49, a tile that has the value; 1175 and 1036).
+// 30 / 20 (dense_gemm_k 28 and 28); one kernel value below 2^-110: 50 and 59 (64 and 49, a tile that has the value; 1175 and 1036).
 template <int MT, int NC, bool RAG, bool RAW>
 __device__ __forceinline__ void pixel_pass(const PixArgs& a, unsigned char* smem, int c0, int c1,
                                            bool want_w, bool want_d, f32x16 (&acc)[1][PixTile<MT, NC>::WT], PixLow& low, float& bad) {
@@ -403,26 +403,41 @@ PixPlan make_plan(const Geom& g) {
 }
 
 template <int MT, int NC>
-void launch_tile(const PixArgs& a, int blocks, bool rag, hipStream_t st) {
-  if (rag) GF_LAUNCH((pointwise_k<MT, NC, true>), dim3(blocks), dim3(kT), 0, st, a);
-  else GF_LAUNCH((pointwise_k<MT, NC, false>), dim3(blocks), dim3(kT), 0, st, a);
+void launch_tile(const PixArgs& a, int blocks, hipStream_t st) {
+  if constexpr (MT > 1) {   // (planes of whole vectors otherwise: pointwise_ok)
+    if (a.PX % VE != 0) {
+      GF_LAUNCH((pointwise_k<MT, NC, true>), dim3(blocks), dim3(kT), 0, st, a);
+      return;
+    }
+  }
+  GF_LAUNCH((pointwise_k<MT, NC, false>), dim3(blocks), dim3(kT), 0, st, a);
 }
 
 }  // namespace
 
 // Layers the pass above takes: fp32, at most 32 channels on one side and 33 to 192 on the other, and enough pixels for a
-// few runs per block.  g: the layer with its pixels as P, sizes as gemm_maps_ok wants them.  Both gradients, us,
-// dense_gemm_k / one pass:
-//   24 -> 144, 56 x 56, n = 32 52 / 32, n = 16 (1568 runs) 31 / 23; 144 -> 24 55 / 36, n = 16 32 / 26; 3 -> 64, 112 x 112,
-//   n = 16 43 / 27; 32 -> 192, 64 x 64, n = 24 57 / 37; 192 -> 32 58 / 46; 8 -> 72, 80 x 80, n = 16 37 / 22
-//   planes at any alignment: 24 -> 144, 57 x 55, n = 25 (2475 runs) 45 / 30, 144 -> 24 47 / 39; 96 -> 32, 39 x 41, n = 64 43 / 35
+// few runs per block -- whichever gradients are asked for, so that each has the same bits alone and beside the other.  g: the
+// layer with its pixels as P, sizes as gemm_maps_ok wants them.  Both gradients, g_w alone, g_x alone in us, dense_gemm_k / one pass
+// (buffers rotating over 600 MB):
+//   24 -> 144, 56 x 56, n = 32 48 / 32, 40 / 25, 26 / 21; 3 -> 64, 112 x 112, n = 16 41 / 28, 37 / 22, 25 / 19; 32 -> 192, 64 x 64,
+//   n = 24 50 / 40, 40 / 30, 30 / 24; n = 12 (1536 runs) 30 / 27, 20 / 22, 18 / 14; 3 -> 40 17 / 12, 13 / 11, 7.8 / 7.0
+//   planes at any alignment: 24 -> 144, 57 x 55, n = 32 50 / 36, 43 / 27, 28 / 25; 3 -> 192, 47 x 49, n = 30 (2160 runs) 39 / 30, 34 / 25, 24 / 21
 // and on the other side
 //   24 -> 144, 28 x 28, n = 32 (800) 17.0 / 20.5; 144 -> 24 18.0 / 21.4; 96 -> 32, 39 x 41, n = 32 (1600) 24.9 / 24.5;
 //   32 -> 32, 80 x 80, n = 16 21.7 / 22.4; bf16, whose products need no split: 144 -> 24, 56 x 56, n = 32 27 / 31
+// Many channels on the input side: a run of g_x is 128 bytes of each row.  Where rows do not start on lines or half lines every
+// line is written in two pieces, 5 us apart, while 64 blocks of an XCD move more than its L2 holds: planes of 16 k pixels only.
+//   144 -> 24, 56 x 56, n = 32 47 / 40, 39 / 26, 27 / 19; 28 x 28, n = 128, 144 -> 16 49 / 43, 41 / 26, 28 / 21; 96 -> 32 41 / 33, 34 / 22, 21 / 16
+//   57 x 56 (3192 pixels), n = 32, 144 -> 24 49 / 59, 40 / 28, 28 / 37; 192 -> 16 52 / 74, 40 / 30, 31 / 49; 57 x 55 55 / 80 (192 -> 24)
+// Not with 161 or more of them for more than 16 outputs either, whose waves have two tiles and two steps of each: 192 -> 32,
+// 64 x 64, n = 12 30 / 35, 21 / 23, 15 / 15, n = 24 48 / 49, 40 / 31, 29 / 21; 28 x 28, n = 128 53 / 59; 192 -> 16, 64 x 64, n = 12 29 / 26,
+// 19 / 19, 15 / 13.  Up to 64 of them, which are a tile there as here, from twice the runs on: 40 -> 16, 64 x 64, n = 12 14.3 / 12.7,
+// 11.8 / 11.5, 6.4 / 7.3; 48 x 48, n = 22 14.9 / 13.8, 13.0 / 12.0, 7.1 / 8.1; 56 x 56, n = 32 (3136) 20 / 17, 17 / 15, 10.9 / 10.5.
 bool pointwise_ok(const Geom& g) {
   const int mt = cdiv(g.Co, 32), nc = cdiv(g.Ci, 32);
   if (g.dtype != GF_F32 || std::min(mt, nc) != 1 || std::max(mt, nc) < 2 || std::max(mt, nc) > 6) return false;
-  return make_plan(g).chunks >= (g.P % VE == 0 ? 1536 : 2048);
+  if (nc > 1 && (g.P % 16 != 0 || (nc > 5 && g.Co > 16))) return false;
+  return make_plan(g).chunks >= (nc == 2 ? 3072 : g.P % VE == 0 ? 1536 : 2048);
 }
 
 size_t ws_pointwise(const Geom& g, bool want_w) {
@@ -441,16 +456,15 @@ hipError_t launch_pointwise(const Geom& g, const void* gy, const void* x, const 
   a.part = g_w ? static_cast<float*>(ws) : nullptr;
   a.gx = static_cast<float*>(g_x);
   a.d_cpi = FastDiv((uint32_t)p.cpi);
-  const bool rag = g.P % VE != 0;
   const int mt = cdiv(g.Co, 32), nc = cdiv(g.Ci, 32);
-  if (mt > 5) launch_tile<6, 1>(a, p.blocks, rag, st);
-  else if (mt > 4) launch_tile<5, 1>(a, p.blocks, rag, st);
-  else if (mt > 2) launch_tile<4, 1>(a, p.blocks, rag, st);
-  else if (mt > 1) launch_tile<2, 1>(a, p.blocks, rag, st);
-  else if (nc > 5) launch_tile<1, 6>(a, p.blocks, rag, st);
-  else if (nc > 4) launch_tile<1, 5>(a, p.blocks, rag, st);
-  else if (nc > 2) launch_tile<1, 4>(a, p.blocks, rag, st);
-  else launch_tile<1, 2>(a, p.blocks, rag, st);
+  if (mt > 5) launch_tile<6, 1>(a, p.blocks, st);
+  else if (mt > 4) launch_tile<5, 1>(a, p.blocks, st);
+  else if (mt > 2) launch_tile<4, 1>(a, p.blocks, st);
+  else if (mt > 1) launch_tile<2, 1>(a, p.blocks, st);
+  else if (nc > 5) launch_tile<1, 6>(a, p.blocks, st);
+  else if (nc > 4) launch_tile<1, 5>(a, p.blocks, st);
+  else if (nc > 2) launch_tile<1, 4>(a, p.blocks, st);
+  else launch_tile<1, 2>(a, p.blocks, st);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || !g_w) return e;
   const int pairs = g.Co * g.Ci;

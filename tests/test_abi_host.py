@@ -109,6 +109,19 @@ def test_slabs_of_code_sums_fit_int32(lib):
     assert checked > 100
 
 
+@pytest.mark.parametrize("layer,taken", [
+    ((32, 24, 144, 57, 55), True), ((32, 144, 24, 56, 56), True), ((128, 144, 24, 28, 28), True),
+    ((32, 144, 24, 57, 56), False), ((32, 144, 24, 57, 55), False), ((32, 64, 24, 58, 58), False),   # rows of g_x that start inside a half line
+    ((24, 160, 32, 64, 64), True), ((24, 161, 16, 64, 64), True), ((24, 161, 17, 64, 64), False), ((24, 192, 32, 64, 64), False),
+    ((24, 64, 32, 64, 64), True), ((23, 64, 32, 64, 64), False), ((12, 65, 32, 64, 64), True), ((12, 24, 144, 64, 63), False),
+])
+def test_layers_of_the_pointwise_pass(lib, layer, taken):
+    """Vanilla pointwise layers of few channels: one pass over the maps, a slab of g_w per block of 512, or two products."""
+    N, Ci, Co, H, W = layer
+    d = B.ConvDesc(N=N, C_in=Ci, C_out=Co, H_in=H, W_in=W, K_h=1, K_w=1, r=1)
+    assert (B.gf_workspace_bytes(d, B.GF_OP_BWD_WEIGHT) == 512 * Co * Ci * 4) == taken
+
+
 OK = dict(N=2, C_in=4, C_out=8, H_in=8, W_in=8, K_h=3, K_w=3, pad=1, r=2)
 FAKE = 0x1000  # non-null, 16-byte aligned; never dereferenced because validation fails first
 

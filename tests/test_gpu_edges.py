@@ -141,6 +141,13 @@ PIXEL_CASES = [
 ]
 
 
+# ... of many input channels: every tile, half lines at the ends of rows, a last run of 16 pixels, and the edges of the rule
+PIXEL_CASES += [
+    (24, 33, 32, 64, 64), (24, 64, 1, 60, 60), (128, 65, 31, 28, 28), (25, 128, 8, 44, 44), (7, 129, 24, 100, 84), (12, 160, 32, 64, 64),
+    (24, 161, 16, 52, 52), (12, 192, 3, 64, 64), (24, 161, 17, 52, 52), (12, 64, 24, 64, 64), (25, 96, 24, 42, 46),
+]
+
+
 @pytest.mark.parametrize("case", PIXEL_CASES)
 def test_vanilla_pointwise_one_pass(oracle, case):
     N, Ci, Co, H, W = case
