@@ -429,7 +429,8 @@ gf_status gf_conv_bwd_weight(const gf_conv_desc* desc, const void* x_u, const vo
   if (rc) return rc;
   if (!x_u || !gy_u || !g_w) return GF_ERR_NULL;
   if (!aligned16(x_u) || !aligned16(gy_u) || !aligned16(g_w)) return GF_ERR_UNSUPPORTED;
-  rc = check_ws(ws_need(g, GF_OP_BWD_WEIGHT, false), ws, ws_bytes);
+  const size_t need = ws_need(g, GF_OP_BWD_WEIGHT, false);
+  rc = check_ws_or(need, g.r == 1 ? ws_exact_least(g, true, false) : need, ws, &ws_bytes);
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (g.r == 1) return dev(launch_exact(g, x_u, nullptr, gy_u, g_w, nullptr, ws, ws_bytes, st));
@@ -508,7 +509,7 @@ static gf_status filtered_body(const gf_conv_desc* desc, const void* g_y, const 
     rc = static_scratch(&ws);
     if (rc) return rc;
   }
-  rc = check_ws(need, ws, ws_bytes);
+  rc = check_ws_or(need, g.r == 1 ? ws_exact_least(filtered_exact_geom(g), true, true) : need, ws, &ws_bytes);
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* wsb = static_cast<char*>(ws);
@@ -610,7 +611,8 @@ static gf_status chained_body(const Geom& g, const void* gy_u, const void* x_u, 
                               size_t ws_bytes, void* stream) {
   gf_status rc;
   size_t off_i = 0;
-  rc = check_ws(ws_chained(g, &off_i), ws, ws_bytes);
+  const size_t need = ws_chained(g, &off_i);
+  rc = check_ws_or(need, g.r == 1 ? ws_exact_least(g, true, true) : need, ws, &ws_bytes);
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* wsb = static_cast<char*>(ws);

@@ -357,6 +357,27 @@ def test_vanilla_depthwise_stride_2(oracle, case, dtype):
         t[at] = kept
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", [(3, 2, 200, 203, 3, 1), (2, 2, 190, 185, 5, 0)])
+def test_vanilla_depthwise_stride_2_without_a_workspace(oracle, case, dtype):
+    """Planes too large for the kernels that stage x: every entry takes the call without a workspace as well."""
+    N, C, H, W, K, p = case
+    d = mk(N, C, C, H, W, K, 2, p, g=C, r=1, dtype=dtype)
+    sh = T.shapes(d)
+    x, w, gy = (randn(sh[k], i, dtype).cuda() for i, k in enumerate(("x", "w", "g_y"), 1))
+    r_w, r_x = oracle.bwd_exact(odesc(oracle, d), to64(x), to64(w), to64(gy))
+    st = torch.cuda.current_stream().cuda_stream
+    px, pw, pg = (B.ptr(t) for t in (x, w, gy))
+    for call in (lambda a, b: B.gf_conv_bwd_exact(d, px, pw, pg, a, b, 0, 0, st), lambda a, b: B.gf_conv_bwd_exact(d, px, pw, pg, a, 0, 0, 0, st),
+                 lambda a, b: B.gf_conv_bwd_weight(d, px, pg, a, 0, 0, st), lambda a, b: B.gf_conv_bwd_filtered(d, pg, px, pw, 0, a, b, 0, 0, st),
+                 lambda a, b: B.gf_conv_bwd_chained(d, pg, px, pw, a, b, False, 0, 0, 0, st)):
+        g_w, g_x = torch.zeros(sh["w"], device="cuda"), torch.zeros_like(x)
+        call(B.ptr(g_w), B.ptr(g_x))
+        torch.cuda.synchronize()
+        assert rel_err(g_w, r_w) <= TOL[dtype]
+        assert not g_x.any() or rel_err(g_x, r_x) <= TOL[dtype]
+
+
 def check_codes(oracle, case, dtype, groups=1):
     """The one-call backward on codes against the oracle's integer contractions of the same codes, bit for bit."""
     N, Ci, Co, H, W, K, s, r = case
