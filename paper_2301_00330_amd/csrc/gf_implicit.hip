@@ -524,9 +524,12 @@ __global__ __launch_bounds__(kT) void stage_k(StageArgs a) {
 
 // 16 bytes per lane from base + off to LDS, lane i to lds + 16 i (both uniform).  Behind the compiler's back: it would wait for
 // every such load at the next read of LDS; the loops below wait themselves.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"   // (m0 is reserved: the compiler sets it where an instruction needs it, and must do so again after this)
 __device__ __forceinline__ void dma16(const void* base, uint32_t off, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 __device__ __forceinline__ uint32_t lds_of(const unsigned char* p) {
   return (uint32_t)(size_t)(__attribute__((address_space(3))) const unsigned char*)p;
 }
