@@ -483,7 +483,7 @@ __global__ __launch_bounds__(kThreads, K == 3 ? 7 : 3) void dw_exact_onepass_k(D
   __shared__ float red[kThreads / 64][K * K];
   constexpr int WN = (kQ + K - 1 + 3) / 4;   // window: WN 16-byte reads per row
   float* fr = reinterpret_cast<float*>(smem);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x;
   const int idx = (int)(blockIdx.x & 7) * (gridDim.x >> 3) + (int)(blockIdx.x >> 3);
   if (idx >= a.blocks) return;   // (uniform)
   const int z = (int)a.d_c.div((uint32_t)idx), c = idx - z * a.C;
@@ -604,6 +604,10 @@ __global__ __launch_bounds__(kThreads, K == 3 ? 7 : 3) void dw_exact_onepass_k(D
 // Errors against 64-bit sums: g_theta 0.81 .. 1.04 of the former ones, g_x 0.82 .. 0.98 (fp32).  What is left of the time on
 // small maps is the chain staging -> barrier -> x -> store that a block walks per group of images.  (x of the pieces at the
 // ends of a row element by element: bf16 46, 68, 31 and 33 us for the first four, fp32 69, 90, 48 and 37.)
+// One gradient alone takes the same pass, so that it has the same bits as beside the other.  300 layers (16 - 576 channels, 7 x 7 -
+// 112 x 112, n = 1 - 64, both kernel sizes and types), two launches / one pass, in the mean: both gradients 2.5, g_w 1.46, g_x 2.2
+// times as fast.  Slower alone: g_w of few large planes, a block or less per CU, and where few blocks leave several slabs (bf16,
+// 16 channels, 112 x 112, n = 16 10.7 / 14.8; 96, n = 4 12.2 / 15.3; 16, 28 x 28, n = 16 5.4 / 7.7), g_x of the smallest calls (3.1 / 3.6).
 template <class T, int K>
 __global__ __launch_bounds__(kThreads, K == 3 ? 7 : 3) void dw_exact_stride2_k(DwBothArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -617,14 +621,14 @@ __global__ __launch_bounds__(kThreads, K == 3 ? 7 : 3) void dw_exact_stride2_k(D
   const int n0 = z * a.npb, n1 = min(n0 + a.npb, a.N);
   const int HW = a.H * a.W, HWy = a.Hy * a.Wy, FR = a.PH * a.PW;
   for (int i = tid; i < a.ipp * FR / 4; i += kThreads) reinterpret_cast<uint4*>(smem)[i] = make_uint4(0, 0, 0, 0);
-  float wk[K * K], aw[K * K], wfin = 0.f;
+  float wk[K * K], aw[K * K];
 #pragma unroll
   for (int t = 0; t < K * K; ++t) {
-    wk[t] = a.gx ? to_f32(static_cast<const T*>(a.w)[c * (K * K) + t]) : 0.f;
-    wfin = __builtin_fmaf(wk[t], 0.f, wfin);
+    if constexpr (sizeof(T) == 2) wk[t] = a.gx ? __uint_as_float(static_cast<const uint16_t*>(a.w)[c * (K * K) + t]) : 0.f;   // (the bits, so far)
+    else wk[t] = a.gx ? static_cast<const float*>(a.w)[c * (K * K) + t] : 0.f;
     aw[t] = 0.f;
   }
-  const bool finite_w = wfin == 0.f;   // (uniform) else the frame's zeros would not be neutral in g_x
+  bool finite_w = true;   // (uniform) else the frame's zeros would not be neutral in g_x
   const int items = a.rows * a.groups;
   const long cHW = (long)a.C * HW, cHWy = (long)a.C * HWy;
   for (int n = n0; n < n1; n += a.ipp) {
@@ -634,6 +638,15 @@ __global__ __launch_bounds__(kThreads, K == 3 ? 7 : 3) void dw_exact_stride2_k(D
     __syncthreads();   // the frames are cleared / the planes before have been read
     stage_frames<T>(a, static_cast<const T*>(a.gy) + n * cHWy + (long)c * HWy, ni, fr, tid);
     __syncthreads();
+    if (n == n0) {   // here, not ahead of the loop: the loads of g_y would wait for those of the kernel
+      float wfin = 0.f;
+#pragma unroll
+      for (int t = 0; t < K * K; ++t) {
+        if constexpr (sizeof(T) == 2) wk[t] = __uint_as_float(__float_as_uint(wk[t]) << 16);
+        wfin = __builtin_fmaf(wk[t], 0.f, wfin);
+      }
+      finite_w = wfin == 0.f;
+    }
     for (int g = tid; g < ni * items; g += kThreads) {
       const int im = (int)a.d_items.div((uint32_t)g), gr = g - im * items;
       const int ar = (int)a.d_grp.div((uint32_t)gr), bc = gr - ar * a.groups;
@@ -935,9 +948,10 @@ hipError_t launch_dw_exact_onepass(const Geom& g, const void* x, const void* w, 
   const int VE = 16 / g.b, HWy = g.Hy * g.Wy, items = f.rows * f.groups;
   a.d_vec = FastDiv((uint32_t)std::max(HWy / VE, 1)); a.d_tail = FastDiv((uint32_t)std::max(HWy % VE, 1));
   a.d_items = FastDiv((uint32_t)items); a.d_c = FastDiv((uint32_t)g.Ci);
-  // images at a time: about two groups of pixels per lane; images per block: what fills the last round of blocks best
+  // images at a time: about two groups of pixels per lane (g_x alone on a chip that is not full: one); images per block: what fills the last round of blocks best
   // (a block costs about a pass beside its passes; seven or three blocks per CU by registers)
-  a.ipp = std::max(1, std::min({g.N, 2 * kThreads / items, (int)(24 * 1024 / f.bytes)}));
+  const int per_lane = !g_w && (long)g.Ci * g.N * items <= 512L * kThreads ? 1 : 2;
+  a.ipp = std::max(1, std::min({g.N, per_lane * kThreads / items, (int)(24 * 1024 / f.bytes)}));
   a.ipp = cdiv(g.N, cdiv(g.N, a.ipp));
   const size_t lds = f.bytes * a.ipp;
   const long slots = 256L * std::min<long>(g.Kh == 5 ? 3 : 7, 160 * 1024 / (lds + 512));
@@ -951,10 +965,11 @@ hipError_t launch_dw_exact_onepass(const Geom& g, const void* x, const void* w, 
   a.npb = k * a.ipp;
   const int nz = cdiv(passes, k);
   a.blocks = nz * g.Ci;
+  if (g_w && nz == 1) a.part = g_w;   // one slab is the result: no launch to add slabs (2.8 us)
   if (g.dtype == GF_BF16) launch_both<bf16_t>(a, g.Kh, g.s, lds, st);
   else launch_both<float>(a, g.Kh, g.s, lds, st);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || !g_w) return e;
+  if (e != hipSuccess || !g_w || nz == 1) return e;
   return launch_finalize(a.part, g_w, g.Ci * g.KK, nz, 1, 1.f, st);
 }
 
