@@ -1233,6 +1233,7 @@ int slab_chunks(int nchunks, long z) {
 // Slabs dealt to the XCDs: also a number that is no multiple of eight while no XCD gets more than a tenth above its share (its
 // last round of block numbers is partly empty).  64 -> 64 channels, 200 x 200, n = 4, 87 slabs: both gradients 94 -> 69 us,
 // 120 x 160, n = 8 (86): 90 -> 65; 128 -> 128, 60 x 80, n = 8 (50): 59 -> 51.
+// 280 layers of all calls that split K (vanilla of both types, bf16 weight gradients of 6 GFLOP and more): 0.89 .. 1.28, mean 1.004.
 bool deal_slabs(int nz) { return 10 * (cdiv(nz, 8) * 8) <= 11 * nz; }
 XPlan make_plan(const Geom& g, bool want_gw, bool want_gx, bool staged) {
   const XGeo q = make_xgeo(g);
@@ -1326,7 +1327,10 @@ int interleave_planes(const Geom& g, const XGeo& q) {
 // element, maps past 64 MiB.  3 x 3, unstaged / staged in us: 128 -> 128, 60 x 80, n = 32 (79 MB) 81 / 86, n = 128 270 / 319;
 // 96 -> 96, 112 x 112, n = 128 629 / 783; 128 -> 256, 60 x 80, n = 128 552 / 594; but 128 -> 128, 28 x 28, n = 64 43.7 / 42.2,
 // 256 -> 256, 60 x 80, n = 128 1613 / 1210; 5 x 5, 128 -> 128, 56 x 56, n = 64 275 / 237.  With planes of whole vectors either
-// form returns the same weight gradient; with others all calls take the same one (57 x 81, n = 64, both gradients 274 / 269).
+// form returns the same weight gradient, with others K is cut into other chunks; there gf_conv_bwd_exact, gf_conv_bwd_weight and the
+// chained entry take the same form whichever gradients they are asked for (57 x 81, n = 64, both gradients 274 / 269).  The one-call entry, which
+// returns the same bits on the library's scratch, keeps the unstaged form where only that fits (256 -> 256, 57 x 57, n = 32: 37 MB,
+// staged 138), with any workspace: its g_w may then differ from theirs in the order of the sums, its g_x does not.
 bool staged_ok(const Geom& g, bool want_gx) {
   if (g.dtype != GF_BF16 || g.KK == 1 || g.KK > kTapsLds) return false;
   const XGeo q = make_xgeo(g);

@@ -243,6 +243,24 @@ def test_vanilla_staged_operands(oracle, case):
     same_values(g_w, r_w, TOL["bf16"]), same_values(g_x, r_x, TOL["bf16"])
 
 
+@pytest.mark.parametrize("H", [57, 56])
+def test_vanilla_one_call_entry_within_the_static_scratch(H):
+    """Layers whose staged operands do not fit the library's scratch: the one-call entry keeps the form that does, on its
+    own scratch and on a workspace.  g_x is gf_conv_bwd_exact's bit for bit; so is g_w on planes of whole vectors, on
+    others up to the order of the fp32 sums."""
+    d = mk(40, 256, 256, H, H, 3, 1, 1, 1, r=1, dtype="bf16")
+    assert B.gf_workspace_bytes(d, B.GF_OP_BWD_FILTERED) <= B.GF_STATIC_SCRATCH_BYTES < B.gf_workspace_bytes(d, B.GF_OP_BWD_EXACT)
+    sh = T.shapes(d)
+    x, w, gy = (randn(sh[k], i, "bf16").cuda() for i, k in enumerate(("x", "w", "g_y"), 1))
+    e_w, e_x = T.conv_bwd_exact(d, x, w, gy)
+    f_w, f_x, _ = T.conv_bwd_filtered(d, gy, x, w)
+    s_w, s_x = torch.empty_like(f_w), torch.empty_like(f_x)
+    B.gf_conv_bwd_filtered_static(d, B.ptr(gy), B.ptr(x), B.ptr(w), 0, B.ptr(s_w), B.ptr(s_x), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.equal(s_w, f_w) and torch.equal(s_x, f_x) and torch.equal(e_x, f_x)
+    assert torch.equal(e_w, f_w) if H * H % 8 == 0 else rel_err(e_w, to64(f_w)) <= 1e-5
+
+
 @pytest.mark.parametrize("case", [(38, 96, 128, 64, 64, 3, 1, 1, 1), (40, 128, 96, 63, 61, 3, 1, 1, 1)])
 def test_vanilla_weight_gradient_alone_on_a_large_map(oracle, case):
     """Past 64 MiB the weight gradient alone of such a layer reads the maps themselves: the bits of the call for both."""
