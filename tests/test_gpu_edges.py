@@ -473,6 +473,21 @@ def test_short_k_weight_gradient(oracle, case, dtype):
     check_codes(oracle, case, dtype)
 
 
+# N, C_in, C_out, H, W: fp32, slabs of 32 x 32 tiles with one chunk for each wave, one more, two for each, one more, two in all
+@pytest.mark.parametrize("case", [(76, 92, 10, 14, 14), (77, 92, 10, 14, 14), (64, 96, 160, 16, 16), (63, 70, 90, 12, 12), (1, 90, 70, 14, 14)])
+def test_short_k_sums_do_not_lean(case):
+    """The matrix instruction rounds its sums towards minus infinity; signs that change from wave to wave take that out: the mean
+    error of n independent sums is within 5 / sqrt(n) of their deviation (without: 25, 15 and 12 / sqrt(n) for
+    the first, the second and the last)."""
+    N, Ci, Co, H, W = case
+    d = mk(N, Ci, Co, H, W, 1, 1, 0, r=2)
+    sh = T.shapes(d)
+    x_u, gy, w = randn(sh["x_u"], 1, "f32").cuda(), randn(sh["g_y"], 2, "f32").cuda(), randn(sh["w"], 3, "f32").cuda()
+    g_w, _, gy_u = T.conv_bwd_filtered(d, gy, x_u, w)
+    err = g_w.view(Co, Ci).cpu().double() - torch.einsum("ncp,nkp->ck", gy_u.cpu().double().flatten(2), x_u.cpu().double().flatten(2))
+    assert abs(err.mean()) <= 5 * err.std() / err.numel() ** 0.5
+
+
 # N, C, H, W, stride, r: edges of the fused depthwise launches
 DW_CASES = [
     (1, 1, 2, 2, 1, 2),                # runs shorter than a vector
