@@ -599,8 +599,8 @@ __global__ __launch_bounds__(kThreads, K == 3 ? 7 : 3) void dw_exact_onepass_k(D
 // launches above a tap costs divisions by the stride and a test, and the weight gradient a shuffle tree per plane.
 // Measured, both gradients, the two launches / one pass (us):
 //   fp32  576 channels, 14 x 14, n = 128 (130 MB): 201 / 66   96, 112 x 112, n = 32: 697 / 92   144, 56 x 56, n = 32: 101 / 47
-//         72, 56 x 56, 5 x 5 taps, n = 32: 96 / 30   576, 15 x 17, n = 8: 17.4 / 12.2   8, 200 x 200, n = 2: 55 / 36   16, 7 x 7, n = 1: 11.6 / 8.0
-//   bf16  138 / 42   150 / 60   89 / 31   98 / 30   18.2 / 11.2   63 / 33   11.7 / 7.9
+//         72, 56 x 56, 5 x 5 taps, n = 32: 96 / 30   576, 15 x 17, n = 8: 17.4 / 12.2   8, 200 x 200, n = 2: 55 / 36   16, 7 x 7, n = 1: 10.2 / 6.2
+//   bf16  138 / 42   150 / 60   89 / 31   98 / 30   18.2 / 11.2   63 / 33   10.3 / 6.7
 // Errors against 64-bit sums: g_theta 0.81 .. 1.04 of the former ones, g_x 0.82 .. 0.98 (fp32).  What is left of the time on
 // small maps is the chain staging -> barrier -> x -> store that a block walks per group of images.  (x of the pieces at the
 // ends of a row element by element: bf16 46, 68, 31 and 33 us for the first four, fp32 69, 90, 48 and 37.)
