@@ -211,11 +211,13 @@ static gf_status check_ws(size_t need, const void* ws, size_t ws_bytes) {
 }
 
 // Paths that exist in two forms, with the workspace gf_workspace_bytes names and with `least` of it: a call that brings
-// only the latter is accepted (*ws_bytes then tells the launch which form to take).
-static gf_status check_ws_or(size_t need, size_t least, const void* ws, size_t* ws_bytes) {
+// only the latter is accepted (*ws_bytes then tells the launch which form to take; no more than `least` where there is no buffer).
+template <class F>   // least: a function, asked only then
+static gf_status check_ws_or(size_t need, F&& least_of, const void* ws, size_t* ws_bytes) {
   if (check_ws(need, ws, *ws_bytes) == GF_OK) return GF_OK;
+  const size_t least = least_of();
   const gf_status rc = check_ws(least, ws, *ws_bytes);
-  if (*ws_bytes >= need) *ws_bytes = least;
+  if (!ws || !aligned16(ws)) *ws_bytes = std::min(*ws_bytes, least);
   return rc;
 }
 
@@ -417,7 +419,7 @@ gf_status gf_conv_bwd_input_q8(const gf_conv_desc* desc, const int8_t* gy_q, con
   if (rc) return rc;
   if (!gy_q || !w_q || !g_x) return GF_ERR_NULL;
   if (!aligned16(gy_q) || !aligned16(w_q) || !aligned16(g_x)) return GF_ERR_UNSUPPORTED;
-  rc = check_ws_or(ws_bwd_input_q8(g, reduced_out != 0), ws_bwd_input_q8_least(g, reduced_out != 0), ws, &ws_bytes);
+  rc = check_ws_or(ws_bwd_input_q8(g, reduced_out != 0), [&] { return ws_bwd_input_q8_least(g, reduced_out != 0); }, ws, &ws_bytes);
   if (rc) return rc;
   return dev(launch_bwd_input_q8(g, gy_q, w_q, scale, g_x, reduced_out != 0, ws, ws_bytes, static_cast<hipStream_t>(stream)));
 }
@@ -430,7 +432,7 @@ gf_status gf_conv_bwd_weight(const gf_conv_desc* desc, const void* x_u, const vo
   if (!x_u || !gy_u || !g_w) return GF_ERR_NULL;
   if (!aligned16(x_u) || !aligned16(gy_u) || !aligned16(g_w)) return GF_ERR_UNSUPPORTED;
   const size_t need = ws_need(g, GF_OP_BWD_WEIGHT, false);
-  rc = check_ws_or(need, g.r == 1 ? ws_exact_least(g, true, false) : need, ws, &ws_bytes);
+  rc = check_ws_or(need, [&] { return g.r == 1 ? ws_exact_least(g, true, false) : need; }, ws, &ws_bytes);
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (g.r == 1) return dev(launch_exact(g, x_u, nullptr, gy_u, g_w, nullptr, ws, ws_bytes, st));
@@ -446,7 +448,7 @@ gf_status gf_conv_bwd_input(const gf_conv_desc* desc, const void* gy_u, const vo
   if (!gy_u || !w || !g_x) return GF_ERR_NULL;
   if (!aligned16(gy_u) || !aligned16(w) || !aligned16(g_x)) return GF_ERR_UNSUPPORTED;
   const size_t need = ws_need(g, GF_OP_BWD_INPUT, reduced_out != 0);
-  rc = check_ws_or(need, g.r == 1 ? ws_exact_least(g, false, true) : need, ws, &ws_bytes);
+  rc = check_ws_or(need, [&] { return g.r == 1 ? ws_exact_least(g, false, true) : need; }, ws, &ws_bytes);
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (g.r == 1) return dev(launch_exact_dgrad(g, w, gy_u, g_x, ws, ws_bytes, st));
@@ -509,7 +511,7 @@ static gf_status filtered_body(const gf_conv_desc* desc, const void* g_y, const 
     rc = static_scratch(&ws);
     if (rc) return rc;
   }
-  rc = check_ws_or(need, g.r == 1 ? ws_exact_least(filtered_exact_geom(g), true, true) : need, ws, &ws_bytes);
+  rc = check_ws_or(need, [&] { return g.r == 1 ? ws_exact_least(filtered_exact_geom(g), true, true) : need; }, ws, &ws_bytes);
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* wsb = static_cast<char*>(ws);
@@ -612,7 +614,7 @@ static gf_status chained_body(const Geom& g, const void* gy_u, const void* x_u, 
   gf_status rc;
   size_t off_i = 0;
   const size_t need = ws_chained(g, &off_i);
-  rc = check_ws_or(need, g.r == 1 ? ws_exact_least(g, true, true) : need, ws, &ws_bytes);
+  rc = check_ws_or(need, [&] { return g.r == 1 ? ws_exact_least(g, true, true) : need; }, ws, &ws_bytes);
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* wsb = static_cast<char*>(ws);
@@ -697,7 +699,7 @@ gf_status gf_conv_bwd_exact(const gf_conv_desc* desc, const void* x, const void*
   if ((g_w && !x) || (g_x && !w)) return GF_ERR_NULL;
   if (!aligned16(g_y) || !aligned16(x) || !aligned16(w) || !aligned16(g_w) || !aligned16(g_x))
     return GF_ERR_UNSUPPORTED;
-  rc = check_ws_or(ws_exact(g, g_w != nullptr, g_x != nullptr), ws_exact_least(g, g_w != nullptr, g_x != nullptr), ws, &ws_bytes);
+  rc = check_ws_or(ws_exact(g, g_w != nullptr, g_x != nullptr), [&] { return ws_exact_least(g, g_w != nullptr, g_x != nullptr); }, ws, &ws_bytes);
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   return dev(launch_exact(g, x, w, g_y, g_w, g_x, ws, ws_bytes, st));
@@ -722,7 +724,7 @@ gf_status gf_conv_bwd_unique(const gf_conv_desc* desc, const void* gy_u, const v
   size_t off_red = 0;
   const bool full = g_x && !reduced_out;
   const size_t need = ws_unique(g, red, g_w != nullptr, g_x != nullptr, reduced_out != 0, &off_red);
-  rc = check_ws_or(need, ws_unique(g, red, g_w != nullptr, g_x != nullptr, reduced_out != 0, nullptr, true), ws, &ws_bytes);
+  rc = check_ws_or(need, [&] { return ws_unique(g, red, g_w != nullptr, g_x != nullptr, reduced_out != 0, nullptr, true); }, ws, &ws_bytes);
   if (rc) return rc;
   if (ws_bytes < need) ws_unique(g, red, g_w != nullptr, g_x != nullptr, reduced_out != 0, &off_red, true);
   hipStream_t st = static_cast<hipStream_t>(stream);

@@ -331,10 +331,11 @@ size_t ws_exact(const Geom& g, bool want_gw, bool want_gx) {
 
 // Pointwise input gradients have a form without a workspace, and so do weight gradients of strided depthwise layers whose
 // planes are too large for the kernels that stage x (the direct kernel; 16 channels, 112 x 112, n = 16, fp32 108 us where the
-// one pass takes 14).
+// one pass takes 14).  Others may have one with less of it (ws_implicit_least).
 size_t ws_exact_least(const Geom& g, bool want_gw, bool want_gx) {
   if (want_gw && g.s == 2 && dw_exact_onepass_ok(g) && !dw_exact_wgrad_ok(g)) return 0;
-  return !want_gw && gemm_path(g) && pointwise_plain(g) ? 0 : ws_exact(g, want_gw, want_gx);
+  if (!want_gw && gemm_path(g) && pointwise_plain(g)) return 0;
+  return implicit_ok(g) && !(want_gw && wgrad_by_columns(g)) ? ws_implicit_least(g, want_gw, want_gx) : ws_exact(g, want_gw, want_gx);
 }
 
 // (layers that launch_exact leaves)
@@ -375,7 +376,7 @@ static hipError_t launch_exact_wgrad(const Geom& g, const void* x, const void* g
 
 hipError_t launch_exact_dgrad(const Geom& g, const void* w, const void* g_y, void* g_x, void* ws, size_t ws_bytes,
                               hipStream_t st) {
-  if (implicit_ok(g) && ws_bytes >= ws_implicit(g, false, true)) return launch_implicit(g, nullptr, w, g_y, nullptr, g_x, ws, st);
+  if (implicit_ok(g) && ws_bytes >= ws_implicit_least(g, false, true)) return launch_implicit(g, nullptr, w, g_y, nullptr, g_x, ws, ws_bytes, st);
   if (gemm_path(g)) {
     const Geom q = dgrad_geom(g);
     if (pointwise_plain(g)) return launch_mfma_dgrad(q, g_y, w, nullptr, g_x, nullptr, st);
@@ -414,7 +415,7 @@ hipError_t launch_exact_dgrad(const Geom& g, const void* w, const void* g_y, voi
 hipError_t launch_exact(const Geom& g, const void* x, const void* w, const void* g_y, float* g_w, void* g_x, void* ws,
                         size_t ws_bytes, hipStream_t st) {
   if (!g_w) return launch_exact_dgrad(g, w, g_y, g_x, ws, ws_bytes, st);
-  if (implicit_ok(g) && !wgrad_by_columns(g)) return launch_implicit(g, x, w, g_y, g_w, g_x, ws, st);
+  if (implicit_ok(g) && !wgrad_by_columns(g)) return launch_implicit(g, x, w, g_y, g_w, g_x, ws, ws_bytes, st);
   if (dw_exact_onepass_ok(g) && ws_bytes >= ws_exact(g, true, g_x != nullptr)) return launch_dw_exact_onepass(g, x, w, g_y, g_w, g_x, ws, st);
   const hipError_t e = launch_exact_wgrad(g, x, g_y, g_w, ws, st);
   if (e != hipSuccess || !g_x) return e;

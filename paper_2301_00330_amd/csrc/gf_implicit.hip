@@ -1328,7 +1328,7 @@ int interleave_planes(const Geom& g, const XGeo& q) {
 // 96 -> 96, 112 x 112, n = 128 629 / 783; 128 -> 256, 60 x 80, n = 128 552 / 594; but 128 -> 128, 28 x 28, n = 64 43.7 / 42.2,
 // 256 -> 256, 60 x 80, n = 128 1613 / 1210; 5 x 5, 128 -> 128, 56 x 56, n = 64 275 / 237.  With planes of whole vectors either
 // form returns the same weight gradient, with others K is cut into other chunks; there gf_conv_bwd_exact, gf_conv_bwd_weight and the
-// chained entry take the same form whichever gradients they are asked for (57 x 81, n = 64, both gradients 274 / 269).  The one-call entry, which
+// chained entry, with the workspace gf_workspace_bytes names, take the same form whichever gradients they are asked for (57 x 81, n = 64, both gradients 274 / 269).  The one-call entry, which
 // returns the same bits on the library's scratch, keeps the unstaged form where only that fits (256 -> 256, 57 x 57, n = 32: 37 MB,
 // staged 138), with any workspace: its g_w may then differ from theirs in the order of the sums, its g_x does not.
 bool staged_ok(const Geom& g, bool want_gx) {
@@ -1420,10 +1420,9 @@ hipError_t implicit_products(const Geom& g, const XGeo& q, const XPlan& p, const
 
 template <class T>
 hipError_t implicit_t(const Geom& g, const void* x, const void* w, const void* g_y, float* g_w, void* g_x,
-                      void* ws, hipStream_t st) {
+                      void* ws, bool staged, hipStream_t st) {
   const bool want_gw = g_w != nullptr, want_gx = g_x != nullptr;
   const XGeo q = make_xgeo(g);
-  const bool staged = staged_ok(g, want_gx);
   const XPlan p = make_plan(g, want_gw, want_gx, staged);
   constexpr int VE = El<T>::VE;
   char* wsb = static_cast<char*>(ws);
@@ -1562,16 +1561,25 @@ size_t ws_implicit(const Geom& g, bool want_gw, bool want_gx) {
   return make_plan(g, want_gw, want_gx, staged_ok(g, want_gx)).total;
 }
 
+// Layers of the one pass over the maps take the two products, and layers on staged operands the maps themselves, with a workspace
+// that only those fit: the copies are many times the rest (512 -> 512, 30 x 40, n = 128: 357 MB and 42).
+size_t ws_implicit_least(const Geom& g, bool want_gw, bool want_gx) {
+  Geom e;
+  if (plain_pointwise(g, &e)) return std::min(ws_implicit(g, want_gw, want_gx), ws_dense(e, want_gw, want_gx, true, false));
+  return std::min(ws_implicit(g, want_gw, want_gx), make_plan(g, want_gw, want_gx, false).total);
+}
+
 // g_w and / or g_x (either may be null): one set-up launch, then the GEMM launches
 hipError_t launch_implicit(const Geom& g, const void* x, const void* w, const void* g_y, float* g_w, void* g_x,
-                           void* ws, hipStream_t st) {
+                           void* ws, size_t ws_bytes, hipStream_t st) {
   Geom e;
+  const bool all = ws_bytes >= ws_implicit(g, g_w != nullptr, g_x != nullptr);
   if (plain_pointwise(g, &e)) {
-    if (pointwise_ok(e)) return launch_pointwise(e, g_y, x, w, g_w, g_x, ws, st);
+    if (pointwise_ok(e) && all) return launch_pointwise(e, g_y, x, w, g_w, g_x, ws, st);
     return launch_dense(e, g_y, false, x, w, nullptr, g_w, g_x, true, nullptr, ws, st);
   }
-  return g.dtype == GF_BF16 ? implicit_t<bf16_t>(g, x, w, g_y, g_w, g_x, ws, st)
-                            : implicit_t<float>(g, x, w, g_y, g_w, g_x, ws, st);
+  return g.dtype == GF_BF16 ? implicit_t<bf16_t>(g, x, w, g_y, g_w, g_x, ws, all && staged_ok(g, g_x != nullptr), st)
+                            : implicit_t<float>(g, x, w, g_y, g_w, g_x, ws, false, st);
 }
 
 }  // namespace gf

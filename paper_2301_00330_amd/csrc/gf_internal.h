@@ -306,15 +306,16 @@ hipError_t launch_exact_dgrad(const Geom& g, const void* w, const void* g_y, voi
 
 
 // S5 for dense stride-1 "same"-size layers: implicit GEMMs without a column tensor
-// (gf_implicit.hip).  ws as sized by ws_implicit().
+// (gf_implicit.hip).  ws_bytes: what the workspace holds, ws_implicit() or at least ws_implicit_least().
 bool implicit_ok(const Geom& g);
 size_t ws_implicit(const Geom& g, bool want_gw, bool want_gx);
+size_t ws_implicit_least(const Geom& g, bool want_gw, bool want_gx);
 // plain contraction part[z][co][ci] = sum_{n, p} gy_u * x_u on the same 128 x 128 tiles (large dense S3)
 bool plain_wgrad_ok(const Geom& g);
 int plain_wgrad_splits(const Geom& g);
 hipError_t launch_plain_wgrad(const Geom& g, const void* x_u, const void* gy_u, float* part, int* nz_out,
                               hipStream_t st);
 hipError_t launch_implicit(const Geom& g, const void* x, const void* w, const void* g_y, float* g_w, void* g_x,
-                           void* ws, hipStream_t st);
+                           void* ws, size_t ws_bytes, hipStream_t st);
 
 }  // namespace gf

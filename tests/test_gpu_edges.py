@@ -280,6 +280,47 @@ def test_vanilla_weight_gradient_alone_on_a_large_map(oracle, case):
     assert rel_err(g_x[N - 1:], r_x) <= TOL["bf16"]
 
 
+# N, C_in, C_out, H, W, K, stride, padding, dtype; bytes for both gradients, g_w, g_x without the forms that need more
+@pytest.mark.parametrize("case,least", [
+    ((16, 192, 255, 28, 28, 3, 1, 1, "bf16"), (14984192, 14102784, 883712)),
+    ((2, 97, 127, 13, 11, 3, 2, 1, "bf16"), (813056, 509952, 304128)),
+    ((12, 24, 144, 64, 64, 1, 1, 0, "f32"), (1769472, 1769472, 256)),
+])
+def test_vanilla_layers_with_less_workspace(oracle, case, least):
+    """Staged operands and the one pass over the maps: a call whose workspace holds what the unstaged form or the two products need,
+    but not the copies and slabs, is taken; one byte less than the smallest is not."""
+    N, Ci, Co, H, W, K, s, p, dtype = case
+    d = mk(N, Ci, Co, H, W, K, s, p, r=1, dtype=dtype)
+    sh = T.shapes(d)
+    x, w, gy = (randn(sh[k], i, dtype) for i, k in enumerate(("x", "w", "g_y"), 1))
+    r_w, r_x = oracle.bwd_exact(odesc(oracle, d), to64(x), to64(w), to64(gy))
+    x, w, gy = x.cuda(), w.cuda(), gy.cuda()
+    ws = torch.empty(B.gf_workspace_bytes(d, B.GF_OP_BWD_EXACT) + 4096, dtype=torch.uint8, device="cuda")
+    st = torch.cuda.current_stream().cuda_stream
+
+    def call(n, a, b):   # the outputs, or None: refused
+        g_w, g_x = torch.zeros(sh["w"], device="cuda"), torch.zeros_like(x)
+        ws[n:].fill_(77)
+        try:
+            B.gf_conv_bwd_exact(d, B.ptr(x), B.ptr(w), B.ptr(gy), B.ptr(g_w) if a else 0, B.ptr(g_x) if b else 0, B.ptr(ws), n, st)
+        except B.GfError as e:
+            assert e.status == B.GF_ERR_WORKSPACE
+            return None
+        assert (ws[n:] == 77).all()
+        return g_w, g_x
+
+    for (a, b), most in zip(((1, 1), (1, 0), (0, 1)), least):
+        lo, hi = 0, most   # refused without one (g_x of pointwise layers is not), taken with what these calls always needed
+        assert call(hi, a, b) is not None
+        while hi - lo > 1:
+            mid = (lo + hi) // 2
+            lo, hi = (lo, mid) if call(mid, a, b) is not None else (mid, hi)
+        for n in (hi, most):
+            g_w, g_x = call(n, a, b)
+            assert not a or rel_err(g_w, r_w) <= TOL[dtype]
+            assert not b or rel_err(g_x, r_x) <= TOL[dtype]
+
+
 # N, C, H, W, K, padding: both gradients of a depthwise layer in one pass (ragged groups of pixels, frames, image runs)
 DW_EXACT_CASES = [
     (3, 5, 20, 20, 3, 1),
