@@ -6,6 +6,7 @@
 // two deterministic stages (partials in the workspace, then a fixed-order sum),
 // never with floating-point atomics.
 #include "gf_internal.h"
+#include "gf_mma.h"
 
 #include <type_traits>
 
@@ -152,6 +153,71 @@ __global__ __launch_bounds__(kThreads) void dw_chain_k(const T* xu, const T* gyu
     }
   }
   for (int m = L >> 1; m > 0; m >>= 1) acc += __shfl_xor(acc, m, 64);
+  if (plane < planes && lane == 0) part[plane] = acc;
+}
+
+// Same with 16-byte loads and stores (P of at least a vector; UNAL: planes that are no whole vectors, at the alignment of an
+// element).  L lanes per plane; four vectors of every operand are in flight per lane, at clamped positions, so that a
+// plane costs one trip to memory.  The last vector of an UNAL plane starts P - VE elements in and its first elements belong
+// to the lane before: they are neither summed nor stored.  HBM; 144 channels, 56 x 56, r = 2, n = 32, fp32, with a mask (58 MB): element
+// by element 19.0 us, so 13.2 (4.4 TB/s); bf16 16.4 and 9.0.
+template <class T, bool UNAL, bool MASK>
+__global__ __launch_bounds__(kThreads) void dw_chain_vec_k(const T* xu, const T* gyu, const T* w, float* part, T* gxu,
+                                                          const T* mask, int planes, int P, int nvec, int L, int C, int KK,
+                                                          float scalar) {
+  constexpr int VE = Vec16<T>::N, U = 4;
+  const int gid = blockIdx.x * kThreads + threadIdx.x;
+  const int plane = gid / L;
+  const int lane = gid - plane * L;
+  float acc = 0.f;
+  if (plane < planes) {
+    const long base = (long)plane * P;
+    const float sc = scalar * kernel_sum_of(w, plane % C, KK);
+    for (int v0 = lane; v0 < nvec; v0 += U * L) {
+      uint4 a[U], b[U], m[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const long o = base + min(min(v0 + u * L, nvec - 1) * VE, P - VE);
+        if constexpr (UNAL) {
+          a[u] = load_vec<T>(xu + o);
+          b[u] = load_vec<T>(gyu + o);
+          if (MASK) m[u] = load_vec<T>(mask + o);
+        } else {
+          a[u] = *reinterpret_cast<const uint4*>(xu + o);
+          b[u] = *reinterpret_cast<const uint4*>(gyu + o);
+          if (MASK) m[u] = *reinterpret_cast<const uint4*>(mask + o);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int v = v0 + u * L;
+        if (v >= nvec) break;
+        const int at = min(v * VE, P - VE), dup = v * VE - at;   // elements of the vector before
+        float fa[VE], fb[VE], fm[VE];
+        Vec16<T>::unpack(a[u], fa);
+        Vec16<T>::unpack(b[u], fb);
+        if (MASK) Vec16<T>::unpack(m[u], fm);
+        T o[VE];
+#pragma unroll
+        for (int e = 0; e < VE; ++e) {
+          if (!UNAL || e >= dup) acc += fa[e] * fb[e];
+          o[e] = from_f32<T>(fb[e] * sc);
+          if (MASK) o[e] = from_f32<T>(to_f32(o[e]) * fm[e]);   // the rounded value times the mask fraction
+        }
+        T* d = gxu + base + at;
+        if (!UNAL) {
+          *reinterpret_cast<uint4*>(d) = __builtin_bit_cast(uint4, o);
+        } else if (dup == 0) {
+          *reinterpret_cast<Unal<T>*>(d) = __builtin_bit_cast(Unal<T>, o);
+        } else {
+#pragma unroll
+          for (int e = 0; e < VE; ++e)
+            if (e >= dup) d[e] = o[e];
+        }
+      }
+    }
+  }
+  for (int k = L >> 1; k > 0; k >>= 1) acc += __shfl_xor(acc, k, 64);
   if (plane < planes && lane == 0) part[plane] = acc;
 }
 
@@ -810,25 +876,39 @@ hipError_t launch_gf_bwd_input(const Geom& g, const void* gy_u, const void* w, v
                             static_cast<float*>(g_x), reduced_out, ws, st);
 }
 
+template <class T>
+static hipError_t launch_dw_chain_t(const Geom& g, const T* xu, const T* gyu, const T* w, float* part, T* gxu, const T* mask,
+                                    hipStream_t st) {
+  constexpr int VE = Vec16<T>::N;
+  const int planes = g.N * g.Ci;
+  const float scalar = 1.f / ((float)g.s * (float)g.s);
+  if (g.P < VE) {
+    const int L = dw_lanes(g.P);
+    GF_LAUNCH(dw_chain_k<T>, dim3(cdiv((long)planes * L, kThreads)), dim3(kThreads), 0, st, xu, gyu, w, part, gxu, mask, planes,
+              g.P, L, g.Ci, g.KK, scalar);
+    return hipGetLastError();
+  }
+  const int nvec = cdiv(g.P, VE), L = dw_lanes(cdiv(nvec, 4));
+  const dim3 grid(cdiv((long)planes * L, kThreads));
+  if (g.P % VE) {
+    if (mask) GF_LAUNCH((dw_chain_vec_k<T, true, true>), grid, dim3(kThreads), 0, st, xu, gyu, w, part, gxu, mask, planes, g.P, nvec, L, g.Ci, g.KK, scalar);
+    else GF_LAUNCH((dw_chain_vec_k<T, true, false>), grid, dim3(kThreads), 0, st, xu, gyu, w, part, gxu, mask, planes, g.P, nvec, L, g.Ci, g.KK, scalar);
+  } else {
+    if (mask) GF_LAUNCH((dw_chain_vec_k<T, false, true>), grid, dim3(kThreads), 0, st, xu, gyu, w, part, gxu, mask, planes, g.P, nvec, L, g.Ci, g.KK, scalar);
+    else GF_LAUNCH((dw_chain_vec_k<T, false, false>), grid, dim3(kThreads), 0, st, xu, gyu, w, part, gxu, mask, planes, g.P, nvec, L, g.Ci, g.KK, scalar);
+  }
+  return hipGetLastError();
+}
+
 // Depthwise layer of a chain: partial dot products [N, C] and the reduced input gradient in one
 // launch (then launch_finalize with nz = N).
 hipError_t launch_dw_chain(const Geom& g, const void* x_u, const void* gy_u, const void* w, float* part,
                            void* g_xu, const void* mask_u, hipStream_t st) {
-  const int planes = g.N * g.Ci;
-  const int L = dw_lanes(g.P);
-  const int blocks = cdiv((long)planes * L, kThreads);
-  const float scalar = 1.f / ((float)g.s * (float)g.s);
   if (g.dtype == GF_BF16)
-    GF_LAUNCH(dw_chain_k<bf16_t>, dim3(blocks), dim3(kThreads), 0, st, static_cast<const bf16_t*>(x_u),
-                       static_cast<const bf16_t*>(gy_u), static_cast<const bf16_t*>(w), part,
-                       static_cast<bf16_t*>(g_xu), static_cast<const bf16_t*>(mask_u), planes, g.P, L, g.Ci, g.KK,
-                       scalar);
-  else
-    GF_LAUNCH(dw_chain_k<float>, dim3(blocks), dim3(kThreads), 0, st, static_cast<const float*>(x_u),
-                       static_cast<const float*>(gy_u), static_cast<const float*>(w), part,
-                       static_cast<float*>(g_xu), static_cast<const float*>(mask_u), planes, g.P, L, g.Ci, g.KK,
-                       scalar);
-  return hipGetLastError();
+    return launch_dw_chain_t(g, static_cast<const bf16_t*>(x_u), static_cast<const bf16_t*>(gy_u), static_cast<const bf16_t*>(w),
+                             part, static_cast<bf16_t*>(g_xu), static_cast<const bf16_t*>(mask_u), st);
+  return launch_dw_chain_t(g, static_cast<const float*>(x_u), static_cast<const float*>(gy_u), static_cast<const float*>(w), part,
+                           static_cast<float*>(g_xu), static_cast<const float*>(mask_u), st);
 }
 
 }  // namespace gf

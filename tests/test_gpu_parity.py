@@ -207,6 +207,34 @@ def test_chained_entry_with_mask(oracle, case, dtype):
     assert torch.equal(g_xu, prod)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", [
+    # depthwise (C, H, W, r): planes of less than a vector, of whole ones, with a part left, of more than a round of loads
+    (5, 2, 6, 2), (3, 4, 4, 2), (5, 2, 10, 2), (7, 2, 14, 2), (3, 4, 8, 2), (6, 6, 6, 2), (3, 2, 34, 2), (3, 14, 14, 2),
+    (2, 2, 2062, 2), (2, 4, 2050, 2), (2, 2, 4098, 2),
+    # dense (C_x, C_y, H, W, r): reduced maps of whole vectors, as whole images and in bands with a part left; and not
+    (70, 24, 8, 4, 2), (130, 24, 12, 24, 2), (66, 24, 26, 20, 2), (24, 24, 16, 18, 2), (40, 24, 10, 18, 3)])
+def test_chained_reduced_edges(oracle, case, dtype):
+    """Reduced input gradients of a chain at the edges of the vectors they are stored by, with a mask and without."""
+    N = 3
+    Ci, Co, H, W, r = case if len(case) == 5 else (case[0], *case)
+    g, K, p = (Ci, 3, 1) if len(case) == 4 else (1, 1, 0)
+    d = mk(N, Ci, Co, H, W, K, 1, p, 1, g, r, dtype)
+    od = odesc(oracle, d)
+    _, _, Hp, Wp = B.gf_out_shape(d)
+    x_u = randn((N, Ci, Hp, Wp), 71, dtype)
+    m_u = randn((N, Ci, Hp, Wp), 72, dtype)
+    w = randn((Co, Ci // g, K, K), 73, dtype)
+    gyu = randn((N, Co, Hp, Wp), 74, dtype)
+    g_w, g_xu = T.conv_bwd_chained(d, gyu.cuda(), x_u.cuda(), w.cuda(), reduced_out=True, mask_u=m_u.cuda())
+    g_w0, g_xu0 = T.conv_bwd_chained(d, gyu.cuda(), x_u.cuda(), w.cuda(), reduced_out=True)
+    torch.cuda.synchronize()
+    assert torch.equal(g_w, g_w0)
+    assert rel_err(g_w, oracle.bwd_weight(od, to64(x_u), to64(gyu))) <= TOL[dtype]
+    assert rel_err(g_xu0, oracle.bwd_input(od, to64(gyu), to64(w), reduced_out=True)) <= TOL[dtype]
+    assert torch.equal(g_xu, (g_xu0.float() * m_u.cuda().float()).to(g_xu0.dtype))
+
+
 def test_r1_reductions_are_copies():
     d = mk(2, 3, 4, 14, 14, K=3, s=2, p=1, r=1, dtype="bf16")
     x = randn((2, 3, 14, 14), 1, "bf16").cuda()
