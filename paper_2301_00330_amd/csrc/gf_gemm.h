@@ -224,7 +224,7 @@ __device__ __forceinline__ void mul_all(const uint4 (&fa)[TM][terms_of<T>()], co
 // the four rows (codes: eight) that a transposing read takes together fall into different banks.
 template <class T, int C>
 __device__ __forceinline__ int swz(int k) {
-  if (El<T>::EB == 4) return 0;
+  if (El<T>::EB == 4 || C == 32) return 0;
   const int r = El<T>::EB == 2 ? k : k >> 1;
   return C == 64 ? (r >> 1) & 1 : r & 3;
 }

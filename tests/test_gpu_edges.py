@@ -514,6 +514,38 @@ def test_short_k_weight_gradient(oracle, case, dtype):
     check_codes(oracle, case, dtype)
 
 
+# N, C_in, C_out, H, W, K, stride, r: input gradients on 32 x 32 tiles -- their edges, K of one round of the four waves and of several,
+# a last chunk that is not full, slabs; whole images, bands of patch rows, planes of less than a vector
+FEW_TILE_CASES = [
+    (1, 32, 64, 8, 8, 1, 1, 2),        # one tile, two chunks of 32-bit values
+    (1, 33, 129, 7, 7, 3, 1, 2),       # a row past the tile, a row of k past the chunk
+    (2, 40, 257, 6, 6, 1, 1, 2),       # nine patches: every vector ends inside its plane
+    (3, 70, 800, 9, 7, 1, 1, 2),       # slabs, fp32
+    (2, 64, 1090, 14, 14, 3, 1, 2),    # bands of four and of three patch rows
+    (1, 31, 2100, 10, 62, 1, 1, 2),    # a patch row per band, slabs
+    (4, 36, 130, 5, 5, 3, 2, 2),       # strided
+    (1, 24, 300, 33, 30, 1, 1, 4),     # ragged patches
+    (9, 20, 150, 6, 4, 5, 1, 7),       # one patch per plane
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", FEW_TILE_CASES)
+def test_few_tile_input_gradient(oracle, case, dtype):
+    check_filtered(oracle, case, dtype)
+    check_codes(oracle, case, dtype)
+    N, Ci, Co, H, W, K, s, r = case
+    d = mk(N, Ci, Co, H, W, K, s, K // 2, r=r, dtype=dtype)
+    sh = T.shapes(d)
+    w, gyu = randn(sh["w"], 2, dtype), randn(sh["gy_u"], 3, dtype)
+    g_xu = T.conv_bwd_input(d, gyu.cuda(), w.cuda(), reduced_out=True)
+    assert rel_err(g_xu, oracle.bwd_input(odesc(oracle, d), to64(gyu), to64(w), reduced_out=True)) <= TOL[dtype]
+    # an infinite gradient reaches the pixels of its patch and no others
+    gyu[N - 1, Co - 1, -1, -1] = float("inf")
+    g_x = T.conv_bwd_input(d, gyu.cuda(), w.cuda())
+    assert torch.equal(torch.isfinite(g_x.cpu()), torch.isfinite(torch.from_numpy(oracle.bwd_input(odesc(oracle, d), to64(gyu), to64(w)))))
+
+
 # N, C_in, C_out, H, W: fp32, slabs of 32 x 32 tiles with one chunk for each wave, one more, two for each, one more, two in all
 @pytest.mark.parametrize("case", [(76, 92, 10, 14, 14), (77, 92, 10, 14, 14), (64, 96, 160, 16, 16), (63, 70, 90, 12, 12), (1, 90, 70, 14, 14)])
 def test_short_k_sums_do_not_lean(case):
