@@ -1206,6 +1206,18 @@ struct XPlan {
   int qv, nchunks, nz, cpz, w_tm, w_tn, qd, d_tm, d_tn;
 };
 
+// taps of the phase that has most of them
+int most_taps(const Geom& g) {
+  int most[2] = {0, 0};
+  for (int dim = 0; dim < 2; ++dim)
+    for (int ph = 0; ph < g.s; ++ph) {
+      int n = 0;
+      for (int u = 0; u < (dim ? g.Kw : g.Kh); ++u) n += ((long)u * g.dl + ph - g.p) % g.s == 0;
+      most[dim] = std::max(most[dim], n);
+    }
+  return most[0] * most[1];
+}
+
 // Tile sides in units of 64: 128 x 128 where every block slot of the chip has at least eight steps of such tiles (two
 // blocks per CU: registers), 128 x 64 below that, and 64 x 64 where a side of the layer has no more than 64 channels.
 // An input gradient alone has its few channels in K: 128 x 128 (c_i, pixels) from 384 such tiles on, where K is one slab
@@ -1235,7 +1247,9 @@ int slab_chunks(int nchunks, long z) {
 // 120 x 160, n = 8 (86): 90 -> 65; 128 -> 128, 60 x 80, n = 8 (50): 59 -> 51.
 // 280 layers of all calls that split K (vanilla of both types, bf16 weight gradients of 6 GFLOP and more): 0.89 .. 1.28, mean 1.004.
 bool deal_slabs(int nz) { return 10 * (cdiv(nz, 8) * 8) <= 11 * nz; }
-XPlan make_plan(const Geom& g, bool want_gw, bool want_gx, bool staged) {
+// few: K slabs of the input gradient by an earlier rule, from 16 steps on only and counted up to the taps of the whole kernel, for a
+// workspace that only those fit
+XPlan plan_of(const Geom& g, bool want_gw, bool want_gx, bool staged, bool few) {
   const XGeo q = make_xgeo(g);
   const int VE = 16 / g.b;
   XPlan p = {};
@@ -1259,11 +1273,21 @@ XPlan make_plan(const Geom& g, bool want_gw, bool want_gx, bool staged) {
   // of the chip idle.  Weight gradient: as many slabs as the slots the input gradient leaves can take in one go.
   const long d_tiles = (long)p.d_tm * p.d_tn * q.nph, w_tiles = (long)p.w_tm * p.w_tn * g.KK;
   const int taps = cdiv(g.KK, q.nph);                     // per phase, about
-  const int d_steps = taps * cdiv(g.Co, g.b == 2 ? 64 : 32), d_most = g.KK * cdiv(g.Co, g.b == 2 ? 64 : 32);
+  const int d_steps = taps * cdiv(g.Co, g.b == 2 ? 64 : 32), d_most = (few ? g.KK : most_taps(g)) * cdiv(g.Co, g.b == 2 ? 64 : 32);
   p.d_nz = 1;
-  while (p.d_nz < 64 && d_tiles * p.d_nz * 2 <= slots / 2 && d_steps >= 16 * p.d_nz) p.d_nz *= 2;
+  // Twice the slabs where a block has 16 steps and more and half the slots take them; fp32, whose steps take twice as long: also from
+  // 8 steps on where a quarter of the slots does, from 4 where an eighth does.  Both gradients in us, 16 steps / this rule: 256 -> 88, 3 x 3,
+  // 6 x 6, n = 2 37.9 / 25.9; 154 -> 88, 5 x 5, n = 1 38.5 / 26.9; 216 -> 144, 15 x 15, stride 2, n = 2 42.9 / 26.8; 250 random layers: the 82
+  // that change 1.18 times as fast in the mean, 0.96 at the least.  With 8 steps up to half the slots: 64 -> 32, 25 x 25, n = 19 33 / 40.
+  // bf16 from 8 steps on where a sixteenth takes them: 41 layers 1.05 in the mean, but ten of them 0.88 - 0.95; not taken.
+  auto worth = [&](int steps, long blocks) {
+    return (steps >= 16 && blocks <= slots / 2) || (g.b == 4 && !few && ((steps >= 8 && blocks <= slots / 4) || (steps >= 4 && blocks <= slots / 8)));
+  };
+  while (p.d_nz < 64 && worth(d_steps / p.d_nz, d_tiles * p.d_nz * 2)) p.d_nz *= 2;
   p.d_its = p.d_nz == 1 ? d_most : cdiv(d_steps, p.d_nz);
-  if (p.d_nz > 1) p.d_nz = cdiv(d_most, p.d_its);         // phases with more taps than the average need more slabs
+  // phases with more taps than the average need more slabs (counted up to the taps of the whole kernel, most of them were
+  // empty: 208 -> 104, 5 x 5, 20 x 20, stride 2, n = 10, fp32 98 -> 56 us; 152 -> 488, 10 x 10, n = 12, bf16 47 -> 36)
+  if (p.d_nz > 1) p.d_nz = cdiv(d_most, p.d_its);
   groups_for(p.d_nz, &p.d_grp, &p.d_ngrp);
   p.ntickets = p.d_nz > 1 ? (int)(d_tiles * (1 + p.d_ngrp)) : 0;
   // Both products at once where the slots the input gradient leaves take the weight gradient with blocks of about its
@@ -1307,6 +1331,14 @@ XPlan make_plan(const Geom& g, bool want_gw, bool want_gx, bool staged) {
   if (want_gx && p.d_nz > 1) off += align256((size_t)d_tiles * (p.d_nz + p.d_ngrp) * 4096 * p.tm * p.tn * sizeof(float));
   p.total = off;
   return p;
+}
+// few also where only that keeps both gradients within the library's own scratch, whatever this call asks for (the one-call entry
+// returns the same bits with either)
+XPlan make_plan(const Geom& g, bool want_gw, bool want_gx, bool staged, bool few = false) {
+  if (!staged && !few)
+    few = plan_of(g, true, true, false, false).total > GF_STATIC_SCRATCH_BYTES &&
+          plan_of(g, true, true, false, true).total <= GF_STATIC_SCRATCH_BYTES;
+  return plan_of(g, want_gw, want_gx, staged, few);
 }
 
 // planes a block of the interleave stages: a multiple of VE (runs start on vector boundaries), about 16 KB, and
@@ -1420,10 +1452,10 @@ hipError_t implicit_products(const Geom& g, const XGeo& q, const XPlan& p, const
 
 template <class T>
 hipError_t implicit_t(const Geom& g, const void* x, const void* w, const void* g_y, float* g_w, void* g_x,
-                      void* ws, bool staged, hipStream_t st) {
+                      void* ws, bool staged, bool few, hipStream_t st) {
   const bool want_gw = g_w != nullptr, want_gx = g_x != nullptr;
   const XGeo q = make_xgeo(g);
-  const XPlan p = make_plan(g, want_gw, want_gx, staged);
+  const XPlan p = make_plan(g, want_gw, want_gx, staged, few);
   constexpr int VE = El<T>::VE;
   char* wsb = static_cast<char*>(ws);
   if (staged) {
@@ -1561,12 +1593,13 @@ size_t ws_implicit(const Geom& g, bool want_gw, bool want_gx) {
   return make_plan(g, want_gw, want_gx, staged_ok(g, want_gx)).total;
 }
 
-// Layers of the one pass over the maps take the two products, and layers on staged operands the maps themselves, with a workspace
-// that only those fit: the copies are many times the rest (512 -> 512, 30 x 40, n = 128: 357 MB and 42).
+// Layers of the one pass over the maps take the two products, layers on staged operands the maps themselves, and fp32 layers of few
+// tiles fewer slabs, with a workspace that only those fit: the copies are many times the rest (512 -> 512, 30 x 40, n = 128: 357 MB and 42).
 size_t ws_implicit_least(const Geom& g, bool want_gw, bool want_gx) {
   Geom e;
   if (plain_pointwise(g, &e)) return std::min(ws_implicit(g, want_gw, want_gx), ws_dense(e, want_gw, want_gx, true, false));
-  return std::min(ws_implicit(g, want_gw, want_gx), make_plan(g, want_gw, want_gx, false).total);
+  const size_t least = std::min(ws_implicit(g, want_gw, want_gx), make_plan(g, want_gw, want_gx, false, true).total);
+  return staged_ok(g, want_gx) ? std::min(least, make_plan(g, want_gw, want_gx, true, true).total) : least;
 }
 
 // g_w and / or g_x (either may be null): one set-up launch, then the GEMM launches
@@ -1578,8 +1611,14 @@ hipError_t launch_implicit(const Geom& g, const void* x, const void* w, const vo
     if (pointwise_ok(e) && all) return launch_pointwise(e, g_y, x, w, g_w, g_x, ws, st);
     return launch_dense(e, g_y, false, x, w, nullptr, g_w, g_x, true, nullptr, ws, st);
   }
-  return g.dtype == GF_BF16 ? implicit_t<bf16_t>(g, x, w, g_y, g_w, g_x, ws, all && staged_ok(g, g_x != nullptr), st)
-                            : implicit_t<float>(g, x, w, g_y, g_w, g_x, ws, false, st);
+  const bool gw = g_w != nullptr, gx = g_x != nullptr;
+  bool staged = all && staged_ok(g, gx), few = false;
+  if (!all && ws_bytes < make_plan(g, gw, gx, false).total) {
+    few = true;
+    staged = ws_bytes < make_plan(g, gw, gx, false, true).total;   // (then the staged form of few slabs is the smallest)
+  }
+  return g.dtype == GF_BF16 ? implicit_t<bf16_t>(g, x, w, g_y, g_w, g_x, ws, staged, few, st)
+                            : implicit_t<float>(g, x, w, g_y, g_w, g_x, ws, false, few, st);
 }
 
 }  // namespace gf

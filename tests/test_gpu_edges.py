@@ -280,11 +280,39 @@ def test_vanilla_weight_gradient_alone_on_a_large_map(oracle, case):
     assert rel_err(g_x[N - 1:], r_x) <= TOL["bf16"]
 
 
+# N, C_in, C_out, H, W, K, stride, padding, dilation: input gradients of vanilla layers with few tiles -- slabs of sixteen steps, eight and
+# four, phases with more taps than others, all taps in one phase
+VANILLA_FEW_CASES = [
+    (1, 64, 64, 9, 9, 3, 1, 1, 1),
+    (2, 96, 40, 6, 6, 3, 1, 1, 1),
+    (2, 40, 150, 7, 5, 5, 1, 2, 1),
+    (3, 33, 70, 21, 18, 5, 2, 2, 1),
+    (2, 24, 96, 15, 16, 3, 2, 1, 1),
+    (2, 48, 72, 17, 19, 3, 2, 2, 2),
+    (2, 20, 64, 22, 20, 5, 3, 2, 1),
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", VANILLA_FEW_CASES)
+def test_vanilla_input_gradient_of_few_tiles(oracle, case, dtype):
+    N, Ci, Co, H, W, K, s, p, dl = case
+    d = mk(N, Ci, Co, H, W, K, s, p, dl, r=1, dtype=dtype)
+    sh = T.shapes(d)
+    x, w, gy = (randn(sh[k], i, dtype) for i, k in enumerate(("x", "w", "g_y"), 1))
+    g_w, g_x = T.conv_bwd_exact(d, x.cuda(), w.cuda(), gy.cuda())
+    r_w, r_x = oracle.bwd_exact(odesc(oracle, d), to64(x), to64(w), to64(gy))
+    assert rel_err(g_w, r_w) <= TOL[dtype] and rel_err(g_x, r_x) <= TOL[dtype]
+
+
 # N, C_in, C_out, H, W, K, stride, padding, dtype; bytes for both gradients, g_w, g_x without the forms that need more
 @pytest.mark.parametrize("case,least", [
     ((16, 192, 255, 28, 28, 3, 1, 1, "bf16"), (14984192, 14102784, 883712)),
     ((2, 97, 127, 13, 11, 3, 2, 1, "bf16"), (813056, 509952, 304128)),
     ((12, 24, 144, 64, 64, 1, 1, 0, "f32"), (1769472, 1769472, 256)),
+    ((2, 256, 88, 6, 6, 3, 1, 1, "f32"), (2016256, 812032, 1205248)),     # fewer slabs of few tiles
+    ((10, 52, 26, 20, 20, 5, 2, 2, "f32"), (2748928, 1781504, 970496)),
+    ((18, 445, 179, 5, 20, 5, 2, 2, "bf16"), (53734144, 9790464, 44154624)),
 ])
 def test_vanilla_layers_with_less_workspace(oracle, case, least):
     """Staged operands and the one pass over the maps: a call whose workspace holds what the unstaged form or the two products need,
