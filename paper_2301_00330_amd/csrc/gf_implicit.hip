@@ -1279,9 +1279,10 @@ XPlan plan_of(const Geom& g, bool want_gw, bool want_gx, bool staged, bool few) 
   // 8 steps on where a quarter of the slots does, from 4 where an eighth does.  Both gradients in us, 16 steps / this rule: 256 -> 88, 3 x 3,
   // 6 x 6, n = 2 37.9 / 25.9; 154 -> 88, 5 x 5, n = 1 38.5 / 26.9; 216 -> 144, 15 x 15, stride 2, n = 2 42.9 / 26.8; 250 random layers: the 82
   // that change 1.18 times as fast in the mean, 0.96 at the least.  With 8 steps up to half the slots: 64 -> 32, 25 x 25, n = 19 33 / 40.
-  // bf16 from 8 steps on where a sixteenth takes them: 41 layers 1.05 in the mean, but ten of them 0.88 - 0.95; not taken.
+  // bf16 from 8 steps on where a sixteenth takes them: 41 layers 1.05 in the mean, but ten of them 0.88 - 0.95; not taken.  Nor under
+  // 16 output channels, whose steps are mostly padding: 8 of 4 x 4, n = 2 would bring 128 KB of slabs to 3 KB of tensors.
   auto worth = [&](int steps, long blocks) {
-    return (steps >= 16 && blocks <= slots / 2) || (g.b == 4 && !few && ((steps >= 8 && blocks <= slots / 4) || (steps >= 4 && blocks <= slots / 8)));
+    return (steps >= 16 && blocks <= slots / 2) || (g.b == 4 && !few && g.Co >= 16 && ((steps >= 8 && blocks <= slots / 4) || (steps >= 4 && blocks <= slots / 8)));
   };
   while (p.d_nz < 64 && worth(d_steps / p.d_nz, d_tiles * p.d_nz * 2)) p.d_nz *= 2;
   p.d_its = p.d_nz == 1 ? d_most : cdiv(d_steps, p.d_nz);
