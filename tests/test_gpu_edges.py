@@ -574,6 +574,22 @@ def test_few_tile_input_gradient(oracle, case, dtype):
     assert torch.equal(torch.isfinite(g_x.cpu()), torch.isfinite(torch.from_numpy(oracle.bwd_input(odesc(oracle, d), to64(gyu), to64(w)))))
 
 
+# N, C_in, C_out, H, W, K, stride, r: large bf16 products: both gradients in one launch or in kernels of their own
+LARGE_CASES = [
+    (128, 768, 768, 13, 13, 1, 1, 2),  # cut patches, 49 to a plane
+    (25, 640, 256, 64, 48, 1, 1, 2),   # whole patches and vectors, under 8 GFLOP
+    (12, 1024, 432, 64, 48, 1, 1, 2),  # ... past it
+    (12, 1024, 432, 63, 48, 1, 1, 2),  # ... a cut patch row
+    (13, 1024, 432, 64, 44, 1, 1, 2),  # ... rows that end inside a vector
+    (12, 2048, 224, 64, 48, 3, 1, 2),  # kernel sums
+]
+
+
+@pytest.mark.parametrize("case", LARGE_CASES)
+def test_large_dense_products(oracle, case):
+    check_filtered(oracle, case, "bf16")
+
+
 # N, C_in, C_out, H, W: fp32, slabs of 32 x 32 tiles with one chunk for each wave, one more, two for each, one more, two in all
 @pytest.mark.parametrize("case", [(76, 92, 10, 14, 14), (77, 92, 10, 14, 14), (64, 96, 160, 16, 16), (63, 70, 90, 12, 12), (1, 90, 70, 14, 14)])
 def test_short_k_sums_do_not_lean(case):
