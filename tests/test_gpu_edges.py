@@ -574,6 +574,24 @@ def test_few_tile_input_gradient(oracle, case, dtype):
     assert torch.equal(torch.isfinite(g_x.cpu()), torch.isfinite(torch.from_numpy(oracle.bwd_input(odesc(oracle, d), to64(gyu), to64(w)))))
 
 
+# N, C_in, C_out, H, W, K, stride, r: input gradients on bands of three and five patch rows in tiles of 128 columns, and just not
+WIDE_BAND_CASES = [
+    (4, 768, 24, 65, 65, 1, 1, 2),
+    (4, 705, 17, 66, 83, 3, 1, 2),     # 42 patch columns: two left over; one row of c_i in the last tile
+    (47, 64, 33, 70, 66, 1, 1, 2),     # a last band of two rows
+    (26, 200, 40, 49, 50, 1, 1, 2),    # 25 patch columns
+    (4, 700, 24, 65, 65, 1, 1, 2),     # a tile row less than fills the chip
+    (4, 768, 24, 65, 85, 1, 1, 2),     # 43 patch columns: two rows
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", WIDE_BAND_CASES)
+def test_input_gradient_wide_bands(oracle, case, dtype):
+    check_filtered(oracle, case, dtype)
+    check_codes(oracle, case, dtype)
+
+
 # N, C_in, C_out, H, W, K, stride, r: large bf16 products: both gradients in one launch or in kernels of their own
 LARGE_CASES = [
     (128, 768, 768, 13, 13, 1, 1, 2),  # cut patches, 49 to a plane
