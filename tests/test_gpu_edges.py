@@ -592,6 +592,14 @@ def test_input_gradient_wide_bands(oracle, case, dtype):
     check_codes(oracle, case, dtype)
 
 
+# N, C_in, C_out, H, W, K, stride, r: runs of input-gradient pixels that are less than a vector, one, end vectors alone, one whole between
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", [(3, 5, 9, 1, 3, 1, 1, 2), (3, 6, 9, 1, 7, 1, 1, 2), (2, 7, 16, 3, 3, 1, 1, 2), (3, 65, 12, 2, 7, 3, 1, 2), (2, 9, 12, 1, 19, 1, 1, 4),
+                                  (2, 33, 20, 5, 5, 3, 1, 2), (1, 31, 8, 2, 133, 1, 1, 2)])
+def test_input_gradient_run_ends(oracle, case, dtype):
+    check_filtered(oracle, case, dtype)
+
+
 # N, C_in, C_out, H, W, K, stride, r: large bf16 products: both gradients in one launch or in kernels of their own
 LARGE_CASES = [
     (128, 768, 768, 13, 13, 1, 1, 2),  # cut patches, 49 to a plane
