@@ -85,6 +85,25 @@ def test_one_call_backward_within_the_static_scratch(lib):
         assert B.gf_workspace_bytes(d, B.GF_OP_BWD_FILTERED) <= B.GF_STATIC_SCRATCH_BYTES, d
 
 
+# layer (N, C_in, C_out, H, W, K, r), bf16; bytes of a weight gradient's slabs, an input gradient, one call, a chained layer on kernels of their own
+@pytest.mark.parametrize("layer,most", [
+    ((48, 256, 4096, 16, 16, 1, 2), (33554432, 5767168, 64487424, 39321600)),
+    ((32, 512, 4096, 16, 16, 3, 2), (33554432, 10485760, 60817408, 44040192)),
+    ((48, 384, 3072, 16, 16, 3, 2), (37748736, 7077888, 63700992, 44826624)),
+    ((185, 256, 3488, 10, 76, 1, 8), (28573696, 5466112, 59851008, 34039808)),
+    ((1, 896, 2752, 49, 156, 3, 2), (29589504, 13357568, 53679872, 42947072)),
+    ((6, 640, 3432, 28, 43, 3, 2), (26357760, 11151360, 50193920, 37509120)),
+])
+def test_large_bf16_layers_keep_their_workspace(lib, layer, most):
+    """Both products in one launch take no more workspace than the kernels of their own: no call is refused that was not, nor are
+    the calls on the library's scratch."""
+    N, Ci, Co, H, W, K, r = layer
+    d = B.ConvDesc(N=N, C_in=Ci, C_out=Co, H_in=H, W_in=W, K_h=K, K_w=K, pad=K // 2, r=r, dtype=B.GF_BF16)
+    need = [B.gf_workspace_bytes(d, op) for op in (B.GF_OP_BWD_WEIGHT, B.GF_OP_BWD_INPUT, B.GF_OP_BWD_FILTERED, B.GF_OP_BWD_CHAINED)]
+    assert all(n <= m for n, m in zip(need, most)), need
+    assert need[2] <= B.GF_STATIC_SCRATCH_BYTES
+
+
 def test_slabs_of_code_sums_fit_int32(lib):
     """127^2 n < 2^31 up to n = 133144: the workspace of a weight gradient on codes holds a partial result of every
     C_out x C_in pair per 133000 products, however many tiles the layer has."""
