@@ -157,19 +157,23 @@ __global__ __launch_bounds__(kThreads) void dw_chain_k(const T* xu, const T* gyu
 }
 
 // Same with 16-byte loads and stores (P of at least a vector; UNAL: planes that are no whole vectors, at the alignment of an
-// element).  L lanes per plane; four vectors of every operand are in flight per lane, at clamped positions, so that a
-// plane costs one trip to memory.  The last vector of an UNAL plane starts P - VE elements in and its first elements belong
-// to the lane before: they are neither summed nor stored.  HBM; 144 channels, 56 x 56, r = 2, n = 32, fp32, with a mask (58 MB): element
+// element).  L lanes per plane; U vectors of every operand are in flight per lane, at clamped positions, so that a
+// plane of up to 64 U vectors costs one trip to memory, a larger one another per 64 U.  The last vector of an UNAL plane starts P - VE elements in and its
+// first elements belong to the lane before: they are neither summed nor stored.  Every element of a vector has a sum of its own, and
+// those are added as a tree, as the lanes are: one sum for all of a lane's products left 1.2 - 1.6 times the error of dw_chain_k
+// on planes of 25 patches and more.  HBM; 144 channels, 56 x 56, r = 2, n = 32, fp32, with a mask (58 MB): element
 // by element 19.0 us, so 13.2 (4.4 TB/s); bf16 16.4 and 9.0.
-template <class T, bool UNAL, bool MASK>
+template <class T, bool UNAL, bool MASK, int U>
 __global__ __launch_bounds__(kThreads) void dw_chain_vec_k(const T* xu, const T* gyu, const T* w, float* part, T* gxu,
                                                           const T* mask, int planes, int P, int nvec, int L, int C, int KK,
                                                           float scalar) {
-  constexpr int VE = Vec16<T>::N, U = 4;
+  constexpr int VE = Vec16<T>::N;
   const int gid = blockIdx.x * kThreads + threadIdx.x;
   const int plane = gid / L;
   const int lane = gid - plane * L;
-  float acc = 0.f;
+  float sum[VE];
+#pragma unroll
+  for (int e = 0; e < VE; ++e) sum[e] = 0.f;
   if (plane < planes) {
     const long base = (long)plane * P;
     const float sc = scalar * kernel_sum_of(w, plane % C, KK);
@@ -188,11 +192,11 @@ __global__ __launch_bounds__(kThreads) void dw_chain_vec_k(const T* xu, const T*
           if (MASK) m[u] = *reinterpret_cast<const uint4*>(mask + o);
         }
       }
+      float prod[U][VE];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int v = v0 + u * L;
-        if (v >= nvec) break;
-        const int at = min(v * VE, P - VE), dup = v * VE - at;   // elements of the vector before
+        const int at = min(v * VE, P - VE), dup = v < nvec ? v * VE - at : VE;   // elements of the vector before; none of this one
         float fa[VE], fb[VE], fm[VE];
         Vec16<T>::unpack(a[u], fa);
         Vec16<T>::unpack(b[u], fb);
@@ -200,10 +204,11 @@ __global__ __launch_bounds__(kThreads) void dw_chain_vec_k(const T* xu, const T*
         T o[VE];
 #pragma unroll
         for (int e = 0; e < VE; ++e) {
-          if (!UNAL || e >= dup) acc += fa[e] * fb[e];
+          prod[u][e] = (UNAL ? e >= dup : v < nvec) ? fa[e] * fb[e] : 0.f;
           o[e] = from_f32<T>(fb[e] * sc);
           if (MASK) o[e] = from_f32<T>(to_f32(o[e]) * fm[e]);   // the rounded value times the mask fraction
         }
+        if (v >= nvec) continue;
         T* d = gxu + base + at;
         if (!UNAL) {
           *reinterpret_cast<uint4*>(d) = __builtin_bit_cast(uint4, o);
@@ -215,8 +220,21 @@ __global__ __launch_bounds__(kThreads) void dw_chain_vec_k(const T* xu, const T*
             if (e >= dup) d[e] = o[e];
         }
       }
+#pragma unroll
+      for (int e = 0; e < VE; ++e) {
+#pragma unroll
+        for (int k = 1; k < U; k *= 2)
+#pragma unroll
+          for (int u = 0; u < U; u += 2 * k) prod[u][e] += prod[u + k][e];
+        sum[e] += prod[0][e];
+      }
     }
   }
+#pragma unroll
+  for (int k = VE / 2; k > 0; k /= 2)
+#pragma unroll
+    for (int e = 0; e < k; ++e) sum[e] += sum[e + k];
+  float acc = sum[0];
   for (int k = L >> 1; k > 0; k >>= 1) acc += __shfl_xor(acc, k, 64);
   if (plane < planes && lane == 0) part[plane] = acc;
 }
@@ -876,27 +894,34 @@ hipError_t launch_gf_bwd_input(const Geom& g, const void* gy_u, const void* w, v
                             static_cast<float*>(g_x), reduced_out, ws, st);
 }
 
+template <class T, int U>
+static void launch_dw_chain_vec(const Geom& g, const T* xu, const T* gyu, const T* w, float* part, T* gxu, const T* mask, int nvec,
+                                int L, hipStream_t st) {
+  const int planes = g.N * g.Ci;
+  const float scalar = 1.f / ((float)g.s * (float)g.s);
+  const dim3 grid(cdiv((long)planes * L, kThreads));
+  if (g.P % Vec16<T>::N) {
+    if (mask) GF_LAUNCH((dw_chain_vec_k<T, true, true, U>), grid, dim3(kThreads), 0, st, xu, gyu, w, part, gxu, mask, planes, g.P, nvec, L, g.Ci, g.KK, scalar);
+    else GF_LAUNCH((dw_chain_vec_k<T, true, false, U>), grid, dim3(kThreads), 0, st, xu, gyu, w, part, gxu, mask, planes, g.P, nvec, L, g.Ci, g.KK, scalar);
+  } else {
+    if (mask) GF_LAUNCH((dw_chain_vec_k<T, false, true, U>), grid, dim3(kThreads), 0, st, xu, gyu, w, part, gxu, mask, planes, g.P, nvec, L, g.Ci, g.KK, scalar);
+    else GF_LAUNCH((dw_chain_vec_k<T, false, false, U>), grid, dim3(kThreads), 0, st, xu, gyu, w, part, gxu, mask, planes, g.P, nvec, L, g.Ci, g.KK, scalar);
+  }
+}
+
 template <class T>
 static hipError_t launch_dw_chain_t(const Geom& g, const T* xu, const T* gyu, const T* w, float* part, T* gxu, const T* mask,
                                     hipStream_t st) {
   constexpr int VE = Vec16<T>::N;
-  const int planes = g.N * g.Ci;
-  const float scalar = 1.f / ((float)g.s * (float)g.s);
+  const int planes = g.N * g.Ci, nvec = cdiv(g.P, VE);
   if (g.P < VE) {
     const int L = dw_lanes(g.P);
+    const float scalar = 1.f / ((float)g.s * (float)g.s);
     GF_LAUNCH(dw_chain_k<T>, dim3(cdiv((long)planes * L, kThreads)), dim3(kThreads), 0, st, xu, gyu, w, part, gxu, mask, planes,
               g.P, L, g.Ci, g.KK, scalar);
     return hipGetLastError();
   }
-  const int nvec = cdiv(g.P, VE), L = dw_lanes(cdiv(nvec, 4));
-  const dim3 grid(cdiv((long)planes * L, kThreads));
-  if (g.P % VE) {
-    if (mask) GF_LAUNCH((dw_chain_vec_k<T, true, true>), grid, dim3(kThreads), 0, st, xu, gyu, w, part, gxu, mask, planes, g.P, nvec, L, g.Ci, g.KK, scalar);
-    else GF_LAUNCH((dw_chain_vec_k<T, true, false>), grid, dim3(kThreads), 0, st, xu, gyu, w, part, gxu, mask, planes, g.P, nvec, L, g.Ci, g.KK, scalar);
-  } else {
-    if (mask) GF_LAUNCH((dw_chain_vec_k<T, false, true>), grid, dim3(kThreads), 0, st, xu, gyu, w, part, gxu, mask, planes, g.P, nvec, L, g.Ci, g.KK, scalar);
-    else GF_LAUNCH((dw_chain_vec_k<T, false, false>), grid, dim3(kThreads), 0, st, xu, gyu, w, part, gxu, mask, planes, g.P, nvec, L, g.Ci, g.KK, scalar);
-  }
+  launch_dw_chain_vec<T, 4>(g, xu, gyu, w, part, gxu, mask, nvec, dw_lanes(cdiv(nvec, 4)), st);
   return hipGetLastError();
 }
 
