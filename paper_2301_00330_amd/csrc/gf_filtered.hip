@@ -914,14 +914,24 @@ static hipError_t launch_dw_chain_t(const Geom& g, const T* xu, const T* gyu, co
                                     hipStream_t st) {
   constexpr int VE = Vec16<T>::N;
   const int planes = g.N * g.Ci, nvec = cdiv(g.P, VE);
-  if (g.P < VE) {
+  const bool unal = g.P % VE != 0;
+  if (g.P < VE || (unal && nvec <= 2)) {
     const int L = dw_lanes(g.P);
     const float scalar = 1.f / ((float)g.s * (float)g.s);
     GF_LAUNCH(dw_chain_k<T>, dim3(cdiv((long)planes * L, kThreads)), dim3(kThreads), 0, st, xu, gyu, w, part, gxu, mask, planes,
               g.P, L, g.Ci, g.KK, scalar);
     return hipGetLastError();
   }
-  launch_dw_chain_vec<T, 4>(g, xu, gyu, w, part, gxu, mask, nvec, dw_lanes(cdiv(nvec, 4)), st);
+  // Four vectors a lane where that still leaves the chip 65536 lanes (a lane less on a plane is a trip to memory the less), or a plane is
+  // more than three for each; else one.  The call in us, element by element / four / one: bf16 5 x 5 patches, 256 planes
+  // 5.4 / 7.0 / 5.6, 16384 7.8 / 7.9 / 6.2; fp32 7 x 7, 256 planes 5.5 / 6.0 / 5.5; 14 x 14, 16384 13.7 / 11.7 / 12.3, bf16 (cut vectors)
+  // 13.4 / 11.0 / 10.1; fp32 56 x 56, 256 planes 21.7 / 9.0 / 10.2.  Two cut vectors or less element by element (fp32 2 x 3, 4096
+  // planes 5.6 / 6.3 / 5.9).
+  const int l4 = dw_lanes(cdiv(nvec, 4));
+  if (nvec > 192 || ((long)planes * l4 >= 65536 && !(unal && sizeof(T) == 2)))
+    launch_dw_chain_vec<T, 4>(g, xu, gyu, w, part, gxu, mask, nvec, l4, st);
+  else
+    launch_dw_chain_vec<T, 1>(g, xu, gyu, w, part, gxu, mask, nvec, dw_lanes(nvec), st);
   return hipGetLastError();
 }
 
