@@ -174,6 +174,16 @@ __device__ __forceinline__ u32x4_t keep_mask(int keep) {
   return m;
 }
 
+// s += the six term products of two fp32 operands, smallest first
+__device__ __forceinline__ void add_products(const uint4 (&fa)[3], const uint4 (&fb)[3], f32x16& s) {
+  s = mma32(fa[2], fb[0], s);
+  s = mma32(fa[0], fb[2], s);
+  s = mma32(fa[1], fb[1], s);
+  s = mma32(fa[1], fb[0], s);
+  s = mma32(fa[0], fb[1], s);
+  s = mma32(fa[0], fb[0], s);
+}
+
 // Matrix step ks of a chunk, all tiles.  fp32: the term products are summed from zero -- those of a whole chunk of 32 k
 // for a single tile, of 16 k otherwise (a sum per tile would not fit the registers) -- and then added to the accumulator
 // with one rounding; straight into the accumulator they would round it 24 times per chunk.  And the instruction takes
@@ -191,16 +201,11 @@ __device__ __forceinline__ void mul_all(const uint4 (&fa)[TM][terms_of<T>()], co
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-      if constexpr (is_split<T>()) {   // smallest products first
+      if constexpr (is_split<T>()) {
         if (TM * TN > 1 || ks == 0)
 #pragma unroll
           for (int v = 0; v < 16; ++v) s[v] = 0.f;
-        s = mma32(fa[i][2], fb[j][0], s);
-        s = mma32(fa[i][0], fb[j][2], s);
-        s = mma32(fa[i][1], fb[j][1], s);
-        s = mma32(fa[i][1], fb[j][0], s);
-        s = mma32(fa[i][0], fb[j][1], s);
-        s = mma32(fa[i][0], fb[j][0], s);
+        add_products(fa[i], fb[j], s);
         if (TM * TN > 1 || ks == El<T>::KS - 1) {
           if (NEG) acc[i][j] -= s;
           else acc[i][j] += s;

@@ -28,6 +28,16 @@ def check_filtered(oracle, case, dtype, groups=1):
     assert np.array_equal(to64(g_x), to64(T.conv_bwd_input(d, gy_u, w.cuda())))   # the separate entry, bit for bit
 
 
+def check_reduced(case, dtype):
+    """A reduced input gradient is the full-resolution one, a value per patch, bit for bit."""
+    N, Ci, Co, H, W, K, s, r = case
+    d = mk(N, Ci, Co, H, W, K, s, K // 2, r=r, dtype=dtype)
+    sh = T.shapes(d)
+    w, gyu = randn(sh["w"], 2, dtype).cuda(), randn(sh["gy_u"], 3, dtype).cuda()
+    g_x, g_xu = T.conv_bwd_input(d, gyu, w), T.conv_bwd_input(d, gyu, w, reduced_out=True)
+    assert torch.equal(g_x[:, :, ::r * s, ::r * s], g_xu)
+
+
 # N, C_in, C_out, H, W, K, stride, r: ragged or unaligned maps with more than 64 patches or planes over 16 KB
 BAND_CASES = [
     (2, 24, 40, 65, 65, 1, 1, 4),      # one image in several bands, ragged last patch row and column
@@ -561,6 +571,7 @@ FEW_TILE_CASES = [
 @pytest.mark.parametrize("case", FEW_TILE_CASES)
 def test_few_tile_input_gradient(oracle, case, dtype):
     check_filtered(oracle, case, dtype)
+    check_reduced(case, dtype)
     check_codes(oracle, case, dtype)
     N, Ci, Co, H, W, K, s, r = case
     d = mk(N, Ci, Co, H, W, K, s, K // 2, r=r, dtype=dtype)
@@ -589,6 +600,7 @@ WIDE_BAND_CASES = [
 @pytest.mark.parametrize("case", WIDE_BAND_CASES)
 def test_input_gradient_wide_bands(oracle, case, dtype):
     check_filtered(oracle, case, dtype)
+    check_reduced(case, dtype)
     check_codes(oracle, case, dtype)
 
 
@@ -614,6 +626,14 @@ LARGE_CASES = [
 @pytest.mark.parametrize("case", LARGE_CASES)
 def test_large_dense_products(oracle, case):
     check_filtered(oracle, case, "bf16")
+    check_reduced(case, "bf16")
+
+
+# ... on patch rows that need tiles of 128 columns; K of one chunk, of an odd number, with a part left
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", [(2, 40, 24, 9, 140, 1, 1, 2), (1, 72, 96, 5, 255, 3, 1, 2), (2, 65, 113, 7, 210, 1, 1, 3)])
+def test_reduced_input_gradient_of_wide_rows(case, dtype):
+    check_reduced(case, dtype)
 
 
 # N, C_in, C_out, H, W: fp32, slabs of 32 x 32 tiles with one chunk for each wave, one more, two for each, one more, two in all
