@@ -197,7 +197,9 @@ static size_t ws_need(const Geom& g, int op, bool reduced_out) {
     case GF_OP_BWD_WEIGHT:
       return g.r == 1 ? ws_exact(g, true, false) : dense_weight_ok(g) ? ws_dense(g, true, false, false, false) : ws_bwd_weight(g);
     case GF_OP_BWD_INPUT:
-      return g.r == 1 ? ws_exact(g, false, true) : gemm_ok(g) ? std::max(ws_dense(g, false, true, false, false), ws_dense(g, false, true, true, false)) : ws_bwd_input(g, reduced_out);
+      if (g.r == 1) return ws_exact(g, false, true);
+      if (gemm_ok(g)) return std::max(ws_dense(g, false, true, false, false), ws_dense(g, false, true, true, false));
+      return std::max<size_t>(ws_bwd_input(g, reduced_out), 256);
     default:
       return ws_exact_any(g);
   }

@@ -810,6 +810,9 @@ hipError_t launch_gf_bwd_weight(const Geom& g, const void* x_u, const void* gy_u
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 size_t ws_bwd_input(const Geom& g, bool reduced_out) {
+  // Large layers on planes of few patches, near the line to the launch of both products: no more than that takes, the rounded kernel
+  // sums (g_x is written in place).
+  if (apart_ok(g) && g.P < 512) return g.KK > 1 ? align256((size_t)g.Co * g.Ci * g.b) : 0;
   size_t wsum = align256((size_t)g.Co * g.Cg * sizeof(float));
   if (is_depthwise(g) || reduced_out) return wsum;
   if (g.g == 1) return wsum + (size_t)g.N * g.Ci * g.P * g.b;

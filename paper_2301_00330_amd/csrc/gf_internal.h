@@ -266,6 +266,7 @@ bool mfma_dgrad_writes_full(const Geom& g);
 // gradient gy_u; g_w or g_x may be null to skip that gradient; gy_u_out (nullable) receives the filtered gradient.
 // own_gyu: gy_u lives in the workspace (src is g_y and the caller wants no gy_u).
 bool gemm_ok(const Geom& g);
+bool apart_ok(const Geom& g);   // large bf16 layers that it leaves to kernels of their own
 bool gemm_maps_ok(const Geom& g);
 bool dense_ok(const Geom& g);
 bool dense_weight_ok(const Geom& g);   // ... the layers whose weight gradient alone it takes

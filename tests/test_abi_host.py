@@ -93,6 +93,8 @@ def test_one_call_backward_within_the_static_scratch(lib):
     ((185, 256, 3488, 10, 76, 1, 8), (28573696, 5466112, 59851008, 34039808)),
     ((1, 896, 2752, 49, 156, 3, 2), (29589504, 13357568, 53679872, 42947072)),
     ((6, 640, 3432, 28, 43, 3, 2), (26357760, 11151360, 50193920, 37509120)),
+    ((220, 1024, 728, 16, 16, 1, 2), (23855104, 256, 44355584, 23855104)),          # kernels of their own, planes of few patches
+    ((64, 1096, 1024, 16, 32, 3, 2), (35913728, 2244608, 54935552, 38158336)),
 ])
 def test_large_bf16_layers_keep_their_workspace(lib, layer, most):
     """Both products in one launch take no more workspace than the kernels of their own: no call is refused that was not, nor are

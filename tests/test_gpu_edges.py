@@ -616,10 +616,14 @@ def test_input_gradient_run_ends(oracle, case, dtype):
 LARGE_CASES = [
     (128, 768, 768, 13, 13, 1, 1, 2),  # cut patches, 49 to a plane
     (25, 640, 256, 64, 48, 1, 1, 2),   # whole patches and vectors, under 8 GFLOP
-    (12, 1024, 432, 64, 48, 1, 1, 2),  # ... past it
+    (12, 1024, 432, 64, 48, 1, 1, 2),  # ... past it, but 512 output channels on the larger tiles
     (12, 1024, 432, 63, 48, 1, 1, 2),  # ... a cut patch row
     (13, 1024, 432, 64, 44, 1, 1, 2),  # ... rows that end inside a vector
     (12, 2048, 224, 64, 48, 3, 1, 2),  # kernel sums
+    (14, 1024, 512, 48, 48, 1, 1, 2),  # kernels of their own
+    (14, 1000, 512, 48, 48, 3, 1, 2),
+    (13, 1024, 512, 48, 48, 1, 1, 2),  # too few tiles for them
+    (220, 1024, 728, 16, 16, 1, 1, 2), # more than 20 GFLOP: on small planes too
 ]
 
 
