@@ -38,6 +38,7 @@
 #include "gf_gemm.h"
 
 #include <algorithm>
+#include <numeric>
 
 namespace gf {
 
@@ -1196,6 +1197,10 @@ long max_shift(const Geom& g, const XGeo& q) {
   return ((a > b ? a : b) / g.s + 1) * (q.Wq + 1);
 }
 
+// K slabs of a layer: kFull as many as are fastest; kSlim no more than take a smaller workspace -- of the input gradient (fp32) from 16
+// steps on only, of the weight gradient fewer beside them.
+enum Form { kFull, kSlim };
+
 struct XPlan {
   bool staged;
   int Cop, Cix;   // channels of a staged row
@@ -1206,16 +1211,10 @@ struct XPlan {
   int qv, nchunks, nz, cpz, w_tm, w_tn, qd, d_tm, d_tn;
 };
 
-// taps of the phase that has most of them
+// taps of the phase that has most of them: taps of one phase are s / gcd(dilation, s) apart
 int most_taps(const Geom& g) {
-  int most[2] = {0, 0};
-  for (int dim = 0; dim < 2; ++dim)
-    for (int ph = 0; ph < g.s; ++ph) {
-      int n = 0;
-      for (int u = 0; u < (dim ? g.Kw : g.Kh); ++u) n += ((long)u * g.dl + ph - g.p) % g.s == 0;
-      most[dim] = std::max(most[dim], n);
-    }
-  return most[0] * most[1];
+  const int step = g.s / std::gcd(g.dl, g.s);
+  return cdiv(g.Kh, step) * cdiv(g.Kw, step);
 }
 
 // Tile sides in units of 64: 128 x 128 where every block slot of the chip has at least eight steps of such tiles (two
@@ -1247,9 +1246,7 @@ int slab_chunks(int nchunks, long z) {
 // 120 x 160, n = 8 (86): 90 -> 65; 128 -> 128, 60 x 80, n = 8 (50): 59 -> 51.
 // 280 layers of all calls that split K (vanilla of both types, bf16 weight gradients of 6 GFLOP and more): 0.89 .. 1.28, mean 1.004.
 bool deal_slabs(int nz) { return 10 * (cdiv(nz, 8) * 8) <= 11 * nz; }
-// few: K slabs of the input gradient by an earlier rule, from 16 steps on only and counted up to the taps of the whole kernel, for a
-// workspace that only those fit
-XPlan plan_of(const Geom& g, bool want_gw, bool want_gx, bool staged, bool few) {
+XPlan make_plan(const Geom& g, bool want_gw, bool want_gx, bool staged, Form form) {
   const XGeo q = make_xgeo(g);
   const int VE = 16 / g.b;
   XPlan p = {};
@@ -1273,7 +1270,7 @@ XPlan plan_of(const Geom& g, bool want_gw, bool want_gx, bool staged, bool few) 
   // of the chip idle.  Weight gradient: as many slabs as the slots the input gradient leaves can take in one go.
   const long d_tiles = (long)p.d_tm * p.d_tn * q.nph, w_tiles = (long)p.w_tm * p.w_tn * g.KK;
   const int taps = cdiv(g.KK, q.nph);                     // per phase, about
-  const int d_steps = taps * cdiv(g.Co, g.b == 2 ? 64 : 32), d_most = (few ? g.KK : most_taps(g)) * cdiv(g.Co, g.b == 2 ? 64 : 32);
+  const int d_steps = taps * cdiv(g.Co, g.b == 2 ? 64 : 32), d_most = most_taps(g) * cdiv(g.Co, g.b == 2 ? 64 : 32);
   p.d_nz = 1;
   // Twice the slabs where a block has 16 steps and more and half the slots take them; fp32, whose steps take twice as long: also from
   // 8 steps on where a quarter of the slots does, from 4 where an eighth does.  Both gradients in us, 16 steps / this rule: 256 -> 88, 3 x 3,
@@ -1281,10 +1278,12 @@ XPlan plan_of(const Geom& g, bool want_gw, bool want_gx, bool staged, bool few) 
   // that change 1.18 times as fast in the mean, 0.96 at the least.  With 8 steps up to half the slots: 64 -> 32, 25 x 25, n = 19 33 / 40.
   // bf16 from 8 steps on where a sixteenth takes them: 41 layers 1.05 in the mean, but ten of them 0.88 - 0.95; not taken.  Nor under
   // 16 output channels, whose steps are mostly padding: 8 of 4 x 4, n = 2 would bring 128 KB of slabs to 3 KB of tensors.
-  auto worth = [&](int steps, long blocks) {
-    return (steps >= 16 && blocks <= slots / 2) || (g.b == 4 && !few && g.Co >= 16 && ((steps >= 8 && blocks <= slots / 4) || (steps >= 4 && blocks <= slots / 8)));
-  };
+  auto worth = [&](int steps, long blocks) { return steps >= 16 && blocks <= slots / 2; };
+  auto worth_f32 = [&](int steps, long blocks) { return (steps >= 8 && blocks <= slots / 4) || (steps >= 4 && blocks <= slots / 8); };
   while (p.d_nz < 64 && worth(d_steps / p.d_nz, d_tiles * p.d_nz * 2)) p.d_nz *= 2;
+  const int nz16 = p.d_nz;
+  if (form == kFull && g.b == 4 && g.Co >= 16)
+    while (p.d_nz < 64 && (worth(d_steps / p.d_nz, d_tiles * p.d_nz * 2) || worth_f32(d_steps / p.d_nz, d_tiles * p.d_nz * 2))) p.d_nz *= 2;
   p.d_its = p.d_nz == 1 ? d_most : cdiv(d_steps, p.d_nz);
   // phases with more taps than the average need more slabs (counted up to the taps of the whole kernel, most of them were
   // empty: 208 -> 104, 5 x 5, 20 x 20, stride 2, n = 10, fp32 98 -> 56 us; 152 -> 488, 10 x 10, n = 12, bf16 47 -> 36)
@@ -1293,7 +1292,12 @@ XPlan plan_of(const Geom& g, bool want_gw, bool want_gx, bool staged, bool few) 
   p.ntickets = p.d_nz > 1 ? (int)(d_tiles * (1 + p.d_ngrp)) : 0;
   // Both products at once where the slots the input gradient leaves take the weight gradient with blocks of about its
   // length; else several rounds, with weight-gradient blocks of about half the launch.
-  const long d_blocks = d_tiles * p.d_nz, d_len = p.d_nz == 1 ? d_steps : p.d_its;
+  // (kSlim counts the blocks of the input gradient up to the taps of the whole kernel: fewer slabs are left for g_w)
+  long d_blocks = d_tiles * p.d_nz, d_len = p.d_nz == 1 ? d_steps : p.d_its;
+  if (form != kFull) {
+    d_len = cdiv(d_steps, nz16);
+    d_blocks = d_tiles * (nz16 == 1 ? 1 : cdiv(g.KK * cdiv(g.Co, g.b == 2 ? 64 : 32), (int)d_len));
+  }
   const long per_slot = (w_tiles * p.nchunks + d_blocks * d_len) / slots;
   long z = (slots - d_blocks) / w_tiles;
   if (z < 1 || cdiv(p.nchunks, z) > 1.2 * std::max(d_len, per_slot)) z = cdiv(p.nchunks, std::max(per_slot / 2, 8L));
@@ -1333,13 +1337,18 @@ XPlan plan_of(const Geom& g, bool want_gw, bool want_gx, bool staged, bool few) 
   p.total = off;
   return p;
 }
-// few also where only that keeps both gradients within the library's own scratch, whatever this call asks for (the one-call entry
-// returns the same bits with either)
-XPlan make_plan(const Geom& g, bool want_gw, bool want_gx, bool staged, bool few = false) {
-  if (!staged && !few)
-    few = plan_of(g, true, true, false, false).total > GF_STATIC_SCRATCH_BYTES &&
-          plan_of(g, true, true, false, true).total <= GF_STATIC_SCRATCH_BYTES;
-  return plan_of(g, want_gw, want_gx, staged, few);
+size_t plan_bytes(const Geom& g, bool want_gw, bool want_gx, bool staged, Form form) { return make_plan(g, want_gw, want_gx, staged, form).total; }
+// The form a call on the maps themselves takes with all the workspace it asks for: kSlim where only that keeps both gradients within the library's own
+// scratch.  The one-call entry, which returns the same bits there, and in fp32, where the slabs of g_x differ, all others whatever
+// they ask for.  Layers that cannot come near it are not planned twice: an upper bound of the weight-gradient slabs (a slab has four
+// chunks), the repacked tensors and half the block slots' tiles of g_x.
+Form form_of(const Geom& g) {
+  if (g.b == 2 && !g.own_scratch) return kFull;
+  const XGeo q = make_xgeo(g);
+  const double wel = (double)g.KK * g.Co * (g.Ci + 7), slabs = 4 + (double)g.N * up8(q.PY) * g.b / (4 * 128);
+  const double tiles = 27e6 * most_taps(g) / cdiv(g.KK, q.nph);
+  if (4 * wel * (1 + slabs) + 8. * q.nph * g.N * g.Ci * q.PQ + (double)g.KK * (q.PY + q.nph * (q.PQ + 64)) + tiles <= GF_STATIC_SCRATCH_BYTES) return kFull;
+  return plan_bytes(g, true, true, false, kFull) > GF_STATIC_SCRATCH_BYTES && plan_bytes(g, true, true, false, kSlim) <= GF_STATIC_SCRATCH_BYTES ? kSlim : kFull;
 }
 
 // planes a block of the interleave stages: a multiple of VE (runs start on vector boundaries), about 16 KB, and
@@ -1375,8 +1384,8 @@ bool staged_ok(const Geom& g, bool want_gx) {
   if (g.s == 1 && g.Co > 64 && g.Ci > 64 && (long)g.KK * g.Co * g.Ci <= 800L * (g.Co + g.Ci) &&
       ((long)g.N * q.PY * g.Co + (long)g.N * g.H * g.W * g.Ci) * 2 >= (64L << 20) && !(want_gx && q.PY % 8 == 0))
     return false;
-  return !g.own_scratch || make_plan(g, true, true, true).total <= GF_STATIC_SCRATCH_BYTES ||
-         make_plan(g, true, true, false).total > GF_STATIC_SCRATCH_BYTES;
+  return !g.own_scratch || plan_bytes(g, true, true, true, kFull) <= GF_STATIC_SCRATCH_BYTES ||
+         plan_bytes(g, true, true, false, form_of(g)) > GF_STATIC_SCRATCH_BYTES;
 }
 
 // the product launch and the last one (x: the map itself or its phase planes; staged layers: in the workspace)
@@ -1453,13 +1462,12 @@ hipError_t implicit_products(const Geom& g, const XGeo& q, const XPlan& p, const
 
 template <class T>
 hipError_t implicit_t(const Geom& g, const void* x, const void* w, const void* g_y, float* g_w, void* g_x,
-                      void* ws, bool staged, bool few, hipStream_t st) {
+                      void* ws, const XPlan& p, hipStream_t st) {
   const bool want_gw = g_w != nullptr, want_gx = g_x != nullptr;
   const XGeo q = make_xgeo(g);
-  const XPlan p = make_plan(g, want_gw, want_gx, staged, few);
   constexpr int VE = El<T>::VE;
   char* wsb = static_cast<char*>(ws);
-  if (staged) {
+  if (p.staged) {
     StageArgs t = {};
     t.taps = want_gx ? reinterpret_cast<int4*>(wsb + p.off_taps) : nullptr;
     t.ntap = reinterpret_cast<int*>(wsb + p.off_taps + sizeof(int4) * (size_t)q.nph * g.KK);
@@ -1588,38 +1596,57 @@ static bool plain_pointwise(const Geom& g, Geom* e) {
   return gemm_maps_ok(*e);
 }
 
+// The forms of a call, best first: f(staged, form) of each until it returns true
+template <class F>
+static void each_form(const Geom& g, bool want_gx, F&& f) {
+  const bool staged = staged_ok(g, want_gx);
+  if (staged && f(true, kFull)) return;
+  const Form form = form_of(g);
+  if (f(false, form) || (form == kFull && f(false, kSlim))) return;
+  if (staged) f(true, kSlim);
+}
+
 size_t ws_implicit(const Geom& g, bool want_gw, bool want_gx) {
   Geom e;
   if (plain_pointwise(g, &e)) return pointwise_ok(e) ? ws_pointwise(e, want_gw) : ws_dense(e, want_gw, want_gx, true, false);
-  return make_plan(g, want_gw, want_gx, staged_ok(g, want_gx)).total;
+  size_t total = 0;
+  each_form(g, want_gx, [&](bool staged, Form form) {
+    total = plan_bytes(g, want_gw, want_gx, staged, form);
+    return true;
+  });
+  return total;
 }
 
-// Layers of the one pass over the maps take the two products, layers on staged operands the maps themselves, and fp32 layers of few
-// tiles fewer slabs, with a workspace that only those fit: the copies are many times the rest (512 -> 512, 30 x 40, n = 128: 357 MB and 42).
+// Layers of the one pass over the maps take the two products, layers on staged operands the maps themselves, and layers whose K is cut into
+// many slabs fewer, with a workspace that only those fit: the copies are many times the rest (512 -> 512, 30 x 40, n = 128: 357 MB and 42).
 size_t ws_implicit_least(const Geom& g, bool want_gw, bool want_gx) {
   Geom e;
   if (plain_pointwise(g, &e)) return std::min(ws_implicit(g, want_gw, want_gx), ws_dense(e, want_gw, want_gx, true, false));
-  const size_t least = std::min(ws_implicit(g, want_gw, want_gx), make_plan(g, want_gw, want_gx, false, true).total);
-  return staged_ok(g, want_gx) ? std::min(least, make_plan(g, want_gw, want_gx, true, true).total) : least;
+  size_t least = ~(size_t)0;
+  each_form(g, want_gx, [&](bool staged, Form form) {
+    least = std::min(least, plan_bytes(g, want_gw, want_gx, staged, form));
+    return false;
+  });
+  return least;
 }
 
 // g_w and / or g_x (either may be null): one set-up launch, then the GEMM launches
 hipError_t launch_implicit(const Geom& g, const void* x, const void* w, const void* g_y, float* g_w, void* g_x,
                            void* ws, size_t ws_bytes, hipStream_t st) {
   Geom e;
-  const bool all = ws_bytes >= ws_implicit(g, g_w != nullptr, g_x != nullptr);
+  const bool gw = g_w != nullptr, gx = g_x != nullptr;
   if (plain_pointwise(g, &e)) {
-    if (pointwise_ok(e) && all) return launch_pointwise(e, g_y, x, w, g_w, g_x, ws, st);
+    if (pointwise_ok(e) && ws_bytes >= ws_implicit(g, gw, gx)) return launch_pointwise(e, g_y, x, w, g_w, g_x, ws, st);
     return launch_dense(e, g_y, false, x, w, nullptr, g_w, g_x, true, nullptr, ws, st);
   }
-  const bool gw = g_w != nullptr, gx = g_x != nullptr;
-  bool staged = all && staged_ok(g, gx), few = false;
-  if (!all && ws_bytes < make_plan(g, gw, gx, false).total) {
-    few = true;
-    staged = ws_bytes < make_plan(g, gw, gx, false, true).total;   // (then the staged form of few slabs is the smallest)
-  }
-  return g.dtype == GF_BF16 ? implicit_t<bf16_t>(g, x, w, g_y, g_w, g_x, ws, staged, few, st)
-                            : implicit_t<float>(g, x, w, g_y, g_w, g_x, ws, false, few, st);
+  hipError_t rc = hipErrorInvalidValue;   // (a workspace under ws_implicit_least: the entries refuse it)
+  each_form(g, gx, [&](bool staged, Form form) {
+    const XPlan p = make_plan(g, gw, gx, staged, form);
+    if (ws_bytes < p.total) return false;
+    rc = g.dtype == GF_BF16 ? implicit_t<bf16_t>(g, x, w, g_y, g_w, g_x, ws, p, st) : implicit_t<float>(g, x, w, g_y, g_w, g_x, ws, p, st);
+    return true;
+  });
+  return rc;
 }
 
 }  // namespace gf

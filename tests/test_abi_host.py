@@ -428,6 +428,47 @@ def test_pool_batch_q8_needs_step_sizes(lib):
             T.pool_activation_batch_q8(descs, [None] * len(descs), None)
 
 
+# (N, C_in, C_out, H, W, K, stride, r, dtype, op), at most this many times the query of a layer that needs no plan
+PLANNED = [
+    ((2, 256, 88, 6, 6, 3, 1, 1, 0, 2), 3.9),       # vanilla, few tiles
+]
+
+
+def test_planning_is_short(tmp_path):
+    """A call plans its layer two or three times: beside kernels of 10 us that is not to be seen.  Queries in a loop, the fastest of
+    many rounds, against the same of a pointwise layer."""
+    import subprocess
+    src = tmp_path / "t.cpp"
+    rows = ", ".join("{%s}" % ", ".join(map(str, l)) for l, _ in [((32, 24, 144, 56, 56, 1, 1, 1, 0, 2), 1)] + PLANNED)
+    src.write_text("""
+#include <chrono>
+#include <cstdio>
+#include "gf.h"
+int main() {
+  const int l[][10] = {%s};
+  for (auto& v : l) {
+    gf_conv_desc d = {sizeof d, v[0], v[1], v[2], v[3], v[4], v[5], v[5], v[6], v[5] / 2, 1, 1, v[7], v[8]};
+    size_t bytes;
+    double best = 1e9;
+    for (int r = 0; r < 400; ++r) {
+      const auto t = std::chrono::steady_clock::now();
+      for (int k = 0; k < 200; ++k) if (gf_workspace_bytes(&d, v[9], &bytes) != GF_OK) return 1;
+      const double ns = std::chrono::duration<double, std::nano>(std::chrono::steady_clock::now() - t).count() / 200;
+      if (ns < best) best = ns;
+    }
+    std::printf("%%.1f\\n", best);
+  }
+}
+""" % rows)
+    lib_dir = os.path.dirname(B.LIB_PATH)
+    exe = tmp_path / "t"
+    subprocess.run(["g++", "-O2", "-std=c++17", "-I" + os.path.join(ROOT, "include"), str(src), "-o", str(exe), "-L" + lib_dir, "-lgf",
+                    "-Wl,-rpath," + lib_dir, "-Wl,--allow-shlib-undefined"], check=True)
+    base, *rest = map(float, subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split())
+    for (layer, limit), ns in zip(PLANNED, rest):
+        assert ns <= limit * base, (layer, ns, base)
+
+
 @pytest.mark.parametrize("dtype,b", [(0, 4), (1, 2)])
 def test_strided_vanilla_layers_take_no_column_tensor(lib, dtype, b):
     """Vanilla BP of strided layers on large maps: phase planes of x and g_x and K slabs, not K_h K_w copies of a map."""

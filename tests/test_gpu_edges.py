@@ -323,6 +323,7 @@ def test_vanilla_input_gradient_of_few_tiles(oracle, case, dtype):
     ((2, 256, 88, 6, 6, 3, 1, 1, "f32"), (2016256, 812032, 1205248)),     # fewer slabs of few tiles
     ((10, 52, 26, 20, 20, 5, 2, 2, "f32"), (2748928, 1781504, 970496)),
     ((18, 445, 179, 5, 20, 5, 2, 2, "bf16"), (53734144, 9790464, 44154624)),
+    ((10, 59, 967, 14, 28, 3, 2, 1, "bf16"), (13948160, 4572672, 9377536)),   # neither staged nor fewer slabs
 ])
 def test_vanilla_layers_with_less_workspace(oracle, case, least):
     """Staged operands and the one pass over the maps: a call whose workspace holds what the unstaged form or the two products need,
@@ -353,10 +354,12 @@ def test_vanilla_layers_with_less_workspace(oracle, case, least):
         while hi - lo > 1:
             mid = (lo + hi) // 2
             lo, hi = (lo, mid) if call(mid, a, b) is not None else (mid, hi)
+        full = call(ws.numel() - 4096, a, b)
         for n in (hi, most):
             g_w, g_x = call(n, a, b)
             assert not a or rel_err(g_w, r_w) <= TOL[dtype]
             assert not b or rel_err(g_x, r_x) <= TOL[dtype]
+            assert not b or dtype == "f32" or torch.equal(g_x, full[1])   # (fp32: fewer slabs, or the products instead of the one pass)
 
 
 # N, C, H, W, K, padding: both gradients of a depthwise layer in one pass (ragged groups of pixels, frames, image runs)
