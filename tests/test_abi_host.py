@@ -431,6 +431,7 @@ def test_pool_batch_q8_needs_step_sizes(lib):
 # (N, C_in, C_out, H, W, K, stride, r, dtype, op), at most this many times the query of a layer that needs no plan
 PLANNED = [
     ((2, 256, 88, 6, 6, 3, 1, 1, 0, 2), 3.9),       # vanilla, few tiles
+    ((8, 2048, 256, 65, 65, 1, 1, 2, 1, 3), 2.2),   # filtered, wide bands
 ]
 
 
