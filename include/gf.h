@@ -49,7 +49,9 @@
  *  - Dilation only affects H_y and the exact entry: the filtered formulas read
  *    the tap's own padded patch wherever it lands (Supp. B "Boundary Elements").
  *  - Results are deterministic: no floating-point atomics, so two calls on the
- *    same inputs give bit-identical outputs.
+ *    same inputs give bit-identical outputs.  Some vanilla layers are also taken
+ *    with less workspace than gf_workspace_bytes names, in a form that needs less:
+ *    the results of that form differ in the order of the fp32 sums.
  */
 #ifndef GF_H
 #define GF_H

@@ -1619,6 +1619,7 @@ size_t ws_implicit(const Geom& g, bool want_gw, bool want_gx) {
 
 // Layers of the one pass over the maps take the two products, layers on staged operands the maps themselves, and layers whose K is cut into
 // many slabs fewer, with a workspace that only those fit: the copies are many times the rest (512 -> 512, 30 x 40, n = 128: 357 MB and 42).
+// Either changes the order of the sums: of g_w, and in fp32 of g_x (bf16: the slabs of g_x are the same in all forms).
 size_t ws_implicit_least(const Geom& g, bool want_gw, bool want_gx) {
   Geom e;
   if (plain_pointwise(g, &e)) return std::min(ws_implicit(g, want_gw, want_gx), ws_dense(e, want_gw, want_gx, true, false));
