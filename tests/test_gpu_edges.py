@@ -588,7 +588,7 @@ def test_few_tile_input_gradient(oracle, case, dtype):
     assert torch.equal(torch.isfinite(g_x.cpu()), torch.isfinite(torch.from_numpy(oracle.bwd_input(odesc(oracle, d), to64(gyu), to64(w)))))
 
 
-# N, C_in, C_out, H, W, K, stride, r: input gradients on bands of three and five patch rows in tiles of 128 columns, and just not
+# N, C_in, C_out, H, W, K, stride, r: input gradients on bands of three, five and more patch rows in tiles of 128 columns, and just not
 WIDE_BAND_CASES = [
     (4, 768, 24, 65, 65, 1, 1, 2),
     (4, 705, 17, 66, 83, 3, 1, 2),     # 42 patch columns: two left over; one row of c_i in the last tile
@@ -596,6 +596,9 @@ WIDE_BAND_CASES = [
     (26, 200, 40, 49, 50, 1, 1, 2),    # 25 patch columns
     (4, 700, 24, 65, 65, 1, 1, 2),     # a tile row less than fills the chip
     (4, 768, 24, 65, 85, 1, 1, 2),     # 43 patch columns: two rows
+    (128, 200, 40, 18, 25, 3, 1, 2),   # nine rows of 13: one band, three of 64 columns
+    (103, 270, 33, 13, 34, 1, 1, 2),   # seven of 17
+    (15, 440, 64, 50, 46, 1, 1, 2),    # 25 of 23: five bands, thirteen
 ]
 
 
