@@ -185,7 +185,8 @@ __device__ __forceinline__ void add_products(const uint4 (&fa)[3], const uint4 (
 }
 
 // Matrix step ks of a chunk, all tiles.  fp32: the term products are summed from zero -- those of a whole chunk of 32 k
-// for a single tile, of 16 k otherwise (a sum per tile would not fit the registers) -- and then added to the accumulator
+// for a single tile, of 16 k otherwise (a sum per tile would not fit the registers; two tiles of a filtered input gradient are taken
+// one after the other instead, d_mainloop of gf_dense.hip) -- and then added to the accumulator
 // with one rounding; straight into the accumulator they would round it 24 times per chunk.  And the instruction takes
 // the sum of eight products down to a multiple of about 2^-23 of the largest one, towards minus infinity: with 35e6
 // products per output every weight gradient came out 0.4 below values of 5e3.  So every other chunk is multiplied with
